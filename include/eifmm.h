@@ -72,7 +72,8 @@ extern "C" {
                              not symmetric, so two EIMs per level (Sec. 3.1)     */
 
 /* precision of the pass */
-#define EIFMM_PREC_FP64 0  /* every step in FP64                                   */
+#define EIFMM_PREC_FP64 0  /* every step in FP64 (the M2L as exact products of the
+                              8-bit digits of its FP64 operands, summed in FP64)  */
 #define EIFMM_PREC_MIXED 1 /* M2L on FP32 MFMA (FP32 products, each offset's
                               contribution added in FP64); P2P with FP64
                               coordinate differences, FP32 kernel values and
@@ -341,8 +342,8 @@ int eifmm_batch_create(const eifmm_config *cfgs, int32_t nprob, eifmm_batch *out
  * eifmm_set_points).  At the first call, a problem with depth -1 gets, among
  * the depths around log8(n_p / 32) (at most 4 of them, within 2..8), the one
  * whose evaluation runs fastest here; later calls keep it.  The first call also
- * times the fused M2L launch with tiles of 3, 4, 5 and 6 MFMA row blocks and keeps
- * the fastest.  Drops the captured graph.  Errors as eifmm_set_points; after
+ * times the fused M2L launch with tiles of 3, 4, 5 and 6 MFMA row blocks (FP64: 3, 4
+ * and 6) and keeps the fastest.  Drops the captured graph.  Errors as eifmm_set_points; after
  * an error the batch must get points again before evaluating. */
 int eifmm_batch_set_points(eifmm_batch b, const double *const *xyz, void *stream);
 

@@ -176,8 +176,11 @@ int setup_tables(eifmm_plan h) {
     if (mixed) {
       std::vector<float> f32(H.kfrag.begin(), H.kfrag.end());
       TRY(upload(&D.kfrag32, f32.data(), f32.size(), tr));
-    } else {
-      TRY(upload(&D.kfrag, H.kfrag.data(), H.kfrag.size(), tr));
+    } else if (P.shared_tables || H.sp2.empty()) {
+      const int dm = H.r > 0 ? H.rp : H.dpB, dk = H.r > 0 ? H.rp : H.dp;
+      TRY(dalloc(&D.k8, (size_t)kNumOffsets * dm * digit_bytes(dk), tr));
+      TRY(dalloc(&D.rscale, (size_t)dm, tr));
+      TRY(upload_digit_operators(H.kfrag, dm, dk, D.k8, D.rscale));
     }
     std::vector<double>().swap(H.kfrag);
     for (int q = 0; q < 4; ++q) TRY(upload(&D.tri[q], H.tri[q].data(), H.tri[q].size(), tr));
@@ -292,6 +295,11 @@ int setup_workspaces(eifmm_plan h, double *shared_ws) {
       if (mixed) TRY(dalloc(&D.Whp32, mr, tr));
     } else if (mixed) {
       TRY(dalloc(&D.Wh32, m, tr));
+    }
+    if (!mixed && !uses_m2l2(P, k)) {
+      const int dk = P.lh[k].r > 0 ? P.lh[k].rp : P.lh[k].dp;
+      TRY(dalloc(&D.w8, D.cap * (size_t)R * digit_bytes(dk), tr));
+      TRY(dalloc(&D.wscale, D.cap * (size_t)R, tr));
     }
     // g and l have the second EIM's size (the first's with one EIM)
     const size_t mb = D.cap * (size_t)R * (size_t)P.lh[k].dpB;
@@ -413,7 +421,8 @@ int shared_plan(eifmm_batch b, int p, int depth, eifmm_plan *out) {
     H.rp = TH.rp;
     LevelDev &D = P.ld[k];
     const LevelDev &TD = T.ld[k];
-    D.kfrag = TD.kfrag;
+    D.k8 = TD.k8;
+    D.rscale = TD.rscale;
     D.kfrag32 = TD.kfrag32;
     D.m2m = TD.m2m;
     D.l2l = TD.l2l;
@@ -1128,13 +1137,14 @@ int eifmm_batch_set_points(eifmm_batch b, const double *const *xyz, void *stream
     double best = 0;
     int pick = 6;
     for (int rbt = 3; rbt <= 6 && !st; ++rbt) {
+      if (rbt == 5 && !b->ex.mixed) continue;  // no FP64 tile of 5 blocks
       if ((st = prepare(b, rbt))) break;
       batch_run_m2l(b->ex, s);
       hipEventRecord(e0, s);
       for (int rep = 0; rep < 3; ++rep) batch_run_m2l(b->ex, s);
       hipEventRecord(e1, s);
       const double ms = elapsed_ms(e0, e1);
-      if (rbt == 4 || ms < best) {
+      if (rbt == 3 || ms < best) {
         best = ms;
         pick = rbt;
       }

@@ -60,6 +60,20 @@ __device__ inline void lds_barrier() {
 // index along axis a (0 = x, 1 = y, 2 = z) of a Morton key
 __host__ __device__ inline uint32_t morton_axis(uint32_t key, int a) { return compact3(key >> a); }
 
+// last m in [0, n) with key(m) <= v (0 if there is none; key ascending)
+template <typename F>
+__device__ inline int find_last_le(int n, int64_t v, F key) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (key(mid) <= v)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  return lo;
+}
+
 // Exclusive prefix sums over n entries (in may equal out); tmp needs
 // (n + 1023) / 1024 + 1 ints.  Enqueued on stream s.
 void scan_exclusive_i32(const int *in, int *out, int64_t n, int *tmp, hipStream_t s);

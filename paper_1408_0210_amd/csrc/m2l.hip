@@ -1,0 +1,765 @@
+// m2l.hip -- the FP64 M2L (Algorithm 3 step 4) on the int8 matrix cores.
+//
+// C[:, col] = sum over the 189 offsets o of the column's child class of A_o b(o, col),
+// A_o the K^delta or C^delta of the level and b the source expansion at that offset.
+// The FP64 MFMA runs at 1/56 of the int8 one on gfx950 (75 TFLOP/s against 4.0 POP/s
+// measured), so every operand is split into 7 signed 8-bit digits (56 bits) and the
+// product is summed from the digit products, which are exact in 32-bit integers:
+//   a = 2^ea sum_i da_i 256^-(i+1),  b = 2^eb sum_j db_j 256^-(j+1),  -128 <= d <= 127,
+//   sum_k a_k b_k = 2^(ea + eb - 16) sum_s 256^-s S_s,  S_s = sum_{i+j=s} sum_k da_ik db_jk.
+// One exponent per operator row (of the level) and one per source column.  Digit
+// pairs with i + j > 6 lie below 2^-56 of the largest product and are left out: 28
+// products instead of 49.  The seven sums S_s of an offset are joined and scaled in
+// FP64 and added to an FP64 sum over the offsets.  Measured against an 80-bit
+// evaluation with the operators and sources of the pass (tau 1e-6, random boxes): 1/r
+// at rank 128 1.1e-15 relative against 5.3e-15 for the chain of FP64 FMAs, e^-r/r
+// 0.8e-15 / 3.9e-15, cos(20 r)/r 1.1e-15 / 6.9e-15, 1/r uncompressed (d = 287) 0.6e-15 /
+// 8.0e-15, e^(-r^2 / 0.01) 7.5e-15 / 8.0e-15.
+//
+// Time of the launch against tiles of FP64 MFMAs: 2.49 ms against 3.96 on 1e6 uniform
+// points (1/r, rank 128, levels 2..5), 2.05 against 2.88 on 2e5 points uncompressed
+// (d = 287, levels 2..4), 0.38 against 0.67 on 2000 points (d = 287, levels 2 and 3).
+// The matrix cores are busy half of the time (1.73e8 products of 16 cycles); copies that
+// load nothing take 1.51 ms and copies that load one operator and no sources (always in
+// L2) 2.07, so what bounds it is the way through LDS (84 KB in and 280 KB out per chunk
+// and CU, 2850 cycles at 128 bytes, beside 3584 of products) and the fabric's latency.
+#include <algorithm>
+#include <climits>
+#include <cmath>
+#include <type_traits>
+#include <vector>
+
+#include "devutil.hpp"
+#include "plan.hpp"
+
+namespace eifmm {
+
+namespace {
+
+typedef int i4v __attribute__((ext_vector_type(4)));
+constexpr int ND = kDigits;  // digits of an operand
+constexpr int kFrag = 1024;  // bytes of one 16 x 64 operand fragment (64 lanes x 16)
+
+// zeros, read in place of a missing source column (7 digits of 1024 elements) and,
+// as a double, of its scale; the slot of a missing source
+__device__ i4v g_digit_zero[7 * 1024 / 16];
+__device__ int g_no_slot = -1;
+
+// the exponent e of the smallest power of two with m 2^-e <= 0.498, so that the top
+// digit of every |x| <= m stays within [-127, 127]; m > 0 and finite
+__device__ inline int digit_exponent(double m) {
+  int e;
+  const double f = frexp(m, &e);  // f in [0.5, 1)
+  return e + 1 + (f > 0.996 ? 1 : 0);
+}
+
+// the digits of x 2^-e, most significant first
+__device__ inline void digits_of(double x, int e, int8_t (&d)[ND]) {
+  long long q = __double2ll_rn(ldexp(x, 8 * ND - e));
+#pragma unroll
+  for (int s = ND - 1; s >= 0; --s) {
+    d[s] = (int8_t)(q & 255);
+    q = (q - d[s]) >> 8;
+  }
+}
+
+// largest |entry| of each operator row over all offsets, as the bits of a double
+// (the table in FP64 fragment order, setup.cpp: lane l of a fragment holds row l % 16)
+__global__ __launch_bounds__(256) void k_op_rowmax(const double *__restrict__ frag, int nrb,
+                                                   int nks, unsigned long long *__restrict__ mx) {
+  const int rb = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double m = 0.0;
+  for (int o = blockIdx.y; o < kNumOffsets; o += gridDim.y)
+    for (int ks = w; ks < nks; ks += 4)
+      m = fmax(m, fabs(frag[(((size_t)o * nrb + rb) * nks + ks) * 64 + lane]));
+  m = fmax(m, __shfl_xor(m, 16));
+  m = fmax(m, __shfl_xor(m, 32));
+  if (lane < 16) atomicMax(&mx[16 * rb + lane], (unsigned long long)__double_as_longlong(m));
+}
+
+// the operators' digit fragments: [offset][row block][64-k chunk][digit][lane][16 k],
+// lane l holding row l % 16 and k = 16 (l / 16) .. + 15 of the chunk; one block of 64
+// lanes per (offset, row block, chunk)
+__global__ __launch_bounds__(64) void k_op_digits(const double *__restrict__ frag, int nrb, int nks,
+                                                  int nkc,
+                                                  const unsigned long long *__restrict__ mx,
+                                                  int8_t *__restrict__ out) {
+  const int lane = threadIdx.x;
+  const int kc = blockIdx.x % nkc, rb = (blockIdx.x / nkc) % nrb, o = blockIdx.x / (nkc * nrb);
+  const double m = __longlong_as_double((long long)mx[16 * rb + (lane & 15)]);
+  const int e = m > 0.0 && m < INFINITY ? digit_exponent(m) : 0;
+  const int c16 = kc * 4 + (lane >> 4);  // 16-column chunk of the table
+  union {
+    int8_t b[16];
+    i4v v;
+  } dig[ND];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    double x = 0.0;
+    if (4 * c16 < nks)
+      x = frag[(((size_t)o * nrb + rb) * nks + 4 * c16 + (k & 3)) * 64 + 16 * (k >> 2) +
+               (lane & 15)];
+    int8_t d[ND] = {0, 0, 0, 0, 0, 0, 0};
+    if (m < INFINITY) digits_of(x, e, d);
+#pragma unroll
+    for (int s = 0; s < ND; ++s) dig[s].b[k] = d[s];
+  }
+#pragma unroll
+  for (int s = 0; s < ND; ++s)
+    *(i4v *)(out + ((size_t)blockIdx.x * ND + s) * kFrag + 16 * lane) = dig[s].v;
+}
+
+// scale of each operator row: value = scale * (source scale) * sum_s 256^-s S_s
+__global__ void k_op_scale(const unsigned long long *__restrict__ mx, int rows,
+                           double *__restrict__ scale) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= rows) return;
+  const double m = __longlong_as_double((long long)mx[r]);
+  scale[r] = !(m < INFINITY) ? (double)INFINITY : m > 0.0 ? ldexp(1.0, digit_exponent(m) - 16) : 0.0;
+}
+
+// Source columns into digits: 16 lanes per column, 4 consecutive k per lane and
+// 64-k chunk; out: [column][chunk][digit][64 k] bytes, scale: one power of two per
+// column (0 for a zero column, NaN for one holding an infinity or a NaN).  The digits
+// are those of the column with its first entry that is not zero made positive, and the
+// scale carries the sign: the digits of x and -x differ otherwise (a digit of -128 has
+// no counterpart), and a pass of -sigma would not be exactly the negative one.
+// Bound by memory (8 bytes read and 7 written per element).
+__device__ inline void digit_column(const DigitDesc &D, int col) {
+  const int li = threadIdx.x & 15;
+  const double *in = D.in + (int64_t)col * D.ld;
+  const int nkc = D.kp >> 6;
+  double m = 0.0;
+  bool bad = false;
+  int first = INT_MAX;  // 2 k + (entry k < 0) of the first entry that is not zero
+  for (int kc = 0; kc < nkc; ++kc) {
+    const int k = 64 * kc + 4 * li;
+    if (k < D.ld) {
+      const d2v a = ldg((const d2v *)(in + k)), b = ldg((const d2v *)(in + k + 2));
+      const double v[4] = {a.x, a.y, b.x, b.y};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        bad = bad || !(fabs(v[q]) < INFINITY);
+        m = fmax(m, fabs(v[q]));
+        if (v[q] != 0.0) first = min(first, 2 * (k + q) + (v[q] < 0.0 ? 1 : 0));
+      }
+    }
+  }
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) {
+    m = fmax(m, __shfl_xor(m, o));
+    bad = __shfl_xor((int)bad, o) || bad;
+    first = min(first, __shfl_xor(first, o));
+  }
+  const bool use = !bad && m > 0.0, neg = use && (first & 1);
+  const int e = use ? digit_exponent(m) : 0;
+  for (int kc = 0; kc < nkc; ++kc) {
+    const int k = 64 * kc + 4 * li;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    if (use && k < D.ld) {
+      const d2v a = ldg((const d2v *)(in + k)), b = ldg((const d2v *)(in + k + 2));
+      v[0] = a.x;
+      v[1] = a.y;
+      v[2] = b.x;
+      v[3] = b.y;
+    }
+    uint32_t pk[ND] = {0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      int8_t d[ND];
+      digits_of(neg ? -v[q] : v[q], e, d);
+#pragma unroll
+      for (int s = 0; s < ND; ++s) pk[s] |= (uint32_t)(uint8_t)d[s] << (8 * q);
+    }
+    int8_t *o = D.out + (int64_t)col * D.kp * ND + (size_t)kc * 64 * ND + 4 * li;
+#pragma unroll
+    for (int s = 0; s < ND; ++s) stg((uint32_t *)(o + 64 * s), pk[s]);
+  }
+  if (li == 0) stg(D.scale + col, bad ? (double)NAN : use ? ldexp(neg ? -1.0 : 1.0, e) : 0.0);
+}
+
+struct DigitArgs {
+  DigitDesc lv[kMaxLevels];
+  int nlev;
+};
+
+// one plan: a descriptor per level, by value
+__global__ __launch_bounds__(256) void k_digits(DigitArgs A) {
+  int li = 0;
+  for (int q = 1; q < A.nlev; ++q)
+    if ((int)blockIdx.x >= A.lv[q].blk_start) li = q;
+  const DigitDesc &D = A.lv[li];
+  const int col = ((int)blockIdx.x - D.blk_start) * kDigitCols + (int)(threadIdx.x >> 4);
+  if (col < D.ncols) digit_column(D, col);
+}
+
+// a batch: every (problem, level), descriptors in device memory
+__global__ __launch_bounds__(256) void k_digits_list(const DigitDesc *__restrict__ L, int n) {
+  const int li =
+      find_last_le(n, blockIdx.x, [&](int m) { return (int64_t)L[m].blk_start; });
+  const DigitDesc D = L[li];
+  const int col = ((int)blockIdx.x - D.blk_start) * kDigitCols + (int)(threadIdx.x >> 4);
+  if (col < D.ncols) digit_column(D, col);
+}
+
+// Global memory straight into LDS, 16 bytes per lane (lane l's to lds + 16 l; lds is
+// wave-uniform; an instruction's offset moves both addresses).  The loads are
+// outstanding on the vector-memory counter: the caller waits for it before the
+// barrier that hands the data over.
+// fragment OFF / 1024 of consecutive ones in both memories; src is wave-uniform, lane l
+// reads src + OFF + 16 l
+template <int OFF>
+__device__ inline void fragment_to_lds(uint64_t src, uint32_t lds, uint32_t lane16) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
+               :
+               : "s"(lds), "v"(lane16), "s"(src), "i"(OFF)
+               : "memory", "m0");
+}
+// one fragment, each lane from its own address src + OFF (the offset is taken off the
+// LDS address again)
+template <int OFF>
+__device__ inline void column_to_lds(const int8_t *src, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2"
+               :
+               : "s"(lds - OFF), "v"(src), "i"(OFF)
+               : "memory", "m0");
+}
+__device__ inline uint64_t uniform64(uint64_t p) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// f(integral_constant<int, I>) for I in [I0, I1)
+template <int I0, int I1, typename F>
+__device__ inline void for_each_from(F &f) {
+  if constexpr (I0 < I1) {
+    f(std::integral_constant<int, I0>{});
+    for_each_from<I0 + 1, I1>(f);
+  }
+}
+
+// a tile's target column
+struct Col8 {
+  const int *slot_map;  // slot map of the level
+  const int8_t *B;      // source digits
+  const double *bs;     // source scales
+  uint32_t tkey;        // target key
+  int r, valid;
+};
+
+// Terms [term0, term1) of one tile of 16 RB RG rows and 128 / RG columns: the result,
+// or a piece (part).  8 waves, RG groups of rows by 8 / RG groups of 16 columns; a wave
+// holds RB row blocks of its 16 columns.  The operator fragments of a 64-k chunk go
+// to LDS one chunk ahead, in two buffers; the source digits (16 columns and 64 k are
+// one fragment per digit) one chunk ahead too, in one buffer that every wave copies
+// to registers at the start of the chunk.  Both are direct loads, which need no
+// registers: the digit sums and the FP64 sums take 144 of a lane's 256.  The slots of
+// the sources are read one term ahead.  A step waits for all of them at its start, a
+// whole chunk of products (RB x 28 MFMAs per wave) after they were issued.
+template <int RB, int RG>
+__device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, int term1,
+                                 double *__restrict__ part, const int8_t *__restrict__ dvec,
+                                 int8_t (*As)[RB * RG * ND * kFrag], int8_t *Bs, Col8 *cst,
+                                 int *sdel) {
+  constexpr int CG = 8 / RG, H = RB * RG, COLS = 16 * CG;
+  __shared__ int sbox[8][6];
+  __shared__ int snk;
+  const int t = threadIdx.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int rg = w / CG, cg = w % CG;
+  const int rowtile = tile_local % J.nrowtiles, coltile = tile_local / J.nrowtiles;
+  const int rb0 = rowtile * H, col0 = coltile * COLS;
+  const int nrb = J.dpm >> 4, nkc = J.dpk >> 6;
+  const int nv = min(H, nrb - rb0);             // row blocks of this tile
+  const int nw = max(0, min(RB, nv - rg * RB));  // row blocks of this wave
+  const int ncols = J.ntgt * J.nrhs;
+  const int64_t colbytes = (int64_t)J.dpk * ND;
+
+  Col8 *my = cst + 16 * cg + (lane & 15);  // (the waves of a column group write the same)
+  int bb[6] = {INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN};
+  {
+    const int jc = col0 + 16 * cg + (lane & 15);
+    Col8 c{};
+    c.valid = jc < ncols;
+    c.slot_map = J.src_slot;
+    c.B = (const int8_t *)J.Bsrc;
+    c.bs = J.bscale;
+    if (c.valid) {
+      const int tt = jc / J.nrhs;
+      c.r = jc - tt * J.nrhs;
+      if (J.colref) {
+        const ColRef cr = J.colref[tt];
+        const ColSrc &cs = J.colsrc[cr.rec];
+        c.tkey = ldg(cs.keys + cr.slot);
+        c.slot_map = cs.slot;
+        c.B = (const int8_t *)cs.B;
+        c.bs = cs.bscale;
+      } else {
+        c.tkey = ldg(J.tgt_keys + ldg(J.tgt + tt));
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) bb[a] = bb[3 + a] = (int)morton_axis(c.tkey, a);
+    }
+    *my = c;
+  }
+  // the terms whose source box lies inside the domain for some column of the tile,
+  // in order, packed (dx+3) | (dy+3) << 3 | (dz+3) << 6 | id << 9: the tile's boxes
+  // span [lo, hi] per axis, and offset delta reaches inside when hi + delta >= 0 and
+  // lo + delta < side on every axis
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      bb[a] = min(bb[a], __shfl_xor(bb[a], o));
+      bb[3 + a] = max(bb[3 + a], __shfl_xor(bb[3 + a], o));
+    }
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int a = 0; a < 6; ++a) sbox[w][a] = bb[a];
+  }
+  lds_barrier();
+  if (w == 0) {
+    int lo[3], hi[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = INT_MAX;
+      hi[a] = INT_MIN;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        lo[a] = min(lo[a], sbox[q][a]);
+        hi[a] = max(hi[a], sbox[q][3 + a]);
+      }
+    }
+    const int side = 1 << J.level;
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    int nk = 0;
+    for (int b = term0; b < term1; b += 64) {
+      const int i = b + lane;
+      bool keep = false;
+      int pk = 0;
+      if (i < term1) {
+        const int id = ldg(J.terms + i);
+        const int d0 = dvec[3 * id], d1 = dvec[3 * id + 1], d2 = dvec[3 * id + 2];
+        pk = (d0 + 3) | ((d1 + 3) << 3) | ((d2 + 3) << 6) | (id << 9);
+        keep = hi[0] + d0 >= 0 && lo[0] + d0 < side && hi[1] + d1 >= 0 && lo[1] + d1 < side &&
+               hi[2] + d2 >= 0 && lo[2] + d2 < side;
+      }
+      const uint64_t m = __ballot(keep);
+      if (keep) sdel[nk + (int)__popcll(m & below)] = pk;
+      nk += (int)__popcll(m);
+    }
+    if (lane == 0) snk = nk;
+  }
+  lds_barrier();
+  const int nt = __builtin_amdgcn_readfirstlane(snk);
+
+  // where the slot of term q's source is read (-1: no box)
+  auto slot_addr = [&](int q) -> const int * {
+    const Col8 c = *my;
+    if (q >= nt || !c.valid || !c.slot_map) return &g_no_slot;
+    const int pk = sdel[q];
+    const int side = 1 << J.level;
+    const int m0 = (int)morton_axis(c.tkey, 0) + (pk & 7) - 3;
+    const int m1 = (int)morton_axis(c.tkey, 1) + ((pk >> 3) & 7) - 3;
+    const int m2 = (int)morton_axis(c.tkey, 2) + ((pk >> 6) & 7) - 3;
+    const bool in = m0 >= 0 && m1 >= 0 && m2 >= 0 && m0 < side && m1 < side && m2 < side;
+    return in ? c.slot_map + morton_encode((uint32_t)m0, (uint32_t)m1, (uint32_t)m2) : &g_no_slot;
+  };
+
+  double sum[RB][4];
+  i4v acc[RB][ND];
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum[i][q] = 0.0;
+  }
+  if (nt > 0) {
+    const uint32_t lds0 =
+        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)&As[0][0];
+    const uint32_t lane16 = 16u * (uint32_t)lane;
+    const int8_t *Abase = (const int8_t *)J.A + (int64_t)rb0 * nkc * ND * kFrag;
+    const uint32_t ldsb =
+        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)Bs + cg * (ND * kFrag);
+    int slotn = ldg(slot_addr(0));  // slot of the next term to load
+    const int8_t *srcp = nullptr, *At = nullptr;
+    // scale of the source and whether the wave has any: of the term aimed at (n), of
+    // the last one loaded (q)
+    double scn = 0.0, scq = 0.0;
+    bool haven = false, haveq = false;
+    int fq = 0, fk = 0;  // next chunk to load: term, chunk
+    // the addresses of the next chunk to load, if it starts a term; runs a step ahead of
+    // that load, behind the products, since its chain of reads is long
+    auto aim = [&]() {
+      if (fq >= nt || fk != 0) return;
+      const Col8 c = *my;
+      const int sl = slotn;
+      const int64_t col = (int64_t)sl * J.nrhs + c.r;
+      srcp = (sl < 0 ? (const int8_t *)g_digit_zero : c.B + col * colbytes) + 16 * (lane >> 4);
+      scn = ldg(sl < 0 ? (const double *)g_digit_zero : c.bs + col);
+      haven = __ballot(sl >= 0) != 0;
+      At = Abase + (int64_t)(__builtin_amdgcn_readfirstlane(sdel[fq]) >> 9) * J.a_stride;
+      slotn = ldg(slot_addr(fq + 1));
+    };
+    // The loads of the next chunk, operators to LDS buffer `buf` and sources to Bs, are
+    // issued one at a time between the products: a burst of them would hold up the
+    // wave.  A column group's seven digits are shared out to its RG waves; a row block's
+    // seven operator fragments make two pieces (4 and 3), dealt to the waves.
+    constexpr int NB = RG == 2 ? 4 : ND, NP = (2 * H + 7) / 8, NL = NB + 4 * NP;
+    static_assert(NL <= ND * RB, "a load per fragment of the products");
+    bool live = false;
+    const int8_t *sp = nullptr;
+    uint64_t ap[NP];
+    uint32_t lp[NP];
+    const int half = w & 1;
+    auto fetch_begin = [&](int buf) {
+      live = fq < nt;
+      if (!live) return;
+      if (fk == 0) {
+        scq = scn;
+        haveq = haven;
+      }
+      sp = srcp + fk * (64 * ND) + (RG == 2 ? rg * 256 : 0);
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const int blk = (w >> 1) + 4 * i;
+        ap[i] = uniform64((uint64_t)(At + (int64_t)(blk * nkc + fk) * (ND * kFrag) + half * 4 * kFrag));
+        lp[i] = __builtin_amdgcn_readfirstlane(
+            lds0 + (uint32_t)(buf * (H * ND * kFrag) + (blk * ND + half * 4) * kFrag));
+      }
+      if (++fk == nkc) {
+        fk = 0;
+        ++fq;
+      }
+    };
+    const uint32_t ldsw = __builtin_amdgcn_readfirstlane(ldsb + (RG == 2 ? rg * 4 * kFrag : 0));
+    auto fetch_one = [&](auto N) {
+      constexpr int n = decltype(N)::value;
+      if (!live) return;
+      if constexpr (n < NB) {
+        if (RG == 1 || n < 3 || rg == 0) column_to_lds<64 * n>(sp, ldsw + n * kFrag);
+      } else if constexpr (n < NL) {
+        constexpr int i = (n - NB) / 4, j = (n - NB) % 4;
+        if ((w >> 1) + 4 * i < nv && (j < 3 || half == 0))
+          fragment_to_lds<j * kFrag>(ap[i], lp[i], lane16);
+      }
+    };
+    auto fetch_all = [&](auto N0) { for_each_from<decltype(N0)::value, NL>(fetch_one); };
+    // The 28 digit products of each of the wave's row blocks [i0, i1) in one chunk, the
+    // operator fragments read three ahead of their products (blocks past the tile's
+    // rows multiply what the buffer holds; their sums are not stored).  first: the
+    // term's first chunk, whose sums start at zero.
+    auto products = [&](auto first, int buf, const i4v(&b)[ND]) {
+      constexpr int NF = RB * ND, AHEAD = 3;
+      const int8_t *Ap = &As[buf][rg * RB * ND * kFrag + 16 * lane];
+      i4v a[AHEAD];
+#pragma unroll
+      for (int f = 0; f < AHEAD; ++f) a[f] = *(const i4v *)(Ap + f * kFrag);
+      __builtin_amdgcn_sched_barrier(0);
+      auto group = [&](auto Fc) {
+        constexpr int f = decltype(Fc)::value, i = f / ND, da = f % ND;
+#pragma unroll
+        for (int db = 0; db + da < ND; ++db) {
+          const i4v c = decltype(first)::value && da == 0 ? i4v{0, 0, 0, 0} : acc[i][da + db];
+          acc[i][da + db] =
+              __builtin_amdgcn_mfma_i32_16x16x64_i8(a[f % AHEAD], b[db], c, 0, 0, 0);
+        }
+        if (f + AHEAD < NF) a[f % AHEAD] = *(const i4v *)(Ap + (f + AHEAD) * kFrag);
+        constexpr int SP = 2 * NL <= NF ? 2 : 1;
+        if constexpr (f % SP == 0) fetch_one(std::integral_constant<int, f / SP>{});
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      for_each_from<0, NF>(group);
+    };
+    // a term's digit sums, joined in FP64 and scaled, added to the tile's sums
+    auto fold = [&](double scf) {
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          double v = (double)acc[i][ND - 1][q];
+#pragma unroll
+          for (int s = ND - 2; s >= 0; --s) v = fma(v, 1.0 / 256.0, (double)acc[i][s][q]);
+          sum[i][q] = fma(v, scf, sum[i][q]);
+        }
+      }
+    };
+    // The two waves of a SIMD (w and w + 4) take turns on its matrix core: the first
+    // has priority and joins a term's sums at the end of the term's last chunk, while
+    // the second multiplies; the second joins them at the start of the next chunk,
+    // while the first multiplies, and issues its loads after its first row block.
+    const bool lead = w < 4;
+    if (lead)
+      __builtin_amdgcn_s_setprio(1);
+    else
+      __builtin_amdgcn_s_setprio(0);
+    double sc = 0.0;
+    bool have = false, pend = false;  // pend: the last term's sums are not joined yet
+    int kc = 0;                       // chunk of the current term
+    auto step = [&](int buf) {
+      // everything this wave issued in the last step has arrived, and after the
+      // barrier what the others issued; the second barrier ends the reads of Bs,
+      // which the next loads overwrite
+      __builtin_amdgcn_s_waitcnt(0x0f70);
+      lds_barrier();
+      i4v Bc[ND];
+#pragma unroll
+      for (int s = 0; s < ND; ++s)
+        Bc[s] = *(const i4v *)&Bs[(cg * ND + s) * kFrag + 16 * lane];
+      lds_barrier();
+      if (pend) {
+        fold(sc);
+        pend = false;
+      }
+      const bool fst = kc == 0;
+      if (fst) {
+        sc = scq;
+        have = haveq && nw > 0;
+      }
+      fetch_begin(buf ^ 1);
+      if (!have)
+        fetch_all(std::integral_constant<int, 0>{});
+      else if (fst)
+        products(std::true_type{}, buf, Bc);
+      else
+        products(std::false_type{}, buf, Bc);
+      aim();
+      if (++kc == nkc) {
+        kc = 0;
+        if (have && lead)
+          fold(sc);
+        else
+          pend = have;
+      }
+    };
+    aim();
+    fetch_begin(0);
+    fetch_all(std::integral_constant<int, 0>{});
+    aim();
+    const int steps = nt * nkc;
+    for (int it = 0; it < steps; ++it) step(it & 1);
+    if (pend) fold(sc);
+    __builtin_amdgcn_s_setprio(0);
+  }
+
+  // result row 16 block + 4 (lane / 16) + q of column lane % 16
+  const int jt = 16 * cg + (lane & 15), jo = col0 + jt;
+  if (jo >= ncols) return;
+  double *out;
+  if (part) {
+    out = part + (size_t)jt * (16 * H);
+  } else {
+    const int tt = jo / J.nrhs, ro = jo - tt * J.nrhs;
+    int tso;
+    double *Cout = J.C;
+    if (J.colref) {
+      const ColRef cr = J.colref[tt];
+      tso = cr.slot;
+      Cout = J.colsrc[cr.rec].C;
+    } else {
+      tso = ldg(J.tgt + tt);
+    }
+    out = Cout + ((int64_t)tso * J.nrhs + ro) * J.dpm + 16 * rb0;
+  }
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    if (i < nw) {
+      const int rt = 16 * (rg * RB + i) + 4 * (lane >> 4);
+#pragma unroll
+      for (int q = 0; q < 4; q += 2) {
+        d2v v;
+        v.x = sum[i][q] * ldg(J.rscale + 16 * rb0 + rt + q);
+        v.y = sum[i][q + 1] * ldg(J.rscale + 16 * rb0 + rt + q + 1);
+        stg((d2v *)(out + rt + q), v);
+      }
+    }
+  }
+}
+
+__device__ inline int job_of_tile(const GemmJob *__restrict__ jobs, int njobs, int tile) {
+  return find_last_le(njobs, tile, [&](int m) { return (int64_t)jobs[m].tiles_start; });
+}
+
+// Tiles [0, full) run whole, G workgroups at a time in the order of the terms (so that
+// the operators they read are shared in L2; the tiles of one XCD (g mod 8) are
+// contiguous); the others are cut into `parts` term ranges each, taken in order from
+// a counter and summed by k_m2l8_sum, so that workgroups whose tiles dropped terms
+// take more of them.  A workgroup that reads a value outside [0, items) stops.
+template <int RB, int RG>
+__global__ __launch_bounds__(512, 2) void k_m2l8(const GemmJob *__restrict__ jobs, int njobs,
+                                                 int G, int full, int items, int parts,
+                                                 double *__restrict__ ws,
+                                                 const int8_t *__restrict__ dvec,
+                                                 int *__restrict__ ctr) {
+  constexpr int H = RB * RG, TILE = H * 16 * (128 / RG);
+  __shared__ __align__(16) int8_t As[2][H * ND * kFrag];
+  __shared__ __align__(16) int8_t Bs[(8 / RG) * ND * kFrag];
+  __shared__ Col8 cst[128 / RG];
+  __shared__ int sdel[189];
+  __shared__ int item_sh;
+  const int g = blockIdx.x;
+  const int gx = (G % 8 == 0) ? (g % 8) * (G / 8) + g / 8 : g;
+  for (int tile = gx; tile < full; tile += G) {
+    const GemmJob J = jobs[job_of_tile(jobs, njobs, tile)];
+    m2l8_tile<RB, RG>(J, tile - J.tiles_start, 0, J.nterms, nullptr, dvec, As, Bs, cst, sdel);
+  }
+  if (items <= 0) return;
+  for (;;) {
+    if (threadIdx.x == 0) item_sh = atomicAdd(ctr, 1);
+    __syncthreads();
+    const int item = item_sh;
+    __syncthreads();
+    if ((unsigned)item >= (unsigned)items) return;
+    const int tile = full + item / parts, q = item % parts;
+    const GemmJob J = jobs[job_of_tile(jobs, njobs, tile)];
+    m2l8_tile<RB, RG>(J, tile - J.tiles_start, q * J.nterms / parts, (q + 1) * J.nterms / parts,
+                      ws + (size_t)item * TILE, dvec, As, Bs, cst, sdel);
+  }
+}
+
+// adds the pieces of the split tiles in part order (kSumSplit blocks per tile) and
+// sets the counter back for the next launch
+constexpr int kSumSplit = 4;
+__global__ __launch_bounds__(256) void k_m2l8_sum(const GemmJob *__restrict__ jobs, int njobs,
+                                                  int ntiles, int full, int parts, int height,
+                                                  const double *__restrict__ ws,
+                                                  int *__restrict__ ctr) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) stg(ctr, 0);
+  const int tile = full + (int)(blockIdx.x / kSumSplit);
+  if (tile >= ntiles) return;
+  const GemmJob J = jobs[job_of_tile(jobs, njobs, tile)];
+  const int cols = m2l8_cols(height), rows = 16 * height, size = rows * cols;
+  const int tile_local = tile - J.tiles_start;
+  const int row0 = (tile_local % J.nrowtiles) * rows, col0 = (tile_local / J.nrowtiles) * cols;
+  const int nrows = min(rows, J.dpm - row0), ncols = J.ntgt * J.nrhs;
+  const double *p = ws + (size_t)(tile - full) * parts * size;
+  for (int e = (int)(blockIdx.x % kSumSplit) * 256 + (int)threadIdx.x; e < size;
+       e += 256 * kSumSplit) {
+    const int jt = e / rows, rt = e - jt * rows, jo = col0 + jt;
+    if (rt >= nrows || jo >= ncols) continue;
+    double v = 0.0;
+    int i = 0;
+    for (; i + 8 <= parts; i += 8) {
+      double u[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) u[q] = ldg(p + (size_t)(i + q) * size + e);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v += u[q];
+    }
+    for (; i < parts; ++i) v += ldg(p + (size_t)i * size + e);
+    const int tt = jo / J.nrhs, ro = jo - tt * J.nrhs;
+    int tso;
+    double *Cout = J.C;
+    if (J.colref) {
+      const ColRef cr = J.colref[tt];
+      tso = cr.slot;
+      Cout = J.colsrc[cr.rec].C;
+    } else {
+      tso = ldg(J.tgt + tt);
+    }
+    stg(Cout + ((int64_t)tso * J.nrhs + ro) * J.dpm + row0 + rt, v);
+  }
+}
+
+template <int RB, int RG>
+void launch(const GemmJob *jobs, int n, int tiles, int cus, double *ws, size_t ws_len,
+            const int8_t *dvec, hipStream_t s) {
+  constexpr int H = RB * RG;
+  const size_t TILE = (size_t)H * 16 * (128 / RG);
+  int *ctr = (int *)(ws + ws_len - kCounterDoubles);
+  const size_t pieces = (ws_len - kCounterDoubles) / TILE;
+  // one workgroup per CU (its operator buffers take most of the LDS)
+  const int G = cus;
+  int full = (tiles / G) * G, rest = tiles - full, parts = 0;
+  if (rest > 0) {
+    // about 4 items per workgroup, at least 4 terms each
+    parts = std::min(47, std::max(4, 4 * G / rest));
+    parts = (int)std::min<size_t>((size_t)parts, pieces / (size_t)rest);
+    if (parts < 2) {  // the pieces do not fit: every tile whole
+      full = tiles;
+      rest = 0;
+    }
+  }
+  const int grid = full > 0 ? G : std::min(G, rest * parts);
+  hipLaunchKernelGGL((k_m2l8<RB, RG>), dim3(grid), dim3(512), 0, s, jobs, n, grid, full,
+                     rest * parts, parts, ws, dvec, ctr);
+  if (rest > 0)
+    hipLaunchKernelGGL(k_m2l8_sum, dim3(rest * kSumSplit), dim3(256), 0, s, jobs, n, tiles, full,
+                       parts, H, ws, ctr);
+}
+
+}  // namespace
+
+// The tile height that leaves the fewest idle row blocks, the taller one on a tie.
+// 8 and 6 blocks are 64 columns wide, the lower ones 128.
+int pick_m2l8(int nrb) {
+  int best = 8, waste = 1 << 30;
+  for (int h : {8, 6, 4, 3, 2}) {
+    const int w = (nrb + h - 1) / h * h - nrb;
+    if (w < waste) {
+      waste = w;
+      best = h;
+    }
+  }
+  return best;
+}
+
+void launch_m2l8(const GemmJob *jobs, int n, int tiles, int height, int cus, double *ws,
+                 size_t ws_len, const int8_t *dvec, hipStream_t s) {
+  if (n == 0 || tiles == 0) return;
+  switch (height) {
+    case 8: launch<4, 2>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+    case 6: launch<3, 2>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+    case 4: launch<4, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+    case 3: launch<3, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+    default: launch<2, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+  }
+}
+
+int digit_blocks(int ncols) { return (ncols + kDigitCols - 1) / kDigitCols; }
+
+void launch_digits(const DigitDesc *lv, int nlev, int blocks, hipStream_t s) {
+  if (nlev == 0 || blocks == 0) return;
+  DigitArgs A{};
+  for (int q = 0; q < nlev; ++q) A.lv[q] = lv[q];
+  A.nlev = nlev;
+  hipLaunchKernelGGL(k_digits, dim3(blocks), dim3(256), 0, s, A);
+}
+
+void launch_digits_list(const DigitDesc *dev, int n, int blocks, hipStream_t s) {
+  if (n == 0 || blocks == 0) return;
+  hipLaunchKernelGGL(k_digits_list, dim3(blocks), dim3(256), 0, s, dev, n);
+}
+
+// The digit fragments and row scales of one level's M2L operators (rows x cols, both
+// multiples of 16) from their FP64 fragments on the host.
+int upload_digit_operators(const std::vector<double> &frag, int rows, int cols, int8_t *dig,
+                           double *scale) {
+  const int nrb = rows / 16, nks = cols / 4, nkc = digit_kp(cols) / 64;
+  double *tab = nullptr;
+  unsigned long long *mx = nullptr;
+  hipError_t e = hipMalloc(&tab, sizeof(double) * std::max<size_t>(frag.size(), 1));
+  if (e == hipSuccess) e = hipMalloc(&mx, sizeof(unsigned long long) * rows);
+  if (e == hipSuccess)
+    e = hipMemcpy(tab, frag.data(), sizeof(double) * frag.size(), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemset(mx, 0, sizeof(unsigned long long) * rows);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(k_op_rowmax, dim3(nrb, 32), dim3(256), 0, nullptr, tab, nrb, nks, mx);
+    hipLaunchKernelGGL(k_op_digits, dim3(kNumOffsets * nrb * nkc), dim3(64), 0, nullptr, tab, nrb,
+                       nks, nkc, mx, dig);
+    hipLaunchKernelGGL(k_op_scale, dim3((rows + 255) / 256), dim3(256), 0, nullptr, mx, rows,
+                       scale);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipDeviceSynchronize();
+  hipFree(tab);
+  hipFree(mx);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return e == hipErrorOutOfMemory ? EIFMM_ENOMEM : EIFMM_EHIP;
+  }
+  return EIFMM_OK;
+}
+
+}  // namespace eifmm

@@ -7,7 +7,8 @@
 //   1  P2M                      k_p2m               one workgroup per leaf
 //   2  M2M (Sec. 4.1 operators) k_gemm<MODE_M2M>    MFMA, 8 children per parent
 //   3  What = Delta W           k_trsm              blocked triangular solves (MFMA)
-//   4  M2L (Sec. 4.2 matrices)  k_gemm<MODE_M2L>    MFMA, 189 offsets per class
+//   4  M2L (Sec. 4.2 matrices)  mixed: k_gemm<MODE_M2L> (FP32 MFMA), 189 offsets per class;
+//                               FP64: k_m2l8 (m2l.hip, int8 MFMA)
 //   5  L2L                      k_gemm<MODE_L2L>    MFMA, adds g
 //   6  lhat = Delta^T l         k_trsm
 //   7  L2P and f = f_far + f_near, input order  k_l2p  one wave per 64 targets
@@ -99,19 +100,6 @@ __host__ __device__ inline double dev_param(int kind, double p) {
 // one chunk per 64-lane workgroup whose two halves share the chunk's work, so
 // a crowded leaf of a clustered cloud spreads over many workgroups and a sparse
 // one (~30 points) does not idle half a wave.
-
-template <typename F>
-__device__ inline int find_last_le(int n, int64_t v, F key) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (key(mid) <= v)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  return lo;
-}
 
 __device__ inline int chunk_leaf(const int *__restrict__ chunk_ptr, int nleaf, int c) {
   return find_last_le(nleaf, c, [&](int m) { return (int64_t)chunk_ptr[m]; });
@@ -1607,9 +1595,11 @@ struct Timer {
 
 int tiles_of(const GemmJob &J) { return J.ncoltiles * J.nrowtiles; }
 
-void finish_job(GemmJob &J, int &tiles, int rbt) {
+// cols: columns of a tile (0: the gathered GEMM's for the height rbt)
+void finish_job(GemmJob &J, int &tiles, int rbt, int cols = 0) {
   const int ncols = J.ntgt * J.nrhs;
-  J.ncoltiles = (ncols + gemm_cols(rbt) - 1) / gemm_cols(rbt);
+  if (cols == 0) cols = gemm_cols(rbt);
+  J.ncoltiles = (ncols + cols - 1) / cols;
   J.nrowtiles = (J.dpm / 16 + rbt - 1) / rbt;
   J.tiles_start = tiles;
   tiles += tiles_of(J);
@@ -1696,27 +1686,34 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
     int tiles = 0;
     jt.m2l_first = (int)h.size();
     const LevelHost &F = P.lh[depth];
-    jt.m2l_rbt = pick_rbt((F.r ? F.rp : F.dpB) / 16);
+    jt.m2l_rbt = mixed ? pick_rbt((F.r ? F.rp : F.dpB) / 16) : pick_m2l8((F.r ? F.rp : F.dpB) / 16);
     for (int k = depth; k >= 2; --k) {
       if (uses_m2l2(P, k)) continue;  // the factored M2L below
       const bool cz = P.lh[k].r > 0;
       // rows: g (the second EIM's size); columns: What
-      const int dm = cz ? P.lh[k].rp : P.lh[k].dpB, dk = cz ? P.lh[k].rp : P.lh[k].dp;
+      // (FP64: whole 64-element chunks)
+      const int dm = cz ? P.lh[k].rp : P.lh[k].dpB;
+      const int dk = mixed ? (cz ? P.lh[k].rp : P.lh[k].dp) : digit_kp(cz ? P.lh[k].rp : P.lh[k].dp);
       for (int c = 0; c < 8; ++c) {
         const int64_t nt = P.cls_off[k][c + 1] - P.cls_off[k][c];
         if (nt == 0) continue;
         GemmJob J{};
-        J.A = mixed ? (const void *)P.ld[k].kfrag32 : (const void *)P.ld[k].kfrag;
-        if (cz)
-          J.Bsrc = mixed ? (const void *)P.ld[k].Whp32 : (const void *)P.ld[k].Whp;
-        else
-          J.Bsrc = mixed ? (const void *)P.ld[k].Wh32 : (const void *)P.ld[k].Wh;
+        if (mixed) {
+          J.A = P.ld[k].kfrag32;
+          J.Bsrc = cz ? P.ld[k].Whp32 : P.ld[k].Wh32;
+          J.a_stride = (int64_t)dm * dk;
+        } else {
+          J.A = P.ld[k].k8;
+          J.Bsrc = P.ld[k].w8;
+          J.bscale = P.ld[k].wscale;
+          J.rscale = P.ld[k].rscale;
+          J.a_stride = (int64_t)dm * dk * kDigits;
+        }
         J.C = cz ? P.ld[k].gp : P.ld[k].g;
         J.tgt = (P.ld[k].ord ? P.ld[k].ord : P.ld[k].cls) + P.cls_off[k][c];
         J.tgt_keys = P.ld[k].act;
         J.src_slot = P.ld[k].slot;
         J.terms = P.dlist + 189 * c;
-        J.a_stride = (int64_t)dm * dk;
         J.ntgt = (int)nt;
         J.nterms = 189;
         J.dpm = dm;
@@ -1725,7 +1722,7 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
         J.cls = c;
         J.mode = MODE_M2L;
         J.nrhs = nrhs;
-        finish_job(J, tiles, jt.m2l_rbt);
+        finish_job(J, tiles, jt.m2l_rbt, mixed ? 0 : m2l8_cols(jt.m2l_rbt));
         h.push_back(J);
       }
     }
@@ -1991,8 +1988,7 @@ void launch_gemm_fused(const FusedGemm &F, int mode, bool fp32, int gmax, double
         launch_gemm_tab<float, MODE_M2L>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, dvec,
                                          s);
       else
-        launch_gemm_tab<double, MODE_M2L>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, dvec,
-                                          s);
+        launch_m2l8(F.dev, F.n, F.tiles, F.rbt, gmax / 2, ws, len, dvec, s);
   }
 }
 
@@ -2104,6 +2100,20 @@ LeafDesc leaf_desc(const Plan &P, int nrhs) {
   return D;
 }
 
+// level k's M2L sources (What' on a compressed level, What otherwise) as digits
+DigitDesc digit_desc(const Plan &P, int k, int nrhs, int blk_start) {
+  const bool cz = P.lh[k].r > 0;
+  DigitDesc D{};
+  D.in = cz ? P.ld[k].Whp : P.ld[k].Wh;
+  D.out = P.ld[k].w8;
+  D.scale = P.ld[k].wscale;
+  D.ncols = (int)(P.nact[k] * nrhs);
+  D.ld = cz ? P.lh[k].rp : P.lh[k].dp;
+  D.kp = digit_kp(D.ld);
+  D.blk_start = blk_start;
+  return D;
+}
+
 template <int KIND>
 void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
   const int depth = P.depth;
@@ -2198,9 +2208,19 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
     if (mixed)
       launch_gemm<float, MODE_M2L>(P, P.jobs.m2l_first, P.jobs.m2l_n, P.jobs.m2l_tiles,
                                    P.jobs.m2l_units, s, P.jobs.m2l_rbt);
-    else
-      launch_gemm<double, MODE_M2L>(P, P.jobs.m2l_first, P.jobs.m2l_n, P.jobs.m2l_tiles,
-                                    P.jobs.m2l_units, s, P.jobs.m2l_rbt);
+    else if (P.jobs.m2l_n) {
+      DigitDesc dd[kMaxLevels];
+      int nd = 0, blk = 0;
+      for (int k = depth; k >= 2; --k) {
+        if (P.nact[k] == 0 || uses_m2l2(P, k)) continue;
+        dd[nd] = digit_desc(P, k, nrhs, blk);
+        blk += digit_blocks(dd[nd++].ncols);
+      }
+      launch_digits(dd, nd, blk, s);
+      launch_m2l8(P.job_dev + P.jobs.m2l_first, P.jobs.m2l_n, P.jobs.m2l_tiles, P.jobs.m2l_rbt,
+                  P.sk_groups / 2, P.run_ws ? P.run_ws : P.sk_ws,
+                  P.run_ws ? P.run_ws_len : stream_k_ws_len(P.sk_groups), P.dvec, s);
+    }
     for (const M2l2Launch &L : P.m2l2_launch) launch_m2l2(P.m2l2_dev, L, P.dvec, P.m2l2_ws, s);
   }
   // launched after the M2L so that the M2L's workgroups are dispatched first
@@ -2492,16 +2512,18 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, bool mixed
           hipSuccess)
         return EIFMM_EHIP;
       const bool cz = P.lh[k].r > 0;
-      const int dm = cz ? P.lh[k].rp : P.lh[k].dp;
+      const int dm = cz ? P.lh[k].rp : P.lh[k].dp, dk = mixed ? dm : digit_kp(dm);
       dmax = std::max(dmax, dm);
-      const void *A = mixed ? (const void *)P.ld[k].kfrag32 : (const void *)P.ld[k].kfrag;
-      ColSrc cs;
+      const void *A = mixed ? (const void *)P.ld[k].kfrag32 : (const void *)P.ld[k].k8;
+      ColSrc cs{};
       cs.keys = P.ld[k].act;
       cs.slot = P.ld[k].slot;
-      if (cz)
-        cs.B = mixed ? (const void *)P.ld[k].Whp32 : (const void *)P.ld[k].Whp;
-      else
-        cs.B = mixed ? (const void *)P.ld[k].Wh32 : (const void *)P.ld[k].Wh;
+      if (mixed) {
+        cs.B = cz ? P.ld[k].Whp32 : P.ld[k].Wh32;
+      } else {
+        cs.B = P.ld[k].w8;
+        cs.bscale = P.ld[k].wscale;
+      }
       cs.C = cz ? P.ld[k].gp : P.ld[k].g;
       const int rec = (int)srcs.size();
       srcs.push_back(cs);
@@ -2515,9 +2537,11 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, bool mixed
           GemmJob J{};
           J.A = A;
           J.terms = P.dlist + 189 * c;
-          J.a_stride = (int64_t)dm * dm;
+          J.a_stride = (int64_t)dm * dk * (mixed ? 1 : kDigits);
+          J.rscale = P.ld[k].rscale;
           J.nterms = 189;
-          J.dpm = J.dpk = dm;
+          J.dpm = dm;
+          J.dpk = dk;
           J.level = k;
           J.cls = c;
           J.mode = MODE_M2L;
@@ -2530,7 +2554,7 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, bool mixed
     }
   }
   F = FusedGemm{};
-  F.rbt = rbt > 0 ? rbt : pick_rbt(dmax / 16);
+  F.rbt = rbt > 0 ? rbt : mixed ? pick_rbt(dmax / 16) : pick_m2l8(dmax / 16);
   if (jobs.empty()) return EIFMM_OK;
   // finest level first (as in a plan's own launch), then operator set and class
   std::vector<int> order(jobs.size());
@@ -2556,7 +2580,7 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, bool mixed
   for (size_t j = 0; j < h.size(); ++j) {
     h[j].colsrc = srcs_dev;
     h[j].colref = refs_dev + off[j];
-    finish_job(h[j], tiles, F.rbt);
+    finish_job(h[j], tiles, F.rbt, mixed ? 0 : m2l8_cols(F.rbt));
   }
   F.units = finish_units(h, 0);
   F.tiles = tiles;
@@ -2694,6 +2718,19 @@ int batch_prepare(BatchExec &B, const std::vector<Plan *> &plans_in, int m2l_rbt
       B.lhat_shm = std::max(B.lhat_shm, trsm_shm(D.dp));
       l.push_back(D);
     }
+    if (!B.mixed) {
+      std::vector<DigitDesc> dd;
+      int blk = 0;
+      for (Plan *Pp : plans)
+        for (int k = Pp->depth; k >= 2; --k) {
+          if (Pp->nact[k] == 0) continue;
+          dd.push_back(digit_desc(*Pp, k, 1, blk));
+          blk += digit_blocks(dd.back().ncols);
+        }
+      B.digit_n = (int)dd.size();
+      B.digit_blk = blk;
+      if ((st = bupload(&B.digit_dev, dd, B.track))) return st;
+    }
     B.what_n = (int)w.size();
     B.what_blk = bw;
     B.lhat_n = (int)l.size();
@@ -2756,6 +2793,7 @@ void batch_run(const BatchExec &B, hipStream_t s, const hipEvent_t *mark) {
   tick();
   launch_gemm_fused(B.pre, MODE_PROJ, false, B.sk_groups, B.sk_ws, B.dvec, s);
   tick();
+  if (!B.mixed) launch_digits_list(B.digit_dev, B.digit_n, B.digit_blk, s);
   batch_run_m2l(B, s);
   tick();
   launch_gemm_fused(B.post, MODE_PROJ, false, B.sk_groups, B.sk_ws, B.dvec, s);

@@ -17,6 +17,15 @@ constexpr int kNumOffsets = 316;  // 7^3 - 3^3 distinct M2L offsets (Sec. 4.2)
 constexpr int kMaxRank2 = 96;     // largest second-stage rank the factored M2L takes
 constexpr int kM2l2RbMin = 4, kM2l2RbMax = 16;  // 16-row blocks of r the factored M2L takes
 
+// FP64 M2L on the int8 matrix cores (m2l.hip): digits per operand, and the columns'
+// length padded to whole 64-element chunks
+constexpr int kDigits = 7;
+constexpr int kDigitCols = 16;  // columns per workgroup of the digit kernels
+inline int digit_kp(int d) { return (d + 63) / 64 * 64; }
+inline size_t digit_bytes(int d) { return (size_t)kDigits * digit_kp(d); }
+// columns of an M2L tile of `height` row blocks
+__host__ __device__ inline int m2l8_cols(int height) { return height >= 6 ? 64 : 128; }
+
 // Host copy of one level's EIM data (Algorithm 1 and the factors of eq. (5)).
 struct LevelHost {
   int d = 0;   // number of interpolation points d_k
@@ -30,7 +39,7 @@ struct LevelHost {
   std::vector<int64_t> ia, ib;  // training-set indices of X and Y
   std::vector<double> B, G;     // d x d row-major: unit-lower B and lower Gamma
   // operator tables, padded to dp and laid out for the device (see setup.cpp)
-  std::vector<double> kfrag;    // 316 M2L matrices K^delta, fragment order
+  std::vector<double> kfrag;    // 316 M2L matrices K^delta, fragment order (host only)
   std::vector<double> m2m;      // level k < depth: 8 ops d_k x d_{k+1}, fragment order
   std::vector<double> l2l;      // level k < depth: 8 ops d_{k+1} x d_k, fragment order
   std::vector<double> tri[4];   // solve tables: Gamma, B^T, B, Gamma^T (setup.cpp)
@@ -61,8 +70,10 @@ struct LevelHost {
 
 // Device copy of one level's tables.
 struct LevelDev {
-  double *kfrag = nullptr;
+  // M2L operators: FP32 fragments (mixed), or digit fragments and row scales (FP64)
   float *kfrag32 = nullptr;
+  int8_t *k8 = nullptr;
+  double *rscale = nullptr;
   double *m2m = nullptr, *l2l = nullptr;
   double *tri[4] = {nullptr, nullptr, nullptr, nullptr};
   double *X = nullptr;   // d x 3 (leaf level: P2M)
@@ -86,6 +97,9 @@ struct LevelDev {
   const double *vf2 = nullptr, *uf2 = nullptr;
   double *Whp = nullptr, *gp = nullptr;  // What' = U^T What and g' (rp per box and RHS)
   float *Whp32 = nullptr;
+  // FP64 M2L: the digits and the scale of each source column (What or What')
+  int8_t *w8 = nullptr;
+  double *wscale = nullptr;
 };
 
 // Packed M2L jobs of a batch: the columns of one job belong to several problems
@@ -95,6 +109,7 @@ struct ColSrc {
   const int *slot;       // slot map of the level
   const void *B;         // source expansions (What or What')
   double *C;             // output (g or g')
+  const double *bscale;  // FP64: scale of each source column (B holds digits)
 };
 struct ColRef {
   int rec;   // ColSrc record
@@ -119,6 +134,9 @@ struct GemmJob {
   int64_t units_start;  // first (tile, term) unit of the job within its launch
   const ColRef *colref;  // packed M2L: per target column (tgt, tgt_keys, src_slot,
   const ColSrc *colsrc;  // Bsrc and C unused); null otherwise
+  // FP64 M2L: scale of each source column and of each operator row (A and Bsrc hold
+  // digits, dpk is the padded column length, a_stride is in bytes)
+  const double *bscale, *rscale;
 };
 
 // One problem's leaf level as the near-field, P2M and L2P kernels read it.
@@ -170,6 +188,15 @@ struct SolveDesc {
   int ncols, dp, blk_start, pad;
 };
 
+// Source columns of one (problem, level) turned into digits (m2l.hip): columns of `ld`
+// doubles into kp-element digit columns; blk_start = first workgroup.
+struct DigitDesc {
+  const double *in;
+  int8_t *out;
+  double *scale;
+  int ncols, ld, kp, blk_start;
+};
+
 // Problems of one kernel kind inside a batch (contiguous descriptor range).
 struct BatchGroup {
   int kind = 0;
@@ -192,6 +219,8 @@ struct BatchExec {
   SolveDesc *what_dev = nullptr, *lhat_dev = nullptr;
   int what_n = 0, what_blk = 0, lhat_n = 0, lhat_blk = 0;
   size_t what_shm = 0, lhat_shm = 0;
+  DigitDesc *digit_dev = nullptr;
+  int digit_n = 0, digit_blk = 0;
   FusedGemm m2m[kMaxLevels], l2l[kMaxLevels], pre, m2l, post;
   int sk_groups = 0;
   double *sk_ws = nullptr;
@@ -368,6 +397,15 @@ struct EimResult {
 int eim_iterate_gpu(const std::vector<double> &R, int64_t nx, int64_t ny, double tau,
                     double abs_scale, int dmax, EimResult &res);
 int pick_rbt(int nrb);
+// FP64 M2L (m2l.hip)
+int pick_m2l8(int nrb);
+int upload_digit_operators(const std::vector<double> &frag, int rows, int cols, int8_t *dig,
+                           double *scale);
+int digit_blocks(int ncols);
+void launch_digits(const DigitDesc *lv, int nlev, int blocks, hipStream_t s);
+void launch_digits_list(const DigitDesc *dev, int n, int blocks, hipStream_t s);
+void launch_m2l8(const GemmJob *jobs, int n, int tiles, int height, int cus, double *ws,
+                 size_t ws_len, const int8_t *dvec, hipStream_t s);
 
 // device-side entry points (tree.hip, pass.hip)
 int tree_build(Plan &P, const double *xyz_in, hipStream_t s);
