@@ -18,7 +18,7 @@
  *     eifmm_plan_create   per-level EIM (Algorithm 1) and operator tables,
  *                         host FP64, uploaded once                (Sec. 2, 4.1, 4.2)
  *     eifmm_set_points    octree build on the GPU: Morton keys, stable sort,
- *                         leaf ranges, active boxes, near lists   (Sec. 3.3)
+ *                         leaf ranges, active boxes, chunk table  (Sec. 3.3)
  *     eifmm_evaluate      Algorithm 3 steps 1-7 plus the near field of eq. (13),
  *                         all on the GPU                          (Sec. 3.3.4)
  *
@@ -35,9 +35,9 @@
  *     return before it finishes, except the export calls, which copy to host
  *     memory and wait, and eifmm_set_points, which waits until the box counts
  *     of the tree are on the host (to report invalid points and size the
- *     pass); its last kernels (near lists, chunk table, M2L column order) are
- *     still in flight on its stream when it returns, so an evaluate on another
- *     stream must first wait for that stream.
+ *     pass); its last kernel (the M2L column order) is still in flight on its
+ *     stream when it returns, so an evaluate on another stream must first
+ *     wait for that stream.
  *   - Every call returns 0 (EIFMM_OK) or a negative status.  A failed call
  *     leaves the plan usable (or, for plan_create, nothing to destroy).
  *   - A plan is not thread-safe; distinct plans are independent.
@@ -195,7 +195,7 @@ int eifmm_plan_create(const eifmm_config *cfg, eifmm_plan *out);
 
 /* Builds the octree for n points xyz (device, 3 x n SoA FP64): Morton keys of
  * the leaf cells, a stable sort by (key, input index), Morton-ordered copies,
- * leaf ranges, active boxes per level and the near lists.  Returns
+ * leaf ranges, active boxes per level and the near field's chunks.  Returns
  * EIFMM_EDOMAIN if a point is outside [lo, lo+L]^3 or not finite (the plan then
  * has no points).  Waits for the box counts (see the conventions above). */
 int eifmm_set_points(eifmm_plan plan, const double *xyz_dev, void *hip_stream);

@@ -246,12 +246,11 @@ int setup_workspaces(eifmm_plan h, double *shared_ws) {
   TRY(dalloc(&P.keys_tmp, nn, tr));
   TRY(dalloc(&P.idx, nn, tr));
   TRY(dalloc(&P.idx_tmp, nn, tr));
-  TRY(dalloc(&P.hist, (size_t)256 * P.ntiles_sort, tr));
+  TRY(dalloc(&P.hist, ((size_t)P.ntiles_sort << kSortBits), tr));
   const int64_t nleaf = (int64_t)1 << (3 * depth);
   TRY(dalloc(&P.leaf_start, nleaf + 1, tr));
   if (P.nt) {
     TRY(dalloc(&P.tgt_begin, nleaf + 1, tr));
-    TRY(dalloc(&P.xin, 3 * nn, tr));
   }
   size_t maxcap = 1;
   for (int k = 0; k <= depth; ++k) {
@@ -264,23 +263,21 @@ int setup_workspaces(eifmm_plan h, double *shared_ws) {
     TRY(dalloc(&D.cls, D.cap, tr));
     if (k >= 2 && k <= kMaxOrderLevel) TRY(dalloc(&D.ord, D.cap, tr));
   }
-  const size_t scan_len = std::max<size_t>((size_t)256 * P.ntiles_sort, maxcap + 2);
+  const size_t scan_len = std::max<size_t>((size_t)P.ntiles_sort << kSortBits, maxcap + 2);
   TRY(dalloc(&P.scan_tmp, scan_len / 1024 + 64, tr));
   {
     size_t blocks = 1;  // blocks of 256 boxes over the levels of the active-box compaction
     for (int k = std::min(2, depth); k <= depth; ++k) blocks += ((size_t)1 << (3 * k)) / 256 + 1;
-    TRY(dalloc(&P.blkcnt, blocks * 9, tr));
+    TRY(dalloc(&P.blkcnt, blocks * kActCols, tr));
   }
   TRY(dalloc(&P.list_cnt, maxcap + 2, tr));
   // the counter block and, right after it, the tree's error flag (one clear and
   // one copy to the host cover both)
   TRY(dalloc(&P.counts_dev, (size_t)16 * kMaxLevels + 1, tr));
   P.errflag = P.counts_dev + 16 * kMaxLevels;
-  P.near_cap = (size_t)27 * P.ld[depth].cap;
-  TRY(dalloc(&P.near_ptr, P.ld[depth].cap + 2, tr));
-  TRY(dalloc(&P.near_src, P.near_cap, tr));
   TRY(dalloc(&P.chunk_ptr, P.ld[depth].cap + 2, tr));
-  TRY(dalloc(&P.npairs_dev, 2, tr));
+  TRY(dalloc(&P.chunk_leaf, P.ld[depth].cap + (size_t)nn / 32 + 1, tr));
+  TRY(dalloc(&P.npairs_dev, 3, tr));
   TRY(dalloc(&P.sig, (size_t)nn * R, tr));
   TRY(dalloc(&P.fnear, (size_t)nn * R, tr));
   for (int k = 2; k <= depth; ++k) {
@@ -634,26 +631,13 @@ int eifmm_plan_create(const eifmm_config *cfg, eifmm_plan *out) {
 }
 
 namespace {
-// tree build over xyz (n points, SoA); with separate targets the sources and
-// the targets are first copied into one array (sources first)
+// tree build over xyz (the sources, SoA) and, with separate targets, tgt
 int set_points_impl(eifmm_plan h, const double *xyz, const double *tgt, void *stream) {
   Plan &P = h->P;
   hipSetDevice(P.device);
   P.points_set = false;
   P.jobs.nrhs = -1;
   hipStream_t s = (hipStream_t)stream;
-  if (P.nt) {
-    for (int a = 0; a < 3; ++a) {
-      if (P.ns > 0 &&
-          hipMemcpyAsync(P.xin + a * P.n, xyz + a * P.ns, sizeof(double) * P.ns,
-                         hipMemcpyDeviceToDevice, s) != hipSuccess)
-        return EIFMM_EHIP;
-      if (hipMemcpyAsync(P.xin + a * P.n + P.ns, tgt + a * P.nt, sizeof(double) * P.nt,
-                         hipMemcpyDeviceToDevice, s) != hipSuccess)
-        return EIFMM_EHIP;
-    }
-    xyz = P.xin;
-  }
   if (P.timing == 1) {
     // tree time is recorded as one phase
     EventPair e;
@@ -666,12 +650,12 @@ int set_points_impl(eifmm_plan h, const double *xyz, const double *tgt, void *st
     }
     e.phase = EIFMM_PH_TREE;
     hipEventRecord(e.a, s);
-    int st = tree_build(P, xyz, s);
+    int st = tree_build(P, xyz, tgt, s);
     hipEventRecord(e.b, s);
     P.ev_pending.push_back(e);
     if (st) return st;
   } else {
-    int st = tree_build(P, xyz, s);
+    int st = tree_build(P, xyz, tgt, s);
     if (st) return st;
   }
   P.points_set = true;

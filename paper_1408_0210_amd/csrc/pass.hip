@@ -96,14 +96,11 @@ __host__ __device__ inline double dev_param(int kind, double p) {
 // search over the first chunk (leaf, point) of every problem.
 //
 // Near field and L2P work on chunks of up to 32 consecutive targets of a leaf
-// (chunk_ptr: exclusive prefix sum of ceil(count / 32) over the active leaves),
+// (chunk_ptr: exclusive prefix sum of ceil(count / 32) over the active leaves;
+// chunk_leaf: the leaf of each),
 // one chunk per 64-lane workgroup whose two halves share the chunk's work, so
 // a crowded leaf of a clustered cloud spreads over many workgroups and a sparse
 // one (~30 points) does not idle half a wave.
-
-__device__ inline int chunk_leaf(const int *__restrict__ chunk_ptr, int nleaf, int c) {
-  return find_last_le(nleaf, c, [&](int m) { return (int64_t)chunk_ptr[m]; });
-}
 
 // the descriptor of work item b (a chunk or a leaf of the launch) and b's index
 // within its problem
@@ -169,32 +166,53 @@ struct NearSrc {
   int own_lo, own_hi;
 };
 
-// pre[e] = first source number of neighbour e, start[e] = its first point
+// pre[e] = first source number of neighbour e, start[e] = its first point.  Lane q < 27
+// looks up the box at offset (q % 3, q / 3 % 3, q / 9) - 1 of leaf j in the leaf ranges;
+// the boxes that hold sources are numbered in key order (the order of their points), by
+// counting the smaller keys.  No near list is read or built (a list's two passes over
+// the boxes took 43-63 us of every tree, and reading it three dependent loads).
 __device__ inline NearSrc near_sources(const LeafDesc &D, int j, int *pre, int *start) {
   const int lane = threadIdx.x;
-  const int q0 = D.near_ptr[j], nq = D.near_ptr[j + 1] - q0;
-  int cnt = 0;
-  bool own = false;
-  if (lane < nq) {
-    const int a = D.near_src[q0 + lane];
-    const uint32_t sk = D.act[a];
-    start[lane] = D.ls[sk];
-    cnt = D.se[sk] - D.ls[sk];
-    own = a == j;
+  const uint32_t own = D.act[j];
+  const int side = 1 << D.depth;
+  const int m0 = (int)morton_axis(own, 0) + lane % 3 - 1,
+            m1 = (int)morton_axis(own, 1) + lane / 3 % 3 - 1,
+            m2 = (int)morton_axis(own, 2) + lane / 9 - 1;
+  uint32_t key = 0xffffffffu;
+  int cnt = 0, first = 0;
+  if (lane < 27 && m0 >= 0 && m1 >= 0 && m2 >= 0 && m0 < side && m1 < side && m2 < side) {
+    const uint32_t k = morton_encode((uint32_t)m0, (uint32_t)m1, (uint32_t)m2);
+    first = D.ls[k];
+    cnt = D.se[k] - first;
+    if (cnt > 0) key = k;
   }
-  const unsigned long long ob = __ballot(own);
-  // inclusive scan of cnt over the (at most 27) lanes
-  int v = cnt;
+  const bool have = cnt > 0;
+  const unsigned long long hb = __ballot(have);
+  int rank = 0;
+#pragma unroll
+  for (int q = 0; q < 27; ++q)
+    rank += (uint32_t)__builtin_amdgcn_readlane((int)key, q) < key ? 1 : 0;
+  if (have) {
+    start[rank] = first;
+    pre[rank + 1] = cnt;
+  }
+  if (lane == 0) pre[0] = 0;
+  __syncthreads();
+  const int nq = (int)__popcll(hb);
+  // inclusive scan of the counts over the (at most 27) neighbours
+  int v = lane < nq ? pre[lane + 1] : 0;
 #pragma unroll
   for (int o = 1; o < 32; o <<= 1) {
     const int u = __shfl_up(v, o);
     if ((lane & 31) >= o) v += u;
   }
-  if (lane < nq) pre[lane + 1] = v;
-  if (lane == 0) pre[0] = 0;
   __syncthreads();
-  const int eo = __ffsll(ob) - 1;  // the own leaf's place in the list (-1: absent)
-  return NearSrc{nq, pre[nq], eo >= 0 ? pre[eo] : 0, eo >= 0 ? pre[eo + 1] : 0};
+  if (lane < nq) pre[lane + 1] = v;
+  __syncthreads();
+  // the own leaf is offset 13 (it may hold targets only)
+  const bool self = (hb >> 13) & 1ull;
+  const int eo = __builtin_amdgcn_readlane(rank, 13);
+  return NearSrc{nq, pre[nq], self ? pre[eo] : 0, self ? pre[eo + 1] : 0};
 }
 
 // point index of source number v (0 <= v < total); e is the neighbour of the
@@ -243,7 +261,7 @@ __global__ __launch_bounds__(64, KIND == EIFMM_K_COSR ? 3 : 1) void k_p2p64(
   const int nrhs = D.nrhs;
   const double *__restrict__ xyz = D.xyz;
   const double *__restrict__ sig = D.sig;
-  const int j = chunk_leaf(D.chunk_ptr, D.nleaf, c);
+  const int j = D.chunk_leaf[c];
   const ChunkLanes CL = chunk_lanes(D, j, c, lane, RB == 1);
   const int i = CL.i;
   const bool tv = CL.tv;
@@ -351,7 +369,7 @@ __global__ __launch_bounds__(64) void k_p2p32(LeafDesc one, const LeafDesc *__re
   const float p = (float)D.p;
   const double *__restrict__ xyz = D.xyz;
   const double *__restrict__ sig = D.sig;
-  const int j = chunk_leaf(D.chunk_ptr, D.nleaf, c);
+  const int j = D.chunk_leaf[c];
   // (several RHS too: 64 RHS on 2^20 points, 264 -> 261 ms)
   const ChunkLanes CL = chunk_lanes(D, j, c, lane, true);
   const int i = CL.i;
@@ -553,7 +571,7 @@ __global__ __launch_bounds__(64) void k_l2p(LeafDesc one, IoDesc ione,
   const int64_t n = D.n;
   double *sX = sm, *sl = sm + 3 * dp;
   const int lane = threadIdx.x;
-  const int j = chunk_leaf(D.chunk_ptr, D.nleaf, c);
+  const int j = D.chunk_leaf[c];
   const uint32_t key = D.act[j];
   // the chunk's lanes as in the near field: 64 / P lanes per target, each
   // summing one of 64 / P equal ranges of the d terms (P = 32: two halves)
@@ -2073,8 +2091,7 @@ LeafDesc leaf_desc(const Plan &P, int nrhs) {
   D.se = P.nt ? P.tgt_begin : P.leaf_start + 1;
   D.tb = P.nt ? P.tgt_begin : P.leaf_start;
   D.chunk_ptr = P.chunk_ptr;
-  D.near_ptr = P.near_ptr;
-  D.near_src = P.near_src;
+  D.chunk_leaf = P.chunk_leaf;
   D.perm = P.idx;
   D.xyz = P.xyz;
   D.X = P.ld[depth].X;
@@ -2088,6 +2105,7 @@ LeafDesc leaf_desc(const Plan &P, int nrhs) {
   D.toff = P.nt ? P.ns : 0;
   D.nleaf = (int)P.nact[depth];
   D.nrhs = nrhs;
+  D.depth = depth;
   D.d = depth >= 2 ? P.lh[depth].d : 0;
   D.dp = depth >= 2 ? P.lh[depth].dp : 0;
   D.dL = depth >= 2 ? P.lh[depth].dB : 0;

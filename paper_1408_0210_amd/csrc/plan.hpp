@@ -17,6 +17,8 @@ constexpr int kNumOffsets = 316;  // 7^3 - 3^3 distinct M2L offsets (Sec. 4.2)
 constexpr int kMaxRank2 = 96;     // largest second-stage rank the factored M2L takes
 constexpr int kM2l2RbMin = 4, kM2l2RbMax = 16;  // 16-row blocks of r the factored M2L takes
 
+constexpr int kSortBits = 9;   // most bits of a radix-sort digit
+constexpr int kActCols = 10;   // counts per block of the active-box compaction (tree.hip)
 // FP64 M2L on the int8 matrix cores (m2l.hip): digits per operand, and the columns'
 // length padded to whole 64-element chunks
 constexpr int kDigits = 7;
@@ -146,7 +148,7 @@ struct LeafDesc {
   const int *se;            // sources of leaf key: [ls[key], se[key])
   const int *tb;            // targets of leaf key: [tb[key], ls[key + 1])
   const int *chunk_ptr;     // first 32-target chunk of each active leaf
-  const int *near_ptr, *near_src;
+  const int *chunk_leaf;    // active leaf of each chunk
   const int *perm;          // sorted position -> input index
   const double *xyz;        // sorted points
   const double *X;          // leaf-level EIM points X (d x 3): P2M
@@ -156,7 +158,7 @@ struct LeafDesc {
   int64_t n;
   int64_t nsrc;             // input indices below nsrc are sources (sigma rows)
   int64_t toff;             // target t has input index toff + t (f row t)
-  int nleaf, nrhs, d, dp;
+  int nleaf, nrhs, d, dp, depth;
   int dL, dpL;              // size of lhat (L2P)
   double lo0, lo1, lo2, h, p;  // domain corner, leaf width, device kernel parameter
   int64_t chunk_base, leaf_base, pt_base;  // batch launches: first chunk / leaf / element
@@ -292,7 +294,6 @@ struct Plan {
   // points: input index i < ns is source i, ns + t is target t.
   int64_t n = 0;
   int64_t ns = 0, nt = 0;       // sources; separate targets (0: targets = sources)
-  double *xin = nullptr;        // separate targets: sources then targets, SoA 3 x n
   int *tgt_begin = nullptr;     // separate targets: first target of each leaf [8^depth + 1]
   int ntiles_sort = 0;
   double *xyz = nullptr;        // sorted points, SoA 3 x n
@@ -307,12 +308,10 @@ struct Plan {
   int *counts_dev = nullptr;    // small counter block
   int *errflag = nullptr;       // counts_dev + 16 kMaxLevels
   int *counts_pin = nullptr;    // pinned host copy of counts_dev and errflag
-  int *near_ptr = nullptr;      // leaf level near lists (CSR over active slots)
-  int *near_src = nullptr;      // source leaf slots
-  size_t near_cap = 0;
   int *chunk_ptr = nullptr;     // per active leaf: first 32-target chunk (prefix sum)
+  int *chunk_leaf = nullptr;    // per chunk: its active leaf
   int64_t nchunk = 0;           // bound on the 32-target chunks over all leaves
-  unsigned long long *npairs_dev = nullptr;  // near-field work counters (2)
+  unsigned long long *npairs_dev = nullptr;  // near-field work counters (3)
   int64_t near_point_pairs = 0;  // target x source point pairs of the near field
   int64_t near_lane_pairs = 0;   // the same with targets rounded up to 32-target chunks
   bool counts_pending = false;   // the three counts above are still on the device
@@ -408,7 +407,7 @@ void launch_m2l8(const GemmJob *jobs, int n, int tiles, int height, int cus, dou
                  size_t ws_len, const int8_t *dvec, hipStream_t s);
 
 // device-side entry points (tree.hip, pass.hip)
-int tree_build(Plan &P, const double *xyz_in, hipStream_t s);
+int tree_build(Plan &P, const double *xyz_in, const double *tgt_in, hipStream_t s);
 int tree_counts(Plan &P);
 int lists_export(Plan &P, int level, int64_t *nactive, uint32_t *active, int64_t *near_ptr,
                  uint32_t *near_src, int64_t *il_ptr, uint32_t *il_src, int16_t *il_off);

@@ -22,17 +22,22 @@ namespace eifmm {
 
 // ---------------------------------------------------------------- keys
 // With separate targets (tbit = 1) the sort key is 2 * leaf key + (i >= tsplit),
-// so each leaf's sources precede its targets.  Each point is also written as one
+// so each leaf's sources precede its targets; targets are read from txyz (SoA, nt of
+// them).  Each point is also written as one
 // 32-byte record (x, y, z, 0) to x4, so that the gather into Morton order reads
 // one cache line per point instead of one per coordinate.
-__global__ void k_keys(int64_t n, const double *__restrict__ xyz, double lo0, double lo1,
-                       double lo2, double L, double scale, int side, int64_t tsplit, int tbit,
+__global__ void k_keys(int64_t n, const double *__restrict__ xyz,
+                       const double *__restrict__ txyz, double lo0, double lo1, double lo2,
+                       double L, double scale, int side, int64_t tsplit, int tbit,
                        uint32_t *__restrict__ keys, int *__restrict__ idx,
                        int *__restrict__ err, double *__restrict__ x4) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double lo[3] = {lo0, lo1, lo2};
-  const double xv[3] = {xyz[i], xyz[n + i], xyz[2 * n + i]};
+  const bool tgt = tbit && i >= tsplit;
+  const double *x = tgt ? txyz + (i - tsplit) : xyz + i;
+  const int64_t st = tgt ? n - tsplit : tbit ? tsplit : n;
+  const double xv[3] = {x[0], x[st], x[2 * st]};
   double2 *rec = reinterpret_cast<double2 *>(x4 + 4 * i);
   rec[0] = make_double2(xv[0], xv[1]);
   rec[1] = make_double2(xv[2], 0.0);
@@ -53,27 +58,31 @@ __global__ void k_keys(int64_t n, const double *__restrict__ xyz, double lo0, do
     c[a] = (uint32_t)q;
   }
   if (bad) atomicOr(err, 1);
-  keys[i] = (morton_encode(c[0], c[1], c[2]) << tbit) | (uint32_t)(tbit && i >= tsplit);
+  keys[i] = (morton_encode(c[0], c[1], c[2]) << tbit) | (uint32_t)tgt;
   idx[i] = (int)i;
 }
 
 // ---------------------------------------------------------------- radix sort
-// Tile of kSortTile keys per block (256 threads x 4 rounds); digits of 8 bits.
+// Tile of kSortTile keys per block (256 threads x 4 rounds).  Digits of up to 9 bits,
+// as few passes as they allow and the key's bits split evenly over them: a pass is
+// launch bound on small clouds and moves 16 bytes a point on large ones, so 9 bits
+// (depth 3) take one pass and 18 (depth 6) two, one less than digits of 8 bits.
 constexpr int kSortTile = 1024;
+constexpr int kSortBins = 1 << kSortBits;
 
 __global__ __launch_bounds__(256) void k_sort_hist(const uint32_t *__restrict__ keys, int64_t n,
-                                                   int shift, unsigned *__restrict__ hist,
-                                                   int ntiles) {
-  __shared__ unsigned cnt[256];
-  const int t = threadIdx.x, tile = blockIdx.x;
-  cnt[t] = 0;
+                                                   int shift, int bits,
+                                                   unsigned *__restrict__ hist, int ntiles) {
+  __shared__ unsigned cnt[kSortBins];
+  const int t = threadIdx.x, tile = blockIdx.x, bins = 1 << bits;
+  for (int b = t; b < bins; b += 256) cnt[b] = 0;
   __syncthreads();
   for (int r = 0; r < kSortTile / 256; ++r) {
     int64_t e = (int64_t)tile * kSortTile + r * 256 + t;
-    if (e < n) atomicAdd(&cnt[(keys[e] >> shift) & 255u], 1u);
+    if (e < n) atomicAdd(&cnt[(keys[e] >> shift) & (unsigned)(bins - 1)], 1u);
   }
   __syncthreads();
-  hist[(int64_t)t * ntiles + tile] = cnt[t];
+  for (int b = t; b < bins; b += 256) hist[(int64_t)b * ntiles + tile] = cnt[b];
 }
 
 // Stable scatter: within a round, lanes of a wave with equal digits are ranked
@@ -82,24 +91,25 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const uint32_t *__restrict
                                                       const int *__restrict__ iin,
                                                       uint32_t *__restrict__ kout,
                                                       int *__restrict__ iout, int64_t n,
-                                                      int shift,
+                                                      int shift, int bits,
                                                       const unsigned *__restrict__ hist,
                                                       int ntiles) {
-  __shared__ unsigned run[256];
-  __shared__ unsigned wcnt[4][256];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6, tile = blockIdx.x;
-  run[t] = hist[(int64_t)t * ntiles + tile];
+  __shared__ unsigned run[kSortBins];
+  __shared__ unsigned wcnt[4][kSortBins];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, tile = blockIdx.x, bins = 1 << bits;
+  for (int b = t; b < bins; b += 256) run[b] = hist[(int64_t)b * ntiles + tile];
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   for (int r = 0; r < kSortTile / 256; ++r) {
-    for (int q = 0; q < 4; ++q) wcnt[q][t] = 0;
+    for (int b = t; b < bins; b += 256)
+      for (int q = 0; q < 4; ++q) wcnt[q][b] = 0;
     __syncthreads();
     int64_t e = (int64_t)tile * kSortTile + r * 256 + t;
     bool valid = e < n;
     uint32_t key = valid ? kin[e] : 0u;
     int id = valid ? iin[e] : 0;
-    unsigned dig = (key >> shift) & 255u;
+    unsigned dig = (key >> shift) & (unsigned)(bins - 1);
     uint64_t mask = __ballot(valid);
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < bits; ++b) {
       bool bit = (dig >> b) & 1u;
       uint64_t bal = __ballot(bit);
       mask &= bit ? bal : ~bal;
@@ -113,7 +123,7 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const uint32_t *__restrict
       for (int q = 0; q < w; ++q) pos += wcnt[q][dig];
     }
     __syncthreads();
-    run[t] += wcnt[0][t] + wcnt[1][t] + wcnt[2][t] + wcnt[3][t];
+    for (int b = t; b < bins; b += 256) run[b] += wcnt[0][b] + wcnt[1][b] + wcnt[2][b] + wcnt[3][b];
     if (valid) {
       kout[pos] = key;
       iout[pos] = id;
@@ -158,54 +168,44 @@ __device__ inline bool box_active(const int *__restrict__ ls, int shift, int64_t
   return ls[(b + 1) << shift] > ls[b << shift];
 }
 
-// per block of 256 boxes: active count per child class and in total
 // near-field work: out[0] = point pairs (count(leaf) x the point count of its
 // near list, summed over active leaves), out[1] = the same with count(leaf)
-// rounded up to 32-target chunks (the sweeps the near-field kernels make);
-// integer atomics, so the totals are exact
+// rounded up to 32-target chunks (the sweeps the near-field kernels make), out[2] =
+// entries of the near lists (active boxes at Chebyshev distance <= 1); integer
+// atomics, so the totals are exact
 // (targets of the leaf [tb[key], ls[key + 1]), sources of a neighbour [ls, se))
-__global__ __launch_bounds__(256) void k_near_pairs(const uint32_t *__restrict__ act,
+__global__ __launch_bounds__(256) void k_near_pairs(int level, const uint32_t *__restrict__ act,
+                                                    const int *__restrict__ slot,
                                                     const int *__restrict__ ls,
                                                     const int *__restrict__ se,
-                                                    const int *__restrict__ tb,
-                                                    const int *__restrict__ near_ptr,
-                                                    const int *__restrict__ near_src, int nact,
+                                                    const int *__restrict__ tb, int nact,
                                                     unsigned long long *__restrict__ out) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= nact) return;
   const uint32_t key = act[j];
-  long long src = 0;
-  for (int q = near_ptr[j]; q < near_ptr[j + 1]; ++q) {
-    const uint32_t sk = act[near_src[q]];
+  const int side = 1 << level;
+  long long src = 0, boxes = 0;
+  for (int q = 0; q < 27; ++q) {
+    const int m0 = (int)morton_axis(key, 0) + q % 3 - 1, m1 = (int)morton_axis(key, 1) + q / 3 % 3 - 1,
+              m2 = (int)morton_axis(key, 2) + q / 9 - 1;
+    if (m0 < 0 || m1 < 0 || m2 < 0 || m0 >= side || m1 >= side || m2 >= side) continue;
+    const uint32_t sk = morton_encode((uint32_t)m0, (uint32_t)m1, (uint32_t)m2);
+    boxes += slot[sk] >= 0 ? 1 : 0;
     src += se[sk] - ls[sk];
   }
   const long long cnt = ls[key + 1] - tb[key];
   atomicAdd(out, (unsigned long long)(cnt * src));
   atomicAdd(out + 1, (unsigned long long)(((cnt + 31) / 32) * 32 * src));
-}
-
-// number of 32-target chunks of each active leaf (targets [tb[key], ls[key + 1]));
-// 0 past the active count
-__global__ __launch_bounds__(256) void k_chunk_count(const uint32_t *__restrict__ act,
-                                                     const int *__restrict__ ls,
-                                                     const int *__restrict__ tb,
-                                                     const int *__restrict__ nact, int64_t len,
-                                                     int *__restrict__ cnt) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= len) return;
-  int c = 0;
-  if (j < *nact) {
-    const uint32_t key = act[j];
-    c = (ls[key + 1] - tb[key] + 31) >> 5;
-  }
-  cnt[j] = c;
+  atomicAdd(out + 2, (unsigned long long)boxes);
 }
 
 // The active boxes of every level from 2 to the leaf level, in three launches
 // for all levels: a box is active when its subtree holds a point (a non-empty
 // range of leaf_start).  Blocks of 256 boxes; block numbers run over the levels
-// one after another (blk0), and blkcnt holds 9 counts per block (one per child
-// class, then the total).
+// one after another (blk0), and blkcnt holds kActCols counts per block: one per child
+// class, the total, and on the leaf level the 32-target chunks of its boxes (the work
+// items of the near-field and L2P kernels), whose prefix sum over the active leaves,
+// chunk_ptr, comes out of the same three launches.
 struct ActLevels {
   int n;                        // levels
   int shift[kMaxLevels];        // 3 (depth - k)
@@ -215,7 +215,17 @@ struct ActLevels {
   int *slot[kMaxLevels];        // dense map key -> compact index or -1
   int *cls[kMaxLevels];         // compact indices grouped by child class
   int *counts[kMaxLevels];      // class offsets [0, 8) and the total [8]
+  int leaf;                     // index of the leaf level (-1: not among the levels)
+  const int *tb;                // targets of leaf key: [tb[key], ls[key + 1])
+  int *chunk_ptr;               // first chunk of each active leaf, and their number
+  int *chunk_leaf;              // active leaf of each chunk
 };
+
+// 32-target chunks of leaf b
+__device__ inline int leaf_chunks(const int *__restrict__ ls, const int *__restrict__ tb,
+                                  int64_t b) {
+  return (ls[b + 1] - tb[b] + 31) >> 5;
+}
 
 __device__ inline int act_level(const ActLevels &L, int blk) {
   int q = 0;
@@ -225,52 +235,53 @@ __device__ inline int act_level(const ActLevels &L, int blk) {
 
 __global__ __launch_bounds__(256) void k_act_count(const int *__restrict__ ls, ActLevels L,
                                                    int *__restrict__ blkcnt) {
-  __shared__ int c[9];
+  __shared__ int c[kActCols];
   const int t = threadIdx.x;
-  if (t < 9) c[t] = 0;
+  if (t < kActCols) c[t] = 0;
   __syncthreads();
   const int q = act_level(L, blockIdx.x);
   const int64_t b = (int64_t)(blockIdx.x - L.blk0[q]) * 256 + t;
   if (b < L.nb[q] && box_active(ls, L.shift[q], b)) {
     atomicAdd(&c[8], 1);
     atomicAdd(&c[b & 7], 1);
+    if (q == L.leaf) atomicAdd(&c[9], leaf_chunks(ls, L.tb, b));
   }
   __syncthreads();
-  if (t < 9) blkcnt[(int64_t)blockIdx.x * 9 + t] = c[t];
+  if (t < kActCols) blkcnt[(int64_t)blockIdx.x * kActCols + t] = c[t];
 }
 
-// one block per level: exclusive scan of the 9 columns over the level's blocks
+// one block per level: exclusive scan of the columns over the level's blocks
 // (in place); the class offsets and the total go to the level's counts
 __global__ __launch_bounds__(1024) void k_act_scan(int *__restrict__ blkcnt, ActLevels L) {
-  __shared__ int part[9][1024];
+  __shared__ int part[kActCols][1024];
   const int q = blockIdx.x, t = threadIdx.x;
   const int b0 = L.blk0[q], nblk = L.blk0[q + 1] - b0;
   const int per = (nblk + 1023) / 1024;
   const int a = min(nblk, t * per), b = min(nblk, a + per);
-  int s[9], run[9];
+  int s[kActCols], run[kActCols];
 #pragma unroll
-  for (int c = 0; c < 9; ++c) s[c] = 0;
+  for (int c = 0; c < kActCols; ++c) s[c] = 0;
   for (int i = a; i < b; ++i)
 #pragma unroll
-    for (int c = 0; c < 9; ++c) s[c] += blkcnt[(int64_t)(b0 + i) * 9 + c];
+    for (int c = 0; c < kActCols; ++c) s[c] += blkcnt[(int64_t)(b0 + i) * kActCols + c];
 #pragma unroll
-  for (int c = 0; c < 9; ++c) part[c][t] = s[c];
+  for (int c = 0; c < kActCols; ++c) part[c][t] = s[c];
   __syncthreads();
   for (int off = 1; off < 1024; off <<= 1) {
-    int v[9];
+    int v[kActCols];
 #pragma unroll
-    for (int c = 0; c < 9; ++c) v[c] = t >= off ? part[c][t - off] : 0;
+    for (int c = 0; c < kActCols; ++c) v[c] = t >= off ? part[c][t - off] : 0;
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < 9; ++c) part[c][t] += v[c];
+    for (int c = 0; c < kActCols; ++c) part[c][t] += v[c];
     __syncthreads();
   }
 #pragma unroll
-  for (int c = 0; c < 9; ++c) run[c] = part[c][t] - s[c];
+  for (int c = 0; c < kActCols; ++c) run[c] = part[c][t] - s[c];
   for (int i = a; i < b; ++i)
 #pragma unroll
-    for (int c = 0; c < 9; ++c) {
-      const int64_t o = (int64_t)(b0 + i) * 9 + c;
+    for (int c = 0; c < kActCols; ++c) {
+      const int64_t o = (int64_t)(b0 + i) * kActCols + c;
       const int v = blkcnt[o];
       blkcnt[o] = run[c];
       run[c] += v;
@@ -282,12 +293,13 @@ __global__ __launch_bounds__(1024) void k_act_scan(int *__restrict__ blkcnt, Act
       off += part[c][1023];
     }
     L.counts[q][8] = part[8][1023];
+    if (q == L.leaf) L.chunk_ptr[part[8][1023]] = part[9][1023];
   }
 }
 
 __global__ __launch_bounds__(256) void k_act_scatter(const int *__restrict__ ls, ActLevels L,
                                                      const int *__restrict__ blkoff) {
-  __shared__ int wtot[4][9];
+  __shared__ int wtot[4][kActCols];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int q = act_level(L, blockIdx.x);
   const int64_t b = (int64_t)(blockIdx.x - L.blk0[q]) * 256 + t;
@@ -301,6 +313,19 @@ __global__ __launch_bounds__(256) void k_act_scatter(const int *__restrict__ ls,
     wtot[w][8] = (int)__popcll(ball);
     for (int k = 0; k < 8; ++k) wtot[w][k] = (int)__popcll(bc[k]);
   }
+  // chunks of the boxes before this one in its wave
+  const bool leaf = q == L.leaf;
+  const int ch = leaf && a ? leaf_chunks(ls, L.tb, b) : 0;
+  int rch = 0;
+  if (leaf) {
+    int v = ch;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(v, o);
+      if (lane >= o) v += u;
+    }
+    rch = v - ch;
+    if (lane == 63) wtot[w][9] = v;
+  }
   __syncthreads();
   if (b >= L.nb[q]) return;
   if (!a) {
@@ -311,10 +336,16 @@ __global__ __launch_bounds__(256) void k_act_scatter(const int *__restrict__ ls,
   for (int k = 0; k < w; ++k) {
     rt += wtot[k][8];
     rc += wtot[k][c];
+    if (leaf) rch += wtot[k][9];
   }
-  const int64_t bo = (int64_t)blockIdx.x * 9;
+  const int64_t bo = (int64_t)blockIdx.x * kActCols;
   const int pos = blkoff[bo + 8] + rt;
   L.act[q][pos] = (uint32_t)b;
+  if (leaf) {
+    const int c0 = blkoff[bo + 9] + rch;
+    L.chunk_ptr[pos] = c0;
+    for (int e = 0; e < ch; ++e) L.chunk_leaf[c0 + e] = pos;
+  }
   L.slot[q][b] = pos;
   L.cls[q][L.counts[q][c] + blkoff[bo + c] + rc] = pos;
 }
@@ -503,14 +534,17 @@ namespace {
 int sort_points(Plan &P, hipStream_t s) {
   const int64_t n = P.n;
   const int bits = 3 * P.depth + (P.nt ? 1 : 0);
+  const int passes = (bits + kSortBits - 1) / kSortBits;
+  const int width = passes ? (bits + passes - 1) / passes : 0;
   const int ntiles = (int)((n + kSortTile - 1) / kSortTile);
   uint32_t *ka = P.keys, *kb = P.keys_tmp;
   int *ia = P.idx, *ib = P.idx_tmp;
-  for (int shift = 0; shift < bits; shift += 8) {
-    hipLaunchKernelGGL(k_sort_hist, dim3(ntiles), dim3(256), 0, s, ka, n, shift, P.hist, ntiles);
-    scan_exclusive_u32(P.hist, P.hist, (int64_t)256 * ntiles, P.scan_tmp, s);
+  for (int shift = 0; shift < bits; shift += width) {
+    hipLaunchKernelGGL(k_sort_hist, dim3(ntiles), dim3(256), 0, s, ka, n, shift, width, P.hist,
+                       ntiles);
+    scan_exclusive_u32(P.hist, P.hist, (int64_t)ntiles << width, P.scan_tmp, s);
     hipLaunchKernelGGL(k_sort_scatter, dim3(ntiles), dim3(256), 0, s, ka, ia, kb, ib, n, shift,
-                       P.hist, ntiles);
+                       width, P.hist, ntiles);
     std::swap(ka, kb);
     std::swap(ia, ib);
   }
@@ -524,9 +558,14 @@ int sort_points(Plan &P, hipStream_t s) {
 // active boxes of levels k0..k1
 void build_active(Plan &P, int k0, int k1, hipStream_t s) {
   ActLevels L{};
+  L.leaf = -1;
+  L.tb = P.nt ? P.tgt_begin : P.leaf_start;
+  L.chunk_ptr = P.chunk_ptr;
+  L.chunk_leaf = P.chunk_leaf;
   int blk = 0;
   for (int k = k0; k <= k1; ++k) {
     const int q = L.n++;
+    if (k == P.depth) L.leaf = q;
     L.shift[q] = 3 * (P.depth - k);
     L.nb[q] = (int64_t)1 << (3 * k);
     L.blk0[q] = blk;
@@ -542,11 +581,10 @@ void build_active(Plan &P, int k0, int k1, hipStream_t s) {
   hipLaunchKernelGGL(k_act_scatter, dim3(blk), dim3(256), 0, s, P.leaf_start, L, P.blkcnt);
 }
 
-// CSR list for level k into (ptr, src, off).  bounded: the entry count cannot
-// exceed cap (27 near entries per box), so it is not read back and 0 is
-// returned; otherwise returns the entry count, or -1 if it exceeds cap.
+// CSR list for level k into (ptr, src, off): the entry count, or -1 if it exceeds cap
+// (exports only: the pass reads a leaf's neighbours from leaf_start)
 int64_t build_list(Plan &P, int k, int mode, int *ptr, int *src, int16_t *off, size_t cap,
-                   bool bounded, hipStream_t s) {
+                   hipStream_t s) {
   LevelDev &L = P.ld[k];
   const int *nact = P.counts_dev + 16 * k + 8;
   const int grid = (int)((L.cap + 1 + 127) / 128);
@@ -559,11 +597,9 @@ int64_t build_list(Plan &P, int k, int mode, int *ptr, int *src, int16_t *off, s
                        cnt, nullptr, nullptr, P.code2id);
   scan_exclusive_i32(cnt, ptr, (int64_t)L.cap + 1, P.scan_tmp, s);
   int total = 0;
-  if (!bounded) {
-    hipMemcpyAsync(&total, ptr + P.nact[k], sizeof(int), hipMemcpyDeviceToHost, s);
-    hipStreamSynchronize(s);
-    if ((size_t)total > cap) return -1;
-  }
+  hipMemcpyAsync(&total, ptr + P.nact[k], sizeof(int), hipMemcpyDeviceToHost, s);
+  hipStreamSynchronize(s);
+  if ((size_t)total > cap) return -1;
   if (mode == 0)
     hipLaunchKernelGGL(k_list<0>, dim3(grid), dim3(128), 0, s, k, L.act, nact, L.slot, ptr,
                        nullptr, src, nullptr, nullptr);
@@ -586,18 +622,17 @@ void il_count_launch(Plan &P, hipStream_t s) {
   }
 }
 
-int tree_build(Plan &P, const double *xyz_in, hipStream_t s) {
+int tree_build(Plan &P, const double *xyz_in, const double *tgt_in, hipStream_t s) {
   const int64_t n = P.n;
   const int depth = P.depth;
   const int side = 1 << depth;
   const double scale = std::ldexp(1.0, depth) / P.cfg.L;
   const int tbit = P.nt ? 1 : 0;
-  const int *tb = tbit ? P.tgt_begin : P.leaf_start;
   // the counter block and the error flag after it
   hipMemsetAsync(P.counts_dev, 0, sizeof(int) * (16 * kMaxLevels + 1), s);
   if (n > 0) {
     hipLaunchKernelGGL(k_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, xyz_in,
-                       P.cfg.lo[0], P.cfg.lo[1], P.cfg.lo[2], P.cfg.L, scale, side, P.ns, tbit,
+                       tgt_in, P.cfg.lo[0], P.cfg.lo[1], P.cfg.lo[2], P.cfg.L, scale, side, P.ns, tbit,
                        P.keys, P.idx, P.errflag, P.xyz4);
     sort_points(P, s);
     hipLaunchKernelGGL(k_gather_points, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n,
@@ -612,8 +647,7 @@ int tree_build(Plan &P, const double *xyz_in, hipStream_t s) {
   build_active(P, std::min(2, depth), depth, s);
   if (!P.il_lazy) il_count_launch(P, s);
   // the counts and the error flag, into pinned memory; the host waits for this
-  // copy only, while the order, the near lists and the chunks below (which read
-  // the counts on the device) run
+  // copy only, while the order below (which reads the counts on the device) runs
   int *host_counts = P.counts_pin;
   hipMemcpyAsync(host_counts, P.counts_dev, sizeof(int) * (16 * kMaxLevels + 1),
                  hipMemcpyDeviceToHost, s);
@@ -631,19 +665,6 @@ int tree_build(Plan &P, const double *xyz_in, hipStream_t s) {
       L.ord[q] = P.ld[k].ord;
     }
     if (L.n) hipLaunchKernelGGL(k_m2l_order, dim3(8 * L.n), dim3(1024), 0, s, L);
-  }
-  // near lists of the leaf level (used by the near-field pass); at most 27
-  // entries per box, within near_cap = 27 cap
-  build_list(P, depth, 0, P.near_ptr, P.near_src, nullptr, P.near_cap, true, s);
-  // 32-target chunks of the leaves (the work of the near-field and L2P kernels).
-  // The grid is launched with the bound nact + ceil(n / 32) on the chunk count,
-  // and workgroups past chunk_ptr[nact] exit, so the count is not read back.
-  {
-    const int64_t cap = P.ld[depth].cap;
-    hipLaunchKernelGGL(k_chunk_count, dim3((unsigned)((cap + 1 + 255) / 256)), dim3(256), 0, s,
-                       P.ld[depth].act, P.leaf_start, tb, P.counts_dev + 16 * depth + 8, cap + 1,
-                       P.list_cnt);
-    scan_exclusive_i32(P.list_cnt, P.chunk_ptr, cap + 1, P.scan_tmp, s);
   }
   hipError_t e = hipEventSynchronize(P.ev_counts);
   const int err = host_counts[16 * kMaxLevels];
@@ -663,7 +684,10 @@ int tree_build(Plan &P, const double *xyz_in, hipStream_t s) {
     }
   }
   P.il_pending = P.il_lazy;
-  P.nchunk = P.nact[depth] > 0 ? P.nact[depth] + (n + 31) / 32 : 0;  // the near-field pair counts (statistics) are taken when they are read
+  // the near-field and L2P launches use a bound on the chunks (workgroups past
+  // chunk_ptr[nact] exit), so their number is not read back
+  P.nchunk = P.nact[depth] > 0 ? P.nact[depth] + (n + 31) / 32 : 0;
+  // the near-field pair counts (statistics) are taken when they are read
   P.counts_pending = true;
   e = hipGetLastError();
   if (e != hipSuccess) {
@@ -694,24 +718,21 @@ int tree_counts(Plan &P) {
   }
   if (!P.counts_pending) return EIFMM_OK;
   const int depth = P.depth;
-  int total = 0;
-  unsigned long long npairs[2] = {0, 0};
+  unsigned long long npairs[3] = {0, 0, 0};
   if (P.nact[depth] > 0) {
     // the tree is complete once the device is idle
     if (hipDeviceSynchronize() != hipSuccess) return EIFMM_EHIP;
     const int *se = P.nt ? P.tgt_begin : P.leaf_start + 1;
     const int *tb = P.nt ? P.tgt_begin : P.leaf_start;
-    hipMemsetAsync(P.npairs_dev, 0, 2 * sizeof(unsigned long long), nullptr);
+    hipMemsetAsync(P.npairs_dev, 0, 3 * sizeof(unsigned long long), nullptr);
     hipLaunchKernelGGL(k_near_pairs, dim3((unsigned)((P.nact[depth] + 255) / 256)), dim3(256), 0,
-                       nullptr, P.ld[depth].act, P.leaf_start, se, tb, P.near_ptr, P.near_src,
+                       nullptr, depth, P.ld[depth].act, P.ld[depth].slot, P.leaf_start, se, tb,
                        (int)P.nact[depth], P.npairs_dev);
   }
   if (P.nact[depth] > 0 &&
-      (hipMemcpy(&total, P.near_ptr + P.nact[depth], sizeof(int), hipMemcpyDeviceToHost) !=
-           hipSuccess ||
-       hipMemcpy(npairs, P.npairs_dev, sizeof(npairs), hipMemcpyDeviceToHost) != hipSuccess))
+      hipMemcpy(npairs, P.npairs_dev, sizeof(npairs), hipMemcpyDeviceToHost) != hipSuccess)
     return EIFMM_EHIP;
-  P.near_total = total;
+  P.near_total = (int64_t)npairs[2];
   P.near_point_pairs = (int64_t)npairs[0];
   P.near_lane_pairs = (int64_t)npairs[1];
   P.counts_pending = false;
@@ -756,7 +777,7 @@ int lists_export(Plan &P, int level, int64_t *nactive, uint32_t *active, int64_t
       continue;
     }
     int64_t tot =
-        build_list(P, level, mode, dptr, dsrc, doff, mode == 0 ? cap_near : cap_il, false, s);
+        build_list(P, level, mode, dptr, dsrc, doff, mode == 0 ? cap_near : cap_il, s);
     if (tot < 0) {
       rc = EIFMM_ENOMEM;
       break;
