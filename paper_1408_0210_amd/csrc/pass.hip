@@ -756,6 +756,138 @@ __device__ inline void trsm_body(const SolveDesc &D, double *zs) {
   }
 }
 
+// The same solve by four waves per 16 columns, for FP64 results.  Each wave owns every
+// fourth row tile: once tile bi is solved (by every wave for itself, from the right-hand
+// side in LDS), each takes its product off its own rows, so the chain from one tile to
+// the next is four products, an LDS hand-off and four more instead of a whole row of
+// products, and the loads of the next tile's operators (which need no solved value) are
+// in flight meanwhile.  On 287 rows a solve of 576 columns takes 46 us against 85 by one
+// wave, half a solve of 4,096 columns 26 against 62; on 37,440 columns, where the
+// matrix cores are busy either way, the repeated diagonal products cost more than the
+// waits (157 against 126 us), so the one-wave form serves more than kSolveFew groups.
+// The products of a row are added in another order, which changes FP64 results in the
+// last bits; the FP32 copy of a solve (mixed precision, uncompressed levels) would
+// change in its own last bit, so the mixed pass solves for What by the one-wave form.
+constexpr int kSolveOwn = 5;  // tiles of a wave with their operators loaded ahead
+constexpr int kSolveFew = 1024;  // 16-column groups up to which the four-wave form serves
+__device__ inline void trsm4_body(const SolveDesc &D, double *zs) {
+  typedef double v4 __attribute__((ext_vector_type(4)));
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = ((int)blockIdx.x - D.blk_start) * 16 + (lane & 15);
+  const bool cv = c < D.ncols;
+  const int dp = D.dp, nb = dp >> 4, rs = lane >> 4;
+  const double *x = D.in + (int64_t)(cv ? c : 0) * dp;
+  double *y = D.out + (int64_t)(cv ? c : 0) * dp;
+  for (int bi = w; bi < nb; bi += 4)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) zs[(bi * 4 + q) * 64 + lane] = cv ? x[16 * bi + rs + 4 * q] : 0.0;
+  // one triangle: step s solves tile bi(s); FWD from the first tile down, else from the
+  // last one up; store: the solved tiles are the result
+  auto sweep = [&](auto fwd, const double *T, bool store) {
+    constexpr bool FWD = decltype(fwd)::value;
+    auto tile_of = [&](int s) { return FWD ? s : nb - 1 - s; };
+    // the wave's rows after step s: own0(s), own0(s) + DIR 4, ..., count(s) of them
+    constexpr int DIR = FWD ? 4 : -4;
+    auto own0 = [&](int s) {
+      return FWD ? s + 1 + ((w - (s + 1)) & 3) : nb - 2 - s - ((nb - 2 - s - w) & 3);
+    };
+    auto count = [&](int s) {
+      const int b = own0(s);
+      return FWD ? (b < nb ? (nb - 1 - b) / 4 + 1 : 0) : (b >= 0 ? b / 4 + 1 : 0);
+    };
+    // diagonal and own operators of a step, loaded two steps ahead
+    struct Ops {
+      double dg[4], a[kSolveOwn][4];
+    };
+    Ops o0, o1;
+    auto load = [&](int s, Ops &o) {
+      if (s >= nb) return;
+      const int bi = tile_of(s), n = count(s);
+      const double *Tl = T + lane;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o.dg[k] = Tl[((int64_t)bi * nb + bi) * 256 + k * 64];
+      const double *Tr = Tl + ((int64_t)own0(s) * nb + bi) * 256;
+#pragma unroll
+      for (int i = 0; i < kSolveOwn; ++i)
+        if (i < n)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) o.a[i][k] = Tr[(int64_t)i * DIR * nb * 256 + k * 64];
+    };
+    load(0, o0);
+    load(1, o1);
+    v4 zp = {0, 0, 0, 0};
+    // the products of the wave's first N rows with the solved tile z, all rows at once
+    auto rows = [&](auto N, int b0, const Ops &o, const v4 &z) {
+      constexpr int n = decltype(N)::value;
+      double *zr = zs + b0 * 256 + lane;
+      v4 r[n];
+#pragma unroll
+      for (int i = 0; i < n; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r[i][q] = zr[i * DIR * 256 + q * 64];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < n; ++i)
+          r[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a[i][k], z[k], r[i], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < n; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) zr[i * DIR * 256 + q * 64] = r[i][q];
+    };
+    auto step = [&](int s, Ops &o) {
+      const int bi = tile_of(s), n = count(s), b0 = own0(s);
+      lds_barrier();  // the rows' right-hand sides are up to date
+      if (s > 0 && w == ((s - 1) & 3)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) zs[(tile_of(s - 1) * 4 + q) * 64 + lane] = zp[q];
+      }
+      v4 z = {0, 0, 0, 0};
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        z = __builtin_amdgcn_mfma_f64_16x16x4f64(o.dg[k], zs[(bi * 4 + k) * 64 + lane], z, 0, 0, 0);
+      static_assert(kSolveOwn == 5, "cases below");
+      switch (n) {
+        case 0: break;
+        case 1: rows(std::integral_constant<int, 1>{}, b0, o, z); break;
+        case 2: rows(std::integral_constant<int, 2>{}, b0, o, z); break;
+        case 3: rows(std::integral_constant<int, 3>{}, b0, o, z); break;
+        case 4: rows(std::integral_constant<int, 4>{}, b0, o, z); break;
+        default: rows(std::integral_constant<int, 5>{}, b0, o, z); break;
+      }
+      load(s + 2, o);
+      // rows further on
+      for (int i = kSolveOwn; i < n; ++i) {
+        const int bj = b0 + DIR * i;
+        v4 rr;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) rr[q] = zs[(bj * 4 + q) * 64 + lane];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          rr = __builtin_amdgcn_mfma_f64_16x16x4f64(T[((int64_t)bj * nb + bi) * 256 + k * 64 + lane],
+                                                    z[k], rr, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) zs[(bj * 4 + q) * 64 + lane] = rr[q];
+      }
+      zp = z;
+      if (store && cv && w == (s & 3)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) y[16 * bi + rs + 4 * q] = z[q];
+      }
+    };
+    for (int s = 0; s < nb; s += 2) {
+      step(s, o0);
+      if (s + 1 < nb) step(s + 1, o1);
+    }
+    if (w == ((nb - 1) & 3)) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) zs[(tile_of(nb - 1) * 4 + q) * 64 + lane] = zp[q];
+    }
+  };
+  if (D.Tf) sweep(std::true_type{}, D.Tf, D.Tb == nullptr);
+  if (D.Tb) sweep(std::false_type{}, D.Tb, true);
+}
+
 // LDS bytes of a solve launch: the solved tiles of the 16 columns
 inline size_t trsm_shm(int dp) { return sizeof(double) * 4 * 64 * (size_t)(dp / 16); }
 
@@ -766,6 +898,21 @@ __global__ __launch_bounds__(64) void k_trsm(SolveArgs A) {
   for (int q = 1; q < A.nlev; ++q)
     if ((int)blockIdx.x >= A.lv[q].blk_start) li = q;
   trsm_body(A.lv[li], zs);
+}
+
+__global__ __launch_bounds__(256) void k_trsm4(SolveArgs A) {
+  extern __shared__ double zs[];  // [nb][4][64]
+  int li = 0;
+  for (int q = 1; q < A.nlev; ++q)
+    if ((int)blockIdx.x >= A.lv[q].blk_start) li = q;
+  trsm4_body(A.lv[li], zs);
+}
+
+__global__ __launch_bounds__(256) void k_trsm4_list(const SolveDesc *__restrict__ L, int n) {
+  extern __shared__ double zs[];
+  const int li = find_last_le(n, blockIdx.x, [&](int m) { return (int64_t)L[m].blk_start; });
+  const SolveDesc D = L[li];
+  trsm4_body(D, zs);
 }
 
 // a batch: every (problem, level) of the launch, descriptors in device memory
@@ -2212,7 +2359,10 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
       shm = std::max(shm, trsm_shm(P.lh[k].dp));
     }
     A.nlev = q;
-    if (blk > 0) hipLaunchKernelGGL(k_trsm, dim3(blk), dim3(64), shm, s, A);
+    if (blk > 0 && (mixed || blk > kSolveFew))
+      hipLaunchKernelGGL(k_trsm, dim3(blk), dim3(64), shm, s, A);
+    else if (blk > 0)
+      hipLaunchKernelGGL(k_trsm4, dim3(blk), dim3(256), shm, s, A);
   }
   // step 4: M2L (with the compression projections around it when enabled)
   if (P.jobs.pre_n) {
@@ -2276,8 +2426,10 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
     A.lv[0].dp = HL.dpB;
     A.lv[0].blk_start = 0;
     A.nlev = 1;
-    if (nc > 0)
+    if (nc > 16 * kSolveFew)
       hipLaunchKernelGGL(k_trsm, dim3((nc + 15) / 16), dim3(64), trsm_shm(HL.dpB), s, A);
+    else if (nc > 0)
+      hipLaunchKernelGGL(k_trsm4, dim3((nc + 15) / 16), dim3(256), trsm_shm(HL.dpB), s, A);
   }
   // step 7: L2P and the final sum (after the near field)
   if (fork) hipStreamWaitEvent(s, P.ev_join, 0);
@@ -2805,8 +2957,11 @@ void batch_run(const BatchExec &B, hipStream_t s, const hipEvent_t *mark) {
   for (int k = B.maxdepth - 1; k >= 2; --k)
     launch_gemm_fused(B.m2m[k], MODE_M2M, false, B.sk_groups, B.sk_ws, B.dvec, s);
   tick();
-  if (B.what_blk > 0)
+  if (B.what_blk > 0 && (B.mixed || B.what_blk > kSolveFew))
     hipLaunchKernelGGL(k_trsm_list, dim3(B.what_blk), dim3(64), B.what_shm, s, B.what_dev,
+                       B.what_n);
+  else if (B.what_blk > 0)
+    hipLaunchKernelGGL(k_trsm4_list, dim3(B.what_blk), dim3(256), B.what_shm, s, B.what_dev,
                        B.what_n);
   tick();
   launch_gemm_fused(B.pre, MODE_PROJ, false, B.sk_groups, B.sk_ws, B.dvec, s);
@@ -2819,8 +2974,11 @@ void batch_run(const BatchExec &B, hipStream_t s, const hipEvent_t *mark) {
   for (int k = 3; k <= B.maxdepth; ++k)
     launch_gemm_fused(B.l2l[k], MODE_L2L, false, B.sk_groups, B.sk_ws, B.dvec, s);
   tick();
-  if (B.lhat_blk > 0)
+  if (B.lhat_blk > kSolveFew)
     hipLaunchKernelGGL(k_trsm_list, dim3(B.lhat_blk), dim3(64), B.lhat_shm, s, B.lhat_dev,
+                       B.lhat_n);
+  else if (B.lhat_blk > 0)
+    hipLaunchKernelGGL(k_trsm4_list, dim3(B.lhat_blk), dim3(256), B.lhat_shm, s, B.lhat_dev,
                        B.lhat_n);
   tick();
   run_groups(B, 2, s, mark, m);  // L2P and the final sum
