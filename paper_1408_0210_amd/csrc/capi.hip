@@ -277,6 +277,10 @@ int setup_workspaces(eifmm_plan h, double *shared_ws) {
   P.errflag = P.counts_dev + 16 * kMaxLevels;
   TRY(dalloc(&P.chunk_ptr, P.ld[depth].cap + 2, tr));
   TRY(dalloc(&P.chunk_leaf, P.ld[depth].cap + (size_t)nn / 32 + 1, tr));
+  TRY(dalloc(&P.seg_ptr, P.ld[depth].cap + 2, tr));
+  TRY(dalloc(&P.seg_leaf, P.ld[depth].cap + (size_t)nn / kSegSources + 1, tr));
+  if (depth >= 2)
+    TRY(dalloc(&P.w_ext, ((size_t)nn / kSegSources + 1) * (size_t)P.lh[depth].dp, tr));
   TRY(dalloc(&P.npairs_dev, 3, tr));
   TRY(dalloc(&P.sig, (size_t)nn * R, tr));
   TRY(dalloc(&P.fnear, (size_t)nn * R, tr));

@@ -104,15 +104,15 @@ __host__ __device__ inline double dev_param(int kind, double p) {
 
 // the descriptor of work item b (a chunk or a leaf of the launch) and b's index
 // within its problem
-template <bool BATCH, int WHICH>  // WHICH: 0 chunk, 1 leaf
+template <bool BATCH, int WHICH>  // WHICH: 0 chunk, 1 P2M segment
 __device__ inline void pick_desc_at(const LeafDesc &one, const LeafDesc *__restrict__ many,
                                     int nmany, int b, LeafDesc &D, int &local, int &prob) {
   if constexpr (BATCH) {
     prob = find_last_le(nmany, b, [&](int m) {
-      return WHICH == 0 ? many[m].chunk_base : many[m].leaf_base;
+      return WHICH == 0 ? many[m].chunk_base : many[m].seg_base;
     });
     D = many[prob];
-    local = b - (int)(WHICH == 0 ? D.chunk_base : D.leaf_base);
+    local = b - (int)(WHICH == 0 ? D.chunk_base : D.seg_base);
   } else {
     prob = 0;
     D = one;
@@ -462,7 +462,12 @@ __global__ __launch_bounds__(64) void k_p2p32(LeafDesc one, const LeafDesc *__re
 
 // ------------------------------------------------------------------ P2M
 // W^I_m = sum_{y_j in I} sigma_j K(x_m^{I_0}, y_j - c_I)  (Algorithm 3, step 1)
-// One NT-thread workgroup per leaf; rows are taken in groups of 4 NT, thread t
+// One NT-thread workgroup per leaf, or with one right-hand side per segment of up to
+// kSegSources sources of a leaf: a crowded leaf's sources spread over many workgroups
+// (32 problems with four clusters each and d = 433 spent 4.5 ms on the workgroups of a
+// few leaves of 1e4 sources).  A leaf's first segment writes W, the others their sums
+// to w_ext (extra i of the leaves before it and of its own), which k_p2m_ext adds.
+// Rows are taken in groups of 4 NT, thread t
 // owning rows m0 + t + NT u, u < 4, of group m0.  NT = 0: the launch's block size
 // (one right-hand side on leaves of many points: a whole number of waves
 // covering d_p, up to 1024, so that every wave takes one row per lane and none
@@ -477,6 +482,15 @@ __global__ __launch_bounds__(NT ? NT : 1024) void k_p2m(LeafDesc one,
   LeafDesc D;
   int j, prob;
   pick_desc<BATCH, 1>(one, many, nmany, D, j, prob);
+  int seg = 0;
+  double *Wj = nullptr;
+  if constexpr (RB == 1) {  // j: segment -> leaf
+    const int sj = j;
+    j = D.seg_leaf[sj];
+    const int s0 = D.seg_ptr[j];
+    seg = sj - s0;
+    Wj = seg == 0 ? D.W + (int64_t)j * D.dp : D.w_ext + (int64_t)(s0 - j + seg - 1) * D.dp;
+  }
   const int t = threadIdx.x;
   const int nt = NT ? NT : (int)blockDim.x;
   const int64_t n = D.n;
@@ -484,7 +498,8 @@ __global__ __launch_bounds__(NT ? NT : 1024) void k_p2m(LeafDesc one,
   const double *__restrict__ xyz = D.xyz;
   const double *__restrict__ sig = D.sig;
   const uint32_t key = D.act[j];
-  const int a = D.ls[key], b = D.se[key];
+  const int a = D.ls[key] + kSegSources * seg;
+  const int b = RB == 1 ? min(D.se[key], a + kSegSources) : D.se[key];
   const double cx = D.lo0 + ((double)morton_axis(key, 0) + 0.5) * D.h;
   const double cy = D.lo1 + ((double)morton_axis(key, 1) + 0.5) * D.h;
   const double cz = D.lo2 + ((double)morton_axis(key, 2) + 0.5) * D.h;
@@ -538,11 +553,31 @@ __global__ __launch_bounds__(NT ? NT : 1024) void k_p2m(LeafDesc one,
         if (u < nu && m < dp) {
 #pragma unroll
           for (int rr = 0; rr < RB; ++rr)
-            if (r0 + rr < nrhs)
+            if (RB == 1)
+              Wj[m] = m < d ? acc[u][rr] : 0.0;
+            else if (r0 + rr < nrhs)
               D.W[((int64_t)j * nrhs + r0 + rr) * dp + m] = m < d ? acc[u][rr] : 0.0;
         }
       }
     }
+  }
+}
+
+// adds the sums of a leaf's later segments to its first one's, in order (one workgroup
+// per segment; those that are not a leaf's first of several exit)
+template <bool BATCH>
+__global__ __launch_bounds__(256) void k_p2m_ext(LeafDesc one, const LeafDesc *__restrict__ many,
+                                                 int nmany) {
+  LeafDesc D;
+  int s, prob;
+  pick_desc<BATCH, 1>(one, many, nmany, D, s, prob);
+  const int j = D.seg_leaf[s], s0 = D.seg_ptr[j], n = D.seg_ptr[j + 1] - s0;
+  if (s != s0 || n < 2) return;
+  const double *e = D.w_ext + (int64_t)(s0 - j) * D.dp;
+  for (int m = threadIdx.x; m < D.d; m += 256) {
+    double v = D.W[(int64_t)j * D.dp + m];
+    for (int i = 0; i < n - 1; ++i) v += e[(int64_t)i * D.dp + m];
+    D.W[(int64_t)j * D.dp + m] = v;
   }
 }
 
@@ -2239,6 +2274,9 @@ LeafDesc leaf_desc(const Plan &P, int nrhs) {
   D.tb = P.nt ? P.tgt_begin : P.leaf_start;
   D.chunk_ptr = P.chunk_ptr;
   D.chunk_leaf = P.chunk_leaf;
+  D.seg_ptr = P.seg_ptr;
+  D.seg_leaf = P.seg_leaf;
+  D.w_ext = P.w_ext;
   D.perm = P.idx;
   D.xyz = P.xyz;
   D.X = P.ld[depth].X;
@@ -2324,8 +2362,11 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
   // step 1: P2M
   if (nleafa > 0) {
     Timer tm(P, s, EIFMM_PH_P2M);
-    launch_p2m<KIND, false>(nrhs, (unsigned)nleafa, HL.dp, LD, nullptr, 0, s,
+    launch_p2m<KIND, false>(nrhs, (unsigned)(nrhs == 1 ? P.nseg : nleafa), HL.dp, LD, nullptr, 0, s,
                             n > 64 * (int64_t)nleafa);
+    if (nrhs == 1 && P.nseg > nleafa)
+      hipLaunchKernelGGL((k_p2m_ext<false>), dim3((unsigned)P.nseg), dim3(256), 0, s, LD, nullptr,
+                         0);
   }
   if (fork && !fork_late) near_field(P.side);
   // step 2: M2M
@@ -2766,7 +2807,12 @@ void run_group(const BatchExec &B, const BatchGroup &g, int phase, hipStream_t s
   if (phase == 0)
     launch_p2p<KIND, true>(B.mixed, 1, g.nchunk, none, many, g.count, s);
   else if (phase == 1)
-    launch_p2m<KIND, true>(1, (unsigned)g.nleaf, g.dpmax, none, many, g.count, s);
+  {
+    launch_p2m<KIND, true>(1, (unsigned)g.nseg, g.dpmax, none, many, g.count, s);
+    if (g.nseg > g.nleaf)
+      hipLaunchKernelGGL((k_p2m_ext<true>), dim3((unsigned)g.nseg), dim3(256), 0, s, none, many,
+                         g.count);
+  }
   else
     launch_l2p<KIND, true>(1, g.nchunk, g.dpmax, none, inone, many, B.io_dev + g.first, g.count,
                            s);
@@ -2828,21 +2874,23 @@ int batch_prepare(BatchExec &B, const std::vector<Plan *> &plans_in, int m2l_rbt
   std::vector<LeafDesc> leaf(np);
   int64_t pts = 0;
   for (BatchGroup &g : B.groups) {
-    int64_t ch = 0, lf = 0;
+    int64_t ch = 0, lf = 0, sg = 0;
     for (int q = g.first; q < g.first + g.count; ++q) {
       const Plan &P = *plans[q];
       LeafDesc D = leaf_desc(P, 1);
       D.chunk_base = ch;
-      D.leaf_base = lf;
+      D.seg_base = sg;
       D.pt_base = pts;
       ch += P.nchunk;
       lf += P.nact[P.depth];
+      sg += P.nseg;
       pts += P.n;
       g.dpmax = std::max(g.dpmax, std::max(P.lh[P.depth].dp, P.lh[P.depth].dpB));
       leaf[q] = D;
     }
     g.nchunk = ch;
     g.nleaf = lf;
+    g.nseg = sg;
   }
   B.total_pts = pts;
   int st = bupload(&B.leaf_dev, leaf, B.track);

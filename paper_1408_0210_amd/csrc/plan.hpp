@@ -18,7 +18,8 @@ constexpr int kMaxRank2 = 96;     // largest second-stage rank the factored M2L 
 constexpr int kM2l2RbMin = 4, kM2l2RbMax = 16;  // 16-row blocks of r the factored M2L takes
 
 constexpr int kSortBits = 9;   // most bits of a radix-sort digit
-constexpr int kActCols = 10;   // counts per block of the active-box compaction (tree.hip)
+constexpr int kActCols = 11;   // counts per block of the active-box compaction (tree.hip)
+constexpr int kSegSources = 256;  // sources of a P2M segment
 // FP64 M2L on the int8 matrix cores (m2l.hip): digits per operand, and the columns'
 // length padded to whole 64-element chunks
 constexpr int kDigits = 7;
@@ -149,6 +150,10 @@ struct LeafDesc {
   const int *tb;            // targets of leaf key: [tb[key], ls[key + 1])
   const int *chunk_ptr;     // first 32-target chunk of each active leaf
   const int *chunk_leaf;    // active leaf of each chunk
+  // P2M, one right-hand side: the sources of a leaf in segments (first segment of each
+  // leaf, leaf of each segment); a leaf's later segments leave their sums in w_ext
+  const int *seg_ptr, *seg_leaf;
+  double *w_ext;
   const int *perm;          // sorted position -> input index
   const double *xyz;        // sorted points
   const double *X;          // leaf-level EIM points X (d x 3): P2M
@@ -161,7 +166,7 @@ struct LeafDesc {
   int nleaf, nrhs, d, dp, depth;
   int dL, dpL;              // size of lhat (L2P)
   double lo0, lo1, lo2, h, p;  // domain corner, leaf width, device kernel parameter
-  int64_t chunk_base, leaf_base, pt_base;  // batch launches: first chunk / leaf / element
+  int64_t chunk_base, seg_base, pt_base;  // batch launches: first chunk / segment / element
 };
 
 // Caller buffers of one evaluation: sigma (input order, column stride ld) and f.
@@ -203,7 +208,7 @@ struct DigitDesc {
 struct BatchGroup {
   int kind = 0;
   int first = 0, count = 0;
-  int64_t nchunk = 0, nleaf = 0;
+  int64_t nchunk = 0, nseg = 0, nleaf = 0;
   int dpmax = 0;
 };
 
@@ -310,6 +315,9 @@ struct Plan {
   int *counts_pin = nullptr;    // pinned host copy of counts_dev and errflag
   int *chunk_ptr = nullptr;     // per active leaf: first 32-target chunk (prefix sum)
   int *chunk_leaf = nullptr;    // per chunk: its active leaf
+  int *seg_ptr = nullptr, *seg_leaf = nullptr;  // the same for the P2M segments
+  double *w_ext = nullptr;      // P2M sums of the segments after a leaf's first
+  int64_t nseg = 0;             // P2M segments of the tree
   int64_t nchunk = 0;           // bound on the 32-target chunks over all leaves
   unsigned long long *npairs_dev = nullptr;  // near-field work counters (3)
   int64_t near_point_pairs = 0;  // target x source point pairs of the near field

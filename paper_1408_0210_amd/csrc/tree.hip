@@ -204,8 +204,8 @@ __global__ __launch_bounds__(256) void k_near_pairs(int level, const uint32_t *_
 // range of leaf_start).  Blocks of 256 boxes; block numbers run over the levels
 // one after another (blk0), and blkcnt holds kActCols counts per block: one per child
 // class, the total, and on the leaf level the 32-target chunks of its boxes (the work
-// items of the near-field and L2P kernels), whose prefix sum over the active leaves,
-// chunk_ptr, comes out of the same three launches.
+// items of the near-field and L2P kernels) and the P2M segments, whose prefix sums over
+// the active leaves, chunk_ptr and seg_ptr, come out of the same three launches.
 struct ActLevels {
   int n;                        // levels
   int shift[kMaxLevels];        // 3 (depth - k)
@@ -214,17 +214,26 @@ struct ActLevels {
   uint32_t *act[kMaxLevels];    // compact keys, ascending
   int *slot[kMaxLevels];        // dense map key -> compact index or -1
   int *cls[kMaxLevels];         // compact indices grouped by child class
-  int *counts[kMaxLevels];      // class offsets [0, 8) and the total [8]
+  int *counts[kMaxLevels];      // class offsets [0, 8), the total [8], leaf: segments [9]
   int leaf;                     // index of the leaf level (-1: not among the levels)
   const int *tb;                // targets of leaf key: [tb[key], ls[key + 1])
+  const int *se;                // sources of leaf key: [ls[key], se[key])
   int *chunk_ptr;               // first chunk of each active leaf, and their number
   int *chunk_leaf;              // active leaf of each chunk
+  int *seg_ptr, *seg_leaf;      // the same for the P2M segments
 };
 
 // 32-target chunks of leaf b
 __device__ inline int leaf_chunks(const int *__restrict__ ls, const int *__restrict__ tb,
                                   int64_t b) {
   return (ls[b + 1] - tb[b] + 31) >> 5;
+}
+
+// P2M segments of active leaf b (at least one, which clears the expansion of a leaf
+// without sources)
+__device__ inline int leaf_segments(const int *__restrict__ ls, const int *__restrict__ se,
+                                    int64_t b) {
+  return max(1, (se[b] - ls[b] + kSegSources - 1) / kSegSources);
 }
 
 __device__ inline int act_level(const ActLevels &L, int blk) {
@@ -244,7 +253,10 @@ __global__ __launch_bounds__(256) void k_act_count(const int *__restrict__ ls, A
   if (b < L.nb[q] && box_active(ls, L.shift[q], b)) {
     atomicAdd(&c[8], 1);
     atomicAdd(&c[b & 7], 1);
-    if (q == L.leaf) atomicAdd(&c[9], leaf_chunks(ls, L.tb, b));
+    if (q == L.leaf) {
+      atomicAdd(&c[9], leaf_chunks(ls, L.tb, b));
+      atomicAdd(&c[10], leaf_segments(ls, L.se, b));
+    }
   }
   __syncthreads();
   if (t < kActCols) blkcnt[(int64_t)blockIdx.x * kActCols + t] = c[t];
@@ -293,7 +305,11 @@ __global__ __launch_bounds__(1024) void k_act_scan(int *__restrict__ blkcnt, Act
       off += part[c][1023];
     }
     L.counts[q][8] = part[8][1023];
-    if (q == L.leaf) L.chunk_ptr[part[8][1023]] = part[9][1023];
+    if (q == L.leaf) {
+      L.chunk_ptr[part[8][1023]] = part[9][1023];
+      L.seg_ptr[part[8][1023]] = part[10][1023];
+      L.counts[q][9] = part[10][1023];
+    }
   }
 }
 
@@ -313,18 +329,26 @@ __global__ __launch_bounds__(256) void k_act_scatter(const int *__restrict__ ls,
     wtot[w][8] = (int)__popcll(ball);
     for (int k = 0; k < 8; ++k) wtot[w][k] = (int)__popcll(bc[k]);
   }
-  // chunks of the boxes before this one in its wave
+  // chunks and segments of the boxes before this one in its wave
   const bool leaf = q == L.leaf;
   const int ch = leaf && a ? leaf_chunks(ls, L.tb, b) : 0;
-  int rch = 0;
+  const int sg = leaf && a ? leaf_segments(ls, L.se, b) : 0;
+  int rch = 0, rsg = 0;
   if (leaf) {
-    int v = ch;
+    int v = ch, x = sg;
     for (int o = 1; o < 64; o <<= 1) {
-      const int u = __shfl_up(v, o);
-      if (lane >= o) v += u;
+      const int u = __shfl_up(v, o), y = __shfl_up(x, o);
+      if (lane >= o) {
+        v += u;
+        x += y;
+      }
     }
     rch = v - ch;
-    if (lane == 63) wtot[w][9] = v;
+    rsg = x - sg;
+    if (lane == 63) {
+      wtot[w][9] = v;
+      wtot[w][10] = x;
+    }
   }
   __syncthreads();
   if (b >= L.nb[q]) return;
@@ -336,7 +360,10 @@ __global__ __launch_bounds__(256) void k_act_scatter(const int *__restrict__ ls,
   for (int k = 0; k < w; ++k) {
     rt += wtot[k][8];
     rc += wtot[k][c];
-    if (leaf) rch += wtot[k][9];
+    if (leaf) {
+      rch += wtot[k][9];
+      rsg += wtot[k][10];
+    }
   }
   const int64_t bo = (int64_t)blockIdx.x * kActCols;
   const int pos = blkoff[bo + 8] + rt;
@@ -345,6 +372,9 @@ __global__ __launch_bounds__(256) void k_act_scatter(const int *__restrict__ ls,
     const int c0 = blkoff[bo + 9] + rch;
     L.chunk_ptr[pos] = c0;
     for (int e = 0; e < ch; ++e) L.chunk_leaf[c0 + e] = pos;
+    const int s0 = blkoff[bo + 10] + rsg;
+    L.seg_ptr[pos] = s0;
+    for (int e = 0; e < sg; ++e) L.seg_leaf[s0 + e] = pos;
   }
   L.slot[q][b] = pos;
   L.cls[q][L.counts[q][c] + blkoff[bo + c] + rc] = pos;
@@ -562,6 +592,9 @@ void build_active(Plan &P, int k0, int k1, hipStream_t s) {
   L.tb = P.nt ? P.tgt_begin : P.leaf_start;
   L.chunk_ptr = P.chunk_ptr;
   L.chunk_leaf = P.chunk_leaf;
+  L.se = P.nt ? P.tgt_begin : P.leaf_start + 1;
+  L.seg_ptr = P.seg_ptr;
+  L.seg_leaf = P.seg_leaf;
   int blk = 0;
   for (int k = k0; k <= k1; ++k) {
     const int q = L.n++;
@@ -684,6 +717,7 @@ int tree_build(Plan &P, const double *xyz_in, const double *tgt_in, hipStream_t 
     }
   }
   P.il_pending = P.il_lazy;
+  P.nseg = P.nact[depth] > 0 ? host_counts[16 * depth + 9] : 0;
   // the near-field and L2P launches use a bound on the chunks (workgroups past
   // chunk_ptr[nact] exit), so their number is not read back
   P.nchunk = P.nact[depth] > 0 ? P.nact[depth] + (n + 31) / 32 : 0;
