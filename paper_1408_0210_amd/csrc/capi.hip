@@ -174,7 +174,10 @@ int setup_tables(eifmm_plan h) {
     LevelHost &H = P.lh[k];
     LevelDev &D = P.ld[k];
     if (mixed) {
-      std::vector<float> f32(H.kfrag.begin(), H.kfrag.end());
+      // four k-steps of a lane side by side: [..][16-k sub-chunk][lane][k-step]
+      std::vector<float> f32(H.kfrag.size());
+      for (size_t q = 0; q < f32.size(); ++q)
+        f32[(q & ~(size_t)255) + (q & 63) * 4 + ((q >> 6) & 3)] = (float)H.kfrag[q];
       TRY(upload(&D.kfrag32, f32.data(), f32.size(), tr));
     } else if (P.shared_tables || H.sp2.empty()) {
       const int dm = H.r > 0 ? H.rp : H.dpB, dk = H.r > 0 ? H.rp : H.dp;

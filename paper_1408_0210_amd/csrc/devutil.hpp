@@ -37,7 +37,7 @@ __host__ __device__ inline uint32_t morton_encode(uint32_t x, uint32_t y, uint32
 // ext_vector_type (HIP's double2 class copies through a generic pointer).
 #define EIFMM_GLOBAL_AS __attribute__((address_space(1)))
 typedef double d2v __attribute__((ext_vector_type(2)));
-typedef float f2v __attribute__((ext_vector_type(2)));
+typedef double d4v __attribute__((ext_vector_type(4)));
 template <typename T>
 __device__ inline T ldg(const T *p) {
   return *(const EIFMM_GLOBAL_AS T *)p;

@@ -24,13 +24,10 @@
 // L2) 2.07, so what bounds it is the way through LDS (84 KB in and 280 KB out per chunk
 // and CU, 2850 cycles at 128 bytes, beside 3584 of products) and the fabric's latency.
 #include <algorithm>
-#include <climits>
 #include <cmath>
-#include <type_traits>
 #include <vector>
 
-#include "devutil.hpp"
-#include "plan.hpp"
+#include "m2l_tile.hpp"
 
 namespace eifmm {
 
@@ -41,9 +38,8 @@ constexpr int ND = kDigits;  // digits of an operand
 constexpr int kFrag = 1024;  // bytes of one 16 x 64 operand fragment (64 lanes x 16)
 
 // zeros, read in place of a missing source column (7 digits of 1024 elements) and,
-// as a double, of its scale; the slot of a missing source
+// as a double, of its scale
 __device__ i4v g_digit_zero[7 * 1024 / 16];
-__device__ int g_no_slot = -1;
 
 // the exponent e of the smallest power of two with m 2^-e <= 0.498, so that the top
 // digit of every |x| <= m stays within [-127, 127]; m > 0 and finite
@@ -202,52 +198,6 @@ __global__ __launch_bounds__(256) void k_digits_list(const DigitDesc *__restrict
   if (col < D.ncols) digit_column(D, col);
 }
 
-// Global memory straight into LDS, 16 bytes per lane (lane l's to lds + 16 l; lds is
-// wave-uniform; an instruction's offset moves both addresses).  The loads are
-// outstanding on the vector-memory counter: the caller waits for it before the
-// barrier that hands the data over.
-// fragment OFF / 1024 of consecutive ones in both memories; src is wave-uniform, lane l
-// reads src + OFF + 16 l
-template <int OFF>
-__device__ inline void fragment_to_lds(uint64_t src, uint32_t lds, uint32_t lane16) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
-               :
-               : "s"(lds), "v"(lane16), "s"(src), "i"(OFF)
-               : "memory", "m0");
-}
-// one fragment, each lane from its own address src + OFF (the offset is taken off the
-// LDS address again)
-template <int OFF>
-__device__ inline void column_to_lds(const int8_t *src, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2"
-               :
-               : "s"(lds - OFF), "v"(src), "i"(OFF)
-               : "memory", "m0");
-}
-__device__ inline uint64_t uniform64(uint64_t p) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
-  return ((uint64_t)hi << 32) | lo;
-}
-
-// f(integral_constant<int, I>) for I in [I0, I1)
-template <int I0, int I1, typename F>
-__device__ inline void for_each_from(F &f) {
-  if constexpr (I0 < I1) {
-    f(std::integral_constant<int, I0>{});
-    for_each_from<I0 + 1, I1>(f);
-  }
-}
-
-// a tile's target column
-struct Col8 {
-  const int *slot_map;  // slot map of the level
-  const int8_t *B;      // source digits
-  const double *bs;     // source scales
-  uint32_t tkey;        // target key
-  int r, valid;
-};
-
 // Terms [term0, term1) of one tile of 16 RB RG rows and 128 / RG columns: the result,
 // or a piece (part).  8 waves, RG groups of rows by 8 / RG groups of 16 columns; a wave
 // holds RB row blocks of its 16 columns.  The operator fragments of a 64-k chunk go
@@ -260,11 +210,9 @@ struct Col8 {
 template <int RB, int RG>
 __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, int term1,
                                  double *__restrict__ part, const int8_t *__restrict__ dvec,
-                                 int8_t (*As)[RB * RG * ND * kFrag], int8_t *Bs, Col8 *cst,
+                                 int8_t (*As)[RB * RG * ND * kFrag], int8_t *Bs, TileCol *cst,
                                  int *sdel) {
   constexpr int CG = 8 / RG, H = RB * RG, COLS = 16 * CG;
-  __shared__ int sbox[8][6];
-  __shared__ int snk;
   const int t = threadIdx.x, lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int rg = w / CG, cg = w % CG;
@@ -276,98 +224,10 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
   const int ncols = J.ntgt * J.nrhs;
   const int64_t colbytes = (int64_t)J.dpk * ND;
 
-  Col8 *my = cst + 16 * cg + (lane & 15);  // (the waves of a column group write the same)
-  int bb[6] = {INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN};
-  {
-    const int jc = col0 + 16 * cg + (lane & 15);
-    Col8 c{};
-    c.valid = jc < ncols;
-    c.slot_map = J.src_slot;
-    c.B = (const int8_t *)J.Bsrc;
-    c.bs = J.bscale;
-    if (c.valid) {
-      const int tt = jc / J.nrhs;
-      c.r = jc - tt * J.nrhs;
-      if (J.colref) {
-        const ColRef cr = J.colref[tt];
-        const ColSrc &cs = J.colsrc[cr.rec];
-        c.tkey = ldg(cs.keys + cr.slot);
-        c.slot_map = cs.slot;
-        c.B = (const int8_t *)cs.B;
-        c.bs = cs.bscale;
-      } else {
-        c.tkey = ldg(J.tgt_keys + ldg(J.tgt + tt));
-      }
-#pragma unroll
-      for (int a = 0; a < 3; ++a) bb[a] = bb[3 + a] = (int)morton_axis(c.tkey, a);
-    }
-    *my = c;
-  }
-  // the terms whose source box lies inside the domain for some column of the tile,
-  // in order, packed (dx+3) | (dy+3) << 3 | (dz+3) << 6 | id << 9: the tile's boxes
-  // span [lo, hi] per axis, and offset delta reaches inside when hi + delta >= 0 and
-  // lo + delta < side on every axis
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      bb[a] = min(bb[a], __shfl_xor(bb[a], o));
-      bb[3 + a] = max(bb[3 + a], __shfl_xor(bb[3 + a], o));
-    }
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int a = 0; a < 6; ++a) sbox[w][a] = bb[a];
-  }
-  lds_barrier();
-  if (w == 0) {
-    int lo[3], hi[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      lo[a] = INT_MAX;
-      hi[a] = INT_MIN;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        lo[a] = min(lo[a], sbox[q][a]);
-        hi[a] = max(hi[a], sbox[q][3 + a]);
-      }
-    }
-    const int side = 1 << J.level;
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    int nk = 0;
-    for (int b = term0; b < term1; b += 64) {
-      const int i = b + lane;
-      bool keep = false;
-      int pk = 0;
-      if (i < term1) {
-        const int id = ldg(J.terms + i);
-        const int d0 = dvec[3 * id], d1 = dvec[3 * id + 1], d2 = dvec[3 * id + 2];
-        pk = (d0 + 3) | ((d1 + 3) << 3) | ((d2 + 3) << 6) | (id << 9);
-        keep = hi[0] + d0 >= 0 && lo[0] + d0 < side && hi[1] + d1 >= 0 && lo[1] + d1 < side &&
-               hi[2] + d2 >= 0 && lo[2] + d2 < side;
-      }
-      const uint64_t m = __ballot(keep);
-      if (keep) sdel[nk + (int)__popcll(m & below)] = pk;
-      nk += (int)__popcll(m);
-    }
-    if (lane == 0) snk = nk;
-  }
-  lds_barrier();
-  const int nt = __builtin_amdgcn_readfirstlane(snk);
-
-  // where the slot of term q's source is read (-1: no box)
-  auto slot_addr = [&](int q) -> const int * {
-    const Col8 c = *my;
-    if (q >= nt || !c.valid || !c.slot_map) return &g_no_slot;
-    const int pk = sdel[q];
-    const int side = 1 << J.level;
-    const int m0 = (int)morton_axis(c.tkey, 0) + (pk & 7) - 3;
-    const int m1 = (int)morton_axis(c.tkey, 1) + ((pk >> 3) & 7) - 3;
-    const int m2 = (int)morton_axis(c.tkey, 2) + ((pk >> 6) & 7) - 3;
-    const bool in = m0 >= 0 && m1 >= 0 && m2 >= 0 && m0 < side && m1 < side && m2 < side;
-    return in ? c.slot_map + morton_encode((uint32_t)m0, (uint32_t)m1, (uint32_t)m2) : &g_no_slot;
-  };
-
+  TileCol *my = cst + 16 * cg + (lane & 15);  // (the waves of a column group write the same)
+  int bb[6];
+  *my = tile_column(J, col0 + 16 * cg + (lane & 15), bb);
+  const int nt = tile_terms(J, term0, term1, bb, dvec, sdel);
   double sum[RB][4];
   i4v acc[RB][ND];
 #pragma unroll
@@ -382,7 +242,7 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
     const int8_t *Abase = (const int8_t *)J.A + (int64_t)rb0 * nkc * ND * kFrag;
     const uint32_t ldsb =
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)Bs + cg * (ND * kFrag);
-    int slotn = ldg(slot_addr(0));  // slot of the next term to load
+    int slotn = ldg(source_slot(J, *my, 0, nt, sdel));  // slot of the next term to load
     const int8_t *srcp = nullptr, *At = nullptr;
     // scale of the source and whether the wave has any: of the term aimed at (n), of
     // the last one loaded (q)
@@ -393,14 +253,14 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
     // that load, behind the products, since its chain of reads is long
     auto aim = [&]() {
       if (fq >= nt || fk != 0) return;
-      const Col8 c = *my;
+      const TileCol c = *my;
       const int sl = slotn;
       const int64_t col = (int64_t)sl * J.nrhs + c.r;
-      srcp = (sl < 0 ? (const int8_t *)g_digit_zero : c.B + col * colbytes) + 16 * (lane >> 4);
+      srcp = (sl < 0 ? (const int8_t *)g_digit_zero : (const int8_t *)c.B + col * colbytes) + 16 * (lane >> 4);
       scn = ldg(sl < 0 ? (const double *)g_digit_zero : c.bs + col);
       haven = __ballot(sl >= 0) != 0;
       At = Abase + (int64_t)(__builtin_amdgcn_readfirstlane(sdel[fq]) >> 9) * J.a_stride;
-      slotn = ldg(slot_addr(fq + 1));
+      slotn = ldg(source_slot(J, c, fq + 1, nt, sdel));
     };
     // The loads of the next chunk, operators to LDS buffer `buf` and sources to Bs, are
     // issued one at a time between the products: a burst of them would hold up the
@@ -550,17 +410,7 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
   if (part) {
     out = part + (size_t)jt * (16 * H);
   } else {
-    const int tt = jo / J.nrhs, ro = jo - tt * J.nrhs;
-    int tso;
-    double *Cout = J.C;
-    if (J.colref) {
-      const ColRef cr = J.colref[tt];
-      tso = cr.slot;
-      Cout = J.colsrc[cr.rec].C;
-    } else {
-      tso = ldg(J.tgt + tt);
-    }
-    out = Cout + ((int64_t)tso * J.nrhs + ro) * J.dpm + 16 * rb0;
+    out = tile_output(J, jo) + 16 * rb0;
   }
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
@@ -577,14 +427,10 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
   }
 }
 
-__device__ inline int job_of_tile(const GemmJob *__restrict__ jobs, int njobs, int tile) {
-  return find_last_le(njobs, tile, [&](int m) { return (int64_t)jobs[m].tiles_start; });
-}
-
 // Tiles [0, full) run whole, G workgroups at a time in the order of the terms (so that
 // the operators they read are shared in L2; the tiles of one XCD (g mod 8) are
 // contiguous); the others are cut into `parts` term ranges each, taken in order from
-// a counter and summed by k_m2l8_sum, so that workgroups whose tiles dropped terms
+// a counter and summed by k_m2l_sum, so that workgroups whose tiles dropped terms
 // take more of them.  A workgroup that reads a value outside [0, items) stops.
 template <int RB, int RG>
 __global__ __launch_bounds__(512, 2) void k_m2l8(const GemmJob *__restrict__ jobs, int njobs,
@@ -595,7 +441,7 @@ __global__ __launch_bounds__(512, 2) void k_m2l8(const GemmJob *__restrict__ job
   constexpr int H = RB * RG, TILE = H * 16 * (128 / RG);
   __shared__ __align__(16) int8_t As[2][H * ND * kFrag];
   __shared__ __align__(16) int8_t Bs[(8 / RG) * ND * kFrag];
-  __shared__ Col8 cst[128 / RG];
+  __shared__ TileCol cst[128 / RG];
   __shared__ int sdel[189];
   __shared__ int item_sh;
   const int g = blockIdx.x;
@@ -618,75 +464,18 @@ __global__ __launch_bounds__(512, 2) void k_m2l8(const GemmJob *__restrict__ job
   }
 }
 
-// adds the pieces of the split tiles in part order (kSumSplit blocks per tile) and
-// sets the counter back for the next launch
-constexpr int kSumSplit = 4;
-__global__ __launch_bounds__(256) void k_m2l8_sum(const GemmJob *__restrict__ jobs, int njobs,
-                                                  int ntiles, int full, int parts, int height,
-                                                  const double *__restrict__ ws,
-                                                  int *__restrict__ ctr) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) stg(ctr, 0);
-  const int tile = full + (int)(blockIdx.x / kSumSplit);
-  if (tile >= ntiles) return;
-  const GemmJob J = jobs[job_of_tile(jobs, njobs, tile)];
-  const int cols = m2l8_cols(height), rows = 16 * height, size = rows * cols;
-  const int tile_local = tile - J.tiles_start;
-  const int row0 = (tile_local % J.nrowtiles) * rows, col0 = (tile_local / J.nrowtiles) * cols;
-  const int nrows = min(rows, J.dpm - row0), ncols = J.ntgt * J.nrhs;
-  const double *p = ws + (size_t)(tile - full) * parts * size;
-  for (int e = (int)(blockIdx.x % kSumSplit) * 256 + (int)threadIdx.x; e < size;
-       e += 256 * kSumSplit) {
-    const int jt = e / rows, rt = e - jt * rows, jo = col0 + jt;
-    if (rt >= nrows || jo >= ncols) continue;
-    double v = 0.0;
-    int i = 0;
-    for (; i + 8 <= parts; i += 8) {
-      double u[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) u[q] = ldg(p + (size_t)(i + q) * size + e);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v += u[q];
-    }
-    for (; i < parts; ++i) v += ldg(p + (size_t)i * size + e);
-    const int tt = jo / J.nrhs, ro = jo - tt * J.nrhs;
-    int tso;
-    double *Cout = J.C;
-    if (J.colref) {
-      const ColRef cr = J.colref[tt];
-      tso = cr.slot;
-      Cout = J.colsrc[cr.rec].C;
-    } else {
-      tso = ldg(J.tgt + tt);
-    }
-    stg(Cout + ((int64_t)tso * J.nrhs + ro) * J.dpm + row0 + rt, v);
-  }
-}
-
 template <int RB, int RG>
 void launch(const GemmJob *jobs, int n, int tiles, int cus, double *ws, size_t ws_len,
             const int8_t *dvec, hipStream_t s) {
   constexpr int H = RB * RG;
-  const size_t TILE = (size_t)H * 16 * (128 / RG);
-  int *ctr = (int *)(ws + ws_len - kCounterDoubles);
-  const size_t pieces = (ws_len - kCounterDoubles) / TILE;
   // one workgroup per CU (its operator buffers take most of the LDS)
-  const int G = cus;
-  int full = (tiles / G) * G, rest = tiles - full, parts = 0;
-  if (rest > 0) {
-    // about 4 items per workgroup, at least 4 terms each
-    parts = std::min(47, std::max(4, 4 * G / rest));
-    parts = (int)std::min<size_t>((size_t)parts, pieces / (size_t)rest);
-    if (parts < 2) {  // the pieces do not fit: every tile whole
-      full = tiles;
-      rest = 0;
-    }
-  }
-  const int grid = full > 0 ? G : std::min(G, rest * parts);
-  hipLaunchKernelGGL((k_m2l8<RB, RG>), dim3(grid), dim3(512), 0, s, jobs, n, grid, full,
-                     rest * parts, parts, ws, dvec, ctr);
-  if (rest > 0)
-    hipLaunchKernelGGL(k_m2l8_sum, dim3(rest * kSumSplit), dim3(256), 0, s, jobs, n, tiles, full,
-                       parts, H, ws, ctr);
+  const TileSplit T = split_tiles(tiles, cus, (size_t)H * 16 * (128 / RG), ws_len);
+  int *ctr = (int *)(ws + ws_len - kCounterDoubles);
+  hipLaunchKernelGGL((k_m2l8<RB, RG>), dim3(T.grid), dim3(512), 0, s, jobs, n, T.grid, T.full,
+                     T.rest * T.parts, T.parts, ws, dvec, ctr);
+  if (T.rest > 0)
+    hipLaunchKernelGGL(k_m2l_sum, dim3(T.rest * kSumSplit), dim3(256), 0, s, jobs, n, tiles, T.full,
+                       T.parts, H, m2l8_cols(H), ws, ctr);
 }
 
 }  // namespace

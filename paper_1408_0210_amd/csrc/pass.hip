@@ -7,8 +7,8 @@
 //   1  P2M                      k_p2m               one workgroup per leaf
 //   2  M2M (Sec. 4.1 operators) k_gemm<MODE_M2M>    MFMA, 8 children per parent
 //   3  What = Delta W           k_trsm              blocked triangular solves (MFMA)
-//   4  M2L (Sec. 4.2 matrices)  mixed: k_gemm<MODE_M2L> (FP32 MFMA), 189 offsets per class;
-//                               FP64: k_m2l8 (m2l.hip, int8 MFMA)
+//   4  M2L (Sec. 4.2 matrices)  189 offsets per class; FP64: k_m2l8 (m2l.hip, int8 MFMA),
+//                               mixed: k_m2l32 (m2l32.hip, FP32 MFMA)
 //   5  L2L                      k_gemm<MODE_L2L>    MFMA, adds g
 //   6  lhat = Delta^T l         k_trsm
 //   7  L2P and f = f_far + f_near, input order  k_l2p  one wave per 64 targets
@@ -985,15 +985,12 @@ __global__ __launch_bounds__(64) void k_trsm_list(const SolveDesc *__restrict__ 
 // ------------------------------------------------------------------ gathered GEMM
 // C[:, col] (+)= sum_t A_t B_t[:, col] for the columns (box, RHS) of a target
 // group, where B_t[:, col] is the expansion of the source box that term t pairs
-// with the column's target box: M2L the box at offset delta; M2M child t; L2L the
-// parent; PROJ the box itself (compression projections).  A workgroup computes a
-// (16 RBT)-row tile, 128 columns wide for 3 and 4 row blocks and 64 for 5 and 6,
-// with 16x16x4 MFMAs; each of the 4 waves owns a quarter of the columns and all
-// RBT row blocks.  The operator chunks of 16 k values pass through LDS in MFMA
-// fragment order, loaded two chunks ahead of their products.  With FOLD (FP32
-// operands) each term's product is accumulated by the MFMA in FP32 and then
-// added to an FP64 sum over the terms, so FP32 rounding grows with one matrix
-// product (d_k terms) rather than with the whole interaction list.
+// with the column's target box: M2M child t; L2L the parent; PROJ the box itself
+// (compression projections).  (The M2L has kernels of its own.)  A workgroup
+// computes a (16 RBT)-row tile, 128 columns wide for 3 and 4 row blocks and 64 for
+// 5 and 6, with 16x16x4 MFMAs; each of the 4 waves owns a quarter of the columns
+// and all RBT row blocks.  The operator chunks of 16 k values pass through LDS in
+// MFMA fragment order, loaded two chunks ahead of their products.
 constexpr int MODE_M2M = 0, MODE_M2L = 1, MODE_L2L = 2, MODE_PROJ = 3;
 // 16-column blocks per wave: 2 (128-column tiles) for 3- and 4-block tiles, 1
 // (64 columns) for taller ones, whose accumulators and three sets of prefetched
@@ -1001,14 +998,6 @@ constexpr int MODE_M2M = 0, MODE_M2L = 1, MODE_L2L = 2, MODE_PROJ = 3;
 __host__ __device__ constexpr int gemm_cpw(int rbt) { return rbt >= 5 ? 1 : 2; }
 static_assert(gemm_cpw(6) == 1 && gemm_cpw(4) == 2 && gemm_cpw(3) == 2, "tile widths");
 __host__ __device__ constexpr int gemm_cols(int rbt) { return 64 * gemm_cpw(rbt); }
-constexpr int kMaxTerms = 189;   // terms of one job (M2L: the offsets of a child class)
-// M2L: the tiles left after the whole-tile rounds are split in `parts` term
-// ranges each (as many as the workspace holds pieces for, up to kMaxTailParts),
-// taken by the workgroups from a counter as they finish, so that workgroups
-// whose tiles skipped products take more of them.  The counter sits in the last
-// kCounterDoubles of the Stream-K workspace; it is zero when a workspace is
-// made, and the fixup that follows each such launch zeroes it.
-constexpr int kMaxTailParts = 16;
 // zeros, read in place of a missing source column or of operator rows past the
 // operator, so that every chunk issues the same loads (static device memory is
 // zero-initialized; 1024 covers the longest column, d_k <= 1024)
@@ -1017,76 +1006,34 @@ __device__ double g_gemm_zero[1024];
 // the dummy loads stay distinct loads)
 __device__ int g_slot_none[2] = {-1, -1};
 
-// Operand layouts (both types): lane l holds A[l % 16][l / 16] and B[l / 16][l % 16].
-// Result layouts differ: FP64 keeps rows (l / 16) + 4 q of column l % 16 in
-// register q, FP32 rows 4 (l / 16) + q.
-template <typename T>
-struct Mfma;
-template <>
-struct Mfma<double> {
-  typedef double v4 __attribute__((ext_vector_type(4)));
-  typedef d2v p2;
-  __device__ static inline v4 op(double a, double b, v4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  __device__ static inline int row(int lane, int q) { return (lane >> 4) + 4 * q; }
-};
-template <>
-struct Mfma<float> {
-  typedef float v4 __attribute__((ext_vector_type(4)));
-  typedef f2v p2;
-  __device__ static inline v4 op(float a, float b, v4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  __device__ static inline int row(int lane, int q) { return 4 * (lane >> 4) + q; }
-};
+// Operand layouts: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16], and rows
+// (l / 16) + 4 q of column l % 16 of the result in register q.
+__device__ inline d4v mfma_f64(double a, double b, d4v c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
 
 // Where the slot of the source box that term `term` pairs with target (tkey, ts)
-// is read: M2L the box at offset delta, M2M child `term`, L2L the parent (entries
-// of the source level's slot map, which holds -1 for an empty box); PROJ needs
-// no read (the box itself).  For a missing column or a source outside the
-// domain the address is g_slot_none[jj] (-1, no box), so that every lane reads,
+// is read: M2M child `term`, L2L the parent (entries of the source level's slot
+// map, which holds -1 for an empty box); PROJ needs no read (the box itself).  For
+// a missing column the address is g_slot_none[jj] (-1, no box), so that every lane reads,
 // the number of loads in flight does not depend on the data, and the value read
 // needs no select (a select right after the load would wait for it).
 template <int MODE>
-__device__ inline const int *gemm_source_addr(const GemmJob &J, int term, bool cvalid,
-                                              uint32_t tkey, const int *sdel,
+__device__ inline const int *gemm_source_addr(int term, bool cvalid, uint32_t tkey,
                                               const int *__restrict__ src_slot, int jj) {
-  uint32_t skey;
-  bool v = cvalid;
-  if constexpr (MODE == MODE_M2L) {
-    const int pk = sdel[term];  // the term's offset, packed (LDS)
-    const int side = 1 << J.level;
-    const int m0 = (int)morton_axis(tkey, 0) + (pk & 7) - 3;
-    const int m1 = (int)morton_axis(tkey, 1) + ((pk >> 3) & 7) - 3;
-    const int m2 = (int)morton_axis(tkey, 2) + ((pk >> 6) & 7) - 3;
-    v = v && m0 >= 0 && m1 >= 0 && m2 >= 0 && m0 < side && m1 < side && m2 < side;
-    skey = morton_encode((uint32_t)m0, (uint32_t)m1, (uint32_t)m2);
-  } else if constexpr (MODE == MODE_M2M) {
-    skey = tkey * 8u + (uint32_t)term;
-  } else {
-    skey = tkey >> 3;
-  }
-  return (v && src_slot) ? src_slot + skey : &g_slot_none[jj];
+  const uint32_t skey = MODE == MODE_M2M ? tkey * 8u + (uint32_t)term : tkey >> 3;
+  return (cvalid && src_slot) ? src_slot + skey : &g_slot_none[jj];
 }
 
-template <typename T>
-__device__ inline const T *gemm_source_ptr(const GemmJob &J, int s, int r, const T *Bsrc) {
+__device__ inline const double *gemm_source_ptr(const GemmJob &J, int s, int r,
+                                                const double *Bsrc) {
   return s < 0 ? nullptr : Bsrc + ((int64_t)s * J.nrhs + r) * J.dpk;
 }
 
-template <typename T, int MODE>
-__device__ inline const T *gemm_operand(const GemmJob &J, int term, const int *sdel) {
-  int64_t idx;
-  if constexpr (MODE == MODE_M2L)
-    idx = sdel[term] >> 9;  // the offset id, from the LDS term table
-  else if constexpr (MODE == MODE_M2M)
-    idx = term;
-  else if constexpr (MODE == MODE_L2L)
-    idx = J.cls;
-  else
-    idx = 0;
-  return (const T *)J.A + idx * J.a_stride;
+template <int MODE>
+__device__ inline const double *gemm_operand(const GemmJob &J, int term) {
+  const int64_t idx = MODE == MODE_M2M ? term : MODE == MODE_L2L ? J.cls : 0;
+  return (const double *)J.A + idx * J.a_stride;
 }
 
 // Schedule (data-parallel + Stream-K): the units of a launch are (tile, term)
@@ -1141,13 +1088,10 @@ struct ColState {
 // straight from memory to registers: within each 16-k chunk lane l supplies
 // k = 4 (l / 16) + ks at k-step ks, four consecutive elements of its column, and
 // the operator tables use the same k order (setup.cpp).
-template <typename T, int MODE, bool FOLD, int RBT>
+template <int MODE, int RBT>
 __device__ inline void gemm_tile(const GemmJob &J, int tile_local, int term0, int term1,
-                                 double *__restrict__ part, const int8_t *__restrict__ dvec,
-                                 T (*As)[RBT * 4 * 64], ColState *cst, int *sdel) {
-  typedef typename Mfma<T>::v4 V4;
-  typedef typename Mfma<T>::p2 P2;
-  typedef double D4 __attribute__((ext_vector_type(4)));
+                                 double *__restrict__ part, double (*As)[RBT * 4 * 64],
+                                 ColState *cst) {
   constexpr int CPW = gemm_cpw(RBT), COLS = 64 * CPW;
   constexpr int NA = RBT * 128;         // A chunk, in pairs
   constexpr int QA = (NA + 255) / 256;  // pairs per thread
@@ -1172,98 +1116,18 @@ __device__ inline void gemm_tile(const GemmJob &J, int tile_local, int term0, in
     if (c.valid) {
       const int tt = jc / J.nrhs;
       c.r = jc - tt * J.nrhs;
-      if (MODE == MODE_M2L && J.colref) {
-        const ColRef cr = J.colref[tt];
-        const ColSrc &cs = J.colsrc[cr.rec];
-        c.tsl = cr.slot;
-        c.tkey = ldg(cs.keys + cr.slot);
-        c.slot_map = cs.slot;
-        c.B = cs.B;
-      } else {
-        c.tsl = J.tgt ? ldg(J.tgt + tt) : tt;
-        if (MODE != MODE_PROJ) c.tkey = ldg(J.tgt_keys + c.tsl);
-      }
+      c.tsl = J.tgt ? ldg(J.tgt + tt) : tt;
+      if (MODE != MODE_PROJ) c.tkey = ldg(J.tgt_keys + c.tsl);
     }
     my[jj] = c;
   }
-  // the job's terms in LDS, packed (dx+3) | (dy+3) << 3 | (dz+3) << 6 | id << 9
-  // (offset and offset id): a source lookup then waits on no global load but
-  // the slot map's, and the operator address on none.  Only the terms of
-  // [term0, term1) whose source box lies inside the domain for some column of
-  // the tile are kept, in order (the others would add zeros): the tile's target
-  // boxes span [lo, hi] per axis, and offset delta reaches inside for some of
-  // them on an axis when hi + delta >= 0 and lo + delta < side.  Boxes of one
-  // child class and one face signature (the M2L column order) share their
-  // missing offsets, so a tile of them drops those terms whole: their loads,
-  // LDS staging and barriers as well as their products.
-  if constexpr (MODE == MODE_M2L) {
-    __shared__ int sbox[4][6];
-    __shared__ int snk;
-    int bb[6] = {INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN};
-#pragma unroll
-    for (int jj = 0; jj < CPW; ++jj) {
-      const ColState c = my[jj];
-      if (c.valid) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          const int m = (int)morton_axis(c.tkey, a);
-          bb[a] = min(bb[a], m);
-          bb[3 + a] = max(bb[3 + a], m);
-        }
-      }
-    }
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        bb[a] = min(bb[a], __shfl_xor(bb[a], o));
-        bb[3 + a] = max(bb[3 + a], __shfl_xor(bb[3 + a], o));
-      }
-    }
-    if (lane < 6) sbox[w][lane] = bb[lane];
-    lds_barrier();
-    if (w == 0) {
-      int lo[3], hi[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        lo[a] = min(min(sbox[0][a], sbox[1][a]), min(sbox[2][a], sbox[3][a]));
-        hi[a] = max(max(sbox[0][3 + a], sbox[1][3 + a]), max(sbox[2][3 + a], sbox[3][3 + a]));
-      }
-      const int side = 1 << J.level;
-      const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-      int nk = 0;
-      for (int b = term0; b < term1; b += 64) {
-        const int i = b + lane;
-        bool keep = false;
-        int pk = 0;
-        if (i < term1) {
-          const int id = ldg(J.terms + i);
-          const int d0 = dvec[3 * id], d1 = dvec[3 * id + 1], d2 = dvec[3 * id + 2];
-          pk = (d0 + 3) | ((d1 + 3) << 3) | ((d2 + 3) << 6) | (id << 9);
-          keep = hi[0] + d0 >= 0 && lo[0] + d0 < side && hi[1] + d1 >= 0 && lo[1] + d1 < side &&
-                 hi[2] + d2 >= 0 && lo[2] + d2 < side;
-        }
-        const uint64_t m = __ballot(keep);
-        if (keep) sdel[nk + (int)__popcll(m & below)] = pk;
-        nk += (int)__popcll(m);
-      }
-      if (lane == 0) snk = nk;
-    }
-    lds_barrier();
-    term0 = 0;
-    term1 = snk;
-  }
-  V4 acc[RBT][CPW];
-  D4 sum[RBT][CPW];
+  d4v acc[RBT][CPW];
   bool rowok[RBT];
 #pragma unroll
   for (int i = 0; i < RBT; ++i) {
     rowok[i] = rb0 + i < nrb;
 #pragma unroll
-    for (int jj = 0; jj < CPW; ++jj) {
-      acc[i][jj] = V4{0, 0, 0, 0};
-      if constexpr (FOLD) sum[i][jj] = D4{0, 0, 0, 0};
-    }
+    for (int jj = 0; jj < CPW; ++jj) acc[i][jj] = d4v{0, 0, 0, 0};
   }
   // Chunks are loaded two ahead of their products: during the products of
   // chunk it, the loads of chunk it + 2 are in flight and chunk it + 1 goes from
@@ -1272,10 +1136,10 @@ __device__ inline void gemm_tile(const GemmJob &J, int tile_local, int term0, in
   // (R, B) rotate by name over a loop unrolled by 3 (a copy from a register a
   // load is filling would wait for that load), and every chunk issues the same
   // loads, so that the waits for them are exact.
-  P2 R0[QA], R1[QA], R2[QA];               // A of a chunk, on its way to LDS
-  P2 B0[CPW][2], B1[CPW][2], B2[CPW][2];   // B of a chunk: [column][pair]
-  const T *srcp[CPW];
-  const T *Ap = nullptr;
+  d2v R0[QA], R1[QA], R2[QA];               // A of a chunk, on its way to LDS
+  d2v B0[CPW][2], B1[CPW][2], B2[CPW][2];   // B of a chunk: [column][pair]
+  const double *srcp[CPW];
+  const double *Ap = nullptr;
   // source slots of the next term (-1: none): read by the fetch of a term's
   // last chunk (the other fetches read g_slot_none), used at the next term's
   // first chunk
@@ -1293,7 +1157,7 @@ __device__ inline void gemm_tile(const GemmJob &J, int tile_local, int term0, in
         nslot[jj] = c.valid ? c.tsl : -1;
       } else {
         const int *addr = &g_slot_none[jj];
-        if (real) addr = gemm_source_addr<MODE>(J, term, c.valid, c.tkey, sdel, c.slot_map, jj);
+        if (real) addr = gemm_source_addr<MODE>(term, c.valid, c.tkey, c.slot_map, jj);
         nslot[jj] = ldg(addr);
       }
     }
@@ -1301,11 +1165,8 @@ __device__ inline void gemm_tile(const GemmJob &J, int tile_local, int term0, in
   // loads chunk (fterm, fkc), the next one in order, into raD and bD; with live
   // false (past the last chunk) the same loads read zeros
   int fterm = term0, fkc = 0;
-  const T *zero = (const T *)g_gemm_zero;
-  // M2L: 1 when none of this wave's columns has a source in the current fetch
-  // term; the wave's products would add zeros and are skipped
-  uint32_t curskip = 0;
-  auto fetch = [&](P2(&raD)[QA], P2(&bD)[CPW][2], uint32_t &skD, bool live) {
+  const double *zero = g_gemm_zero;
+  auto fetch = [&](d2v(&raD)[QA], d2v(&bD)[CPW][2], bool live) {
     const int term = fterm, kc = fkc;
     if (live) {
       if (++fkc == nkc) {
@@ -1316,18 +1177,11 @@ __device__ inline void gemm_tile(const GemmJob &J, int tile_local, int term0, in
 #pragma unroll
         for (int jj = 0; jj < CPW; ++jj) {
           const ColState c = my[jj];
-          srcp[jj] = gemm_source_ptr<T>(J, nslot[jj], c.r, (const T *)c.B);
+          srcp[jj] = gemm_source_ptr(J, nslot[jj], c.r, (const double *)c.B);
         }
-        Ap = gemm_operand<T, MODE>(J, term, sdel);
-        if constexpr (MODE == MODE_M2L) {
-          bool any = false;
-#pragma unroll
-          for (int jj = 0; jj < CPW; ++jj) any = any || srcp[jj] != nullptr;
-          curskip = __ballot(any) == 0 ? 1u : 0u;
-        }
+        Ap = gemm_operand<MODE>(J, term);
       }
     }
-    skD = curskip;
     // the slots of the next term, at the term's last chunk
     lookup(term + 1, live && kc == nkc - 1 && term + 1 < term1);
 #pragma unroll
@@ -1335,65 +1189,49 @@ __device__ inline void gemm_tile(const GemmJob &J, int tile_local, int term0, in
       const int e = t + 256 * q;  // pair index in the chunk
       const int rb = rb0 + (e >> 7);
       if (e < NA) {
-        const T *src = (live && rb < nrb) ? Ap + ((int64_t)rb * nks + kc * 4) * 64 : zero;
-        raD[q] = ldg((const P2 *)(src + 2 * (e & 127)));
+        const double *src = (live && rb < nrb) ? Ap + ((int64_t)rb * nks + kc * 4) * 64 : zero;
+        raD[q] = ldg((const d2v *)(src + 2 * (e & 127)));
       }
     }
 #pragma unroll
     for (int jj = 0; jj < CPW; ++jj) {
-      const T *col = (live && srcp[jj]) ? srcp[jj] + kc * 16 : zero;
-      const P2 *s2 = (const P2 *)(col + koff);
+      const double *col = (live && srcp[jj]) ? srcp[jj] + kc * 16 : zero;
+      const d2v *s2 = (const d2v *)(col + koff);
       bD[jj][0] = ldg(s2);
       bD[jj][1] = ldg(s2 + 1);
     }
   };
-  auto stash = [&](int buf, const P2(&raS)[QA]) {
+  auto stash = [&](int buf, const d2v(&raS)[QA]) {
 #pragma unroll
     for (int q = 0; q < QA; ++q) {
       const int e = t + 256 * q;
-      if (e < NA) *(P2 *)(&As[buf][2 * e]) = raS[q];
+      if (e < NA) *(d2v *)(&As[buf][2 * e]) = raS[q];
     }
   };
   const int it0 = term0 * nkc, it1 = term1 * nkc;
-  int mkc = 0;  // k chunk of the current term
   // the products of chunk it (its A in LDS buffer (it - it0) & 1, its B in Bc),
   // with the loads of chunk it + 2 into (Rf, Bf) and chunk it + 1 (Rn) stashed
   // The products of a chunk's last k-step are deferred to the start of the next
   // step, after the barrier, so that their MFMAs run while the wave issues the
-  // next chunk's loads (a branch around the products, for the skipped terms,
-  // would otherwise keep the compiler from moving them there); their operands
-  // wait in registers.  With FOLD a term's sum is folded after them.
-  T a3[RBT], b3[CPW];
-  bool dpend = false, fpend = false;  // deferred products and fold pending (wave-uniform)
+  // next chunk's loads; their operands wait in registers.
+  double a3[RBT], b3[CPW];
+  bool dpend = false;  // deferred products pending (wave-uniform)
   auto deferred = [&]() {
     if (dpend) {
 #pragma unroll
       for (int i = 0; i < RBT; ++i)
         if (RBT != 6 || rowok[i]) {
 #pragma unroll
-          for (int jj = 0; jj < CPW; ++jj) acc[i][jj] = Mfma<T>::op(a3[i], b3[jj], acc[i][jj]);
+          for (int jj = 0; jj < CPW; ++jj) acc[i][jj] = mfma_f64(a3[i], b3[jj], acc[i][jj]);
         }
     }
-    if constexpr (FOLD) {
-      if (fpend) {  // a term is complete
-#pragma unroll
-        for (int i = 0; i < RBT; ++i)
-#pragma unroll
-          for (int jj = 0; jj < CPW; ++jj) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) sum[i][jj][q] += (double)acc[i][jj][q];
-            acc[i][jj] = V4{0, 0, 0, 0};
-          }
-      }
-    }
     dpend = false;
-    fpend = false;
   };
   // k-steps 0..2 of one chunk, and the operands of k-step 3
-  auto products = [&](int cur, const P2(&Bc)[CPW][2]) {
+  auto products = [&](int cur, const d2v(&Bc)[CPW][2]) {
 #pragma unroll
     for (int ks = 0; ks < 3; ++ks) {
-      T a[RBT], b[CPW];
+      double a[RBT], b[CPW];
 #pragma unroll
       for (int i = 0; i < RBT; ++i) a[i] = As[cur][(i * 4 + ks) * 64 + lane];
 #pragma unroll
@@ -1406,7 +1244,7 @@ __device__ inline void gemm_tile(const GemmJob &J, int tile_local, int term0, in
       for (int i = 0; i < RBT; ++i)
         if (RBT != 6 || rowok[i]) {
 #pragma unroll
-          for (int jj = 0; jj < CPW; ++jj) acc[i][jj] = Mfma<T>::op(a[i], b[jj], acc[i][jj]);
+          for (int jj = 0; jj < CPW; ++jj) acc[i][jj] = mfma_f64(a[i], b[jj], acc[i][jj]);
         }
     }
 #pragma unroll
@@ -1414,37 +1252,31 @@ __device__ inline void gemm_tile(const GemmJob &J, int tile_local, int term0, in
 #pragma unroll
     for (int jj = 0; jj < CPW; ++jj) b3[jj] = Bc[jj][1].y;
   };
-  auto step = [&](int it, const P2(&Bc)[CPW][2], uint32_t skc, const P2(&Rn)[QA], P2(&Rf)[QA],
-                  P2(&Bf)[CPW][2], uint32_t &skf) {
+  auto step = [&](int it, const d2v(&Bc)[CPW][2], const d2v(&Rn)[QA], d2v(&Rf)[QA],
+                  d2v(&Bf)[CPW][2]) {
     const int cur = (it - it0) & 1;
     deferred();  // the previous chunk's last k-step
-    fetch(Rf, Bf, skf, it + 2 < it1);
+    fetch(Rf, Bf, it + 2 < it1);
     stash(cur ^ 1, Rn);
-    const bool run = MODE != MODE_M2L || skc == 0;
-    if (run) products(cur, Bc);
-    dpend = run;
-    if (++mkc == nkc) {
-      mkc = 0;
-      fpend = FOLD;
-    }
+    products(cur, Bc);
+    dpend = true;
     lds_barrier();
   };
 
   if (it0 < it1) {
     lookup(term0, true);
-    uint32_t S0 = 0, S1 = 0, S2 = 0;  // skip flags of the chunks in B0, B1, B2
-    fetch(R0, B0, S0, true);
+    fetch(R0, B0, true);
     stash(0, R0);
-    fetch(R1, B1, S1, it0 + 1 < it1);
+    fetch(R1, B1, it0 + 1 < it1);
     lds_barrier();
     int it = it0;
     for (; it + 3 <= it1; it += 3) {
-      step(it, B0, S0, R1, R2, B2, S2);
-      step(it + 1, B1, S1, R2, R0, B0, S0);
-      step(it + 2, B2, S2, R0, R1, B1, S1);
+      step(it, B0, R1, R2, B2);
+      step(it + 1, B1, R2, R0, B0);
+      step(it + 2, B2, R0, R1, B1);
     }
-    if (it < it1) step(it, B0, S0, R1, R2, B2, S2);
-    if (it + 1 < it1) step(it + 1, B1, S1, R2, R0, B0, S0);
+    if (it < it1) step(it, B0, R1, R2, B2);
+    if (it + 1 < it1) step(it + 1, B1, R2, R0, B0);
     deferred();
   }
 
@@ -1454,33 +1286,21 @@ __device__ inline void gemm_tile(const GemmJob &J, int tile_local, int term0, in
     const int jo = col0 + jt;
     if (jo >= ncols) continue;
     const int tt = jo / J.nrhs, ro = jo - tt * J.nrhs;
-    int tso;
-    double *Cout = J.C;
-    if (MODE == MODE_M2L && J.colref) {
-      const ColRef cr = J.colref[tt];
-      tso = cr.slot;
-      Cout = J.colsrc[cr.rec].C;
-    } else {
-      tso = J.tgt ? ldg(J.tgt + tt) : tt;
-    }
+    const int tso = J.tgt ? ldg(J.tgt + tt) : tt;
     const int64_t cbase = ((int64_t)tso * J.nrhs + ro) * J.dpm;
 #pragma unroll
     for (int i = 0; i < RBT; ++i) {
       if (!rowok[i]) continue;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int rt = 16 * i + Mfma<T>::row(lane, q);
-        double v;
-        if constexpr (FOLD)
-          v = sum[i][jj][q];
-        else
-          v = (double)acc[i][jj][q];
+        const int rt = 16 * i + (lane >> 4) + 4 * q;
+        double v = acc[i][jj][q];
         if (part) {
           stg(part + (size_t)rt * COLS + jt, v);
         } else {
           const int64_t o = cbase + 16 * rb0 + rt;
           if constexpr (MODE == MODE_L2L) v += ldg(J.Cadd + o);
-          stg(Cout + o, v);
+          stg(J.C + o, v);
           if (J.C32) stg(J.C32 + o, (float)v);
         }
       }
@@ -1488,16 +1308,13 @@ __device__ inline void gemm_tile(const GemmJob &J, int tile_local, int term0, in
   }
 }
 
-template <typename T, int MODE, bool FOLD, int RBT>
+template <int MODE, int RBT>
 __global__ __launch_bounds__(256, 2) void k_gemm(const GemmJob *__restrict__ jobs, int njobs,
                                                  int ntiles, int64_t units, int G, int GT,
-                                                 double *__restrict__ ws,
-                                                 const int8_t *__restrict__ dvec, int dyn_items,
-                                                 int parts, int *__restrict__ ctr) {
+                                                 double *__restrict__ ws) {
   constexpr int TILE = RBT * 16 * 64 * gemm_cpw(RBT);
-  __shared__ T As[2][RBT * 4 * 64];
+  __shared__ double As[2][RBT * 4 * 64];
   __shared__ ColState cst[2 * 256];
-  __shared__ int sdel[kMaxTerms];
   const int g = blockIdx.x;
   // whole tiles, G at a time; the tiles of one XCD (g mod 8) are contiguous
   const int full = (ntiles / G) * G;
@@ -1506,26 +1323,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm(const GemmJob *__restrict__ job
   for (int t0 = 0; t0 < full; t0 += G) {
     const int tile = t0 + gx;
     const GemmJob J = jobs[find_job_tiles(jobs, njobs, tile)];
-    gemm_tile<T, MODE, FOLD, RBT>(J, tile - J.tiles_start, 0, J.nterms, nullptr, dvec, As,
-                                  cst, sdel);
+    gemm_tile<MODE, RBT>(J, tile - J.tiles_start, 0, J.nterms, nullptr, As, cst);
   }
   if (full == ntiles) return;
-  if (MODE == MODE_M2L && dyn_items > 0) {
-    // the remaining tiles, `parts` pieces each, taken in order from the counter
-    __shared__ int item_sh;
-    for (;;) {
-      if (threadIdx.x == 0) item_sh = atomicAdd(ctr, 1);
-      __syncthreads();
-      const int item = item_sh;
-      __syncthreads();
-      if ((unsigned)item >= (unsigned)dyn_items) return;  // done (or a stale counter)
-      const int tile = full + item / parts, q = item % parts;
-      const GemmJob J = jobs[find_job_tiles(jobs, njobs, tile)];
-      gemm_tile<T, MODE, FOLD, RBT>(J, tile - J.tiles_start, q * J.nterms / parts,
-                                    (q + 1) * J.nterms / parts, ws + (size_t)item * TILE,
-                                    dvec, As, cst, sdel);
-    }
-  }
   // the remaining units, split evenly
   const GemmJob Jr = jobs[find_job_tiles(jobs, njobs, full)];
   const int64_t S = Jr.units_start + (int64_t)(full - Jr.tiles_start) * Jr.nterms;
@@ -1545,7 +1345,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm(const GemmJob *__restrict__ job
     u = ts + term1;
     const bool whole = term0 == 0 && term1 == J.nterms;
     double *part = whole ? nullptr : ws + (size_t)(2 * g + (ua >= ts ? 0 : 1)) * TILE;
-    gemm_tile<T, MODE, FOLD, RBT>(J, tile_local, term0, term1, part, dvec, As, cst, sdel);
+    gemm_tile<MODE, RBT>(J, tile_local, term0, term1, part, As, cst);
   }
 }
 
@@ -1558,45 +1358,32 @@ constexpr int kFixupSplit = 4;
 template <int RBT>
 __global__ __launch_bounds__(256) void k_gemm_fixup(const GemmJob *__restrict__ jobs, int njobs,
                                                     int ntiles, int64_t units, int G, int GT,
-                                                    const double *__restrict__ ws, int dyn_items,
-                                                    int parts, int *__restrict__ ctr) {
+                                                    const double *__restrict__ ws) {
   constexpr int COLS = 64 * gemm_cpw(RBT), TILE = RBT * 16 * COLS;
   constexpr int SLICE = TILE / kFixupSplit;
   static_assert(SLICE % 256 == 0 && 256 % COLS == 0, "fixup slices");
   const int full = (ntiles / G) * G;
   const int tile = full + (int)(blockIdx.x / kFixupSplit);
   const int slice = (int)(blockIdx.x % kFixupSplit);
-  if (dyn_items > 0 && blockIdx.x == 0 && threadIdx.x == 0) stg(ctr, 0);  // for the next launch
   if (tile >= ntiles) return;
   const GemmJob J = jobs[find_job_tiles(jobs, njobs, tile)];
   const int tile_local = tile - J.tiles_start;
-  int64_t glo;
-  int np, first;
-  if (dyn_items > 0) {
-    // `parts` pieces in slots (tile - full) parts + q
-    np = parts;
-    first = (tile - full) * parts;
-    glo = 0;
-  } else {
-    const GemmJob Jr = jobs[find_job_tiles(jobs, njobs, full)];
-    const int64_t S = Jr.units_start + (int64_t)(full - Jr.tiles_start) * Jr.nterms;
-    const int64_t R = units - S;
-    const int Gt = (int)min((int64_t)GT, R);
-    // unit range of the tile relative to S; workgroup g starts at unit
-    // sk_bound(g) = floor(g R / Gt), so the last one starting at or before ts is
-    // floor(((ts + 1) Gt - 1) / R) and the last one starting before te is
-    // floor((te Gt - 1) / R)
-    const int64_t ts = J.units_start + (int64_t)tile_local * J.nterms - S, te = ts + J.nterms;
-    glo = min(((ts + 1) * Gt - 1) / R, (int64_t)Gt - 1);
-    const int64_t ghi = min((te * Gt - 1) / R, (int64_t)Gt - 1);
-    if (ghi == glo) return;  // written directly
-    np = (int)(ghi - glo + 1);
-    first = (int)(2 * glo + (sk_bound(glo, R, Gt) == ts ? 0 : 1));
-  }
-  // slot of piece i: consecutive slots for the counter's pieces; for the even
-  // split, glo's piece then the first slot of each later workgroup
-  const bool dyn = dyn_items > 0;
-  auto slot_of = [&](int i) { return dyn ? first + i : (i == 0 ? first : (int)(2 * (glo + i))); };
+  const GemmJob Jr = jobs[find_job_tiles(jobs, njobs, full)];
+  const int64_t S = Jr.units_start + (int64_t)(full - Jr.tiles_start) * Jr.nterms;
+  const int64_t R = units - S;
+  const int Gt = (int)min((int64_t)GT, R);
+  // unit range of the tile relative to S; workgroup g starts at unit
+  // sk_bound(g) = floor(g R / Gt), so the last one starting at or before ts is
+  // floor(((ts + 1) Gt - 1) / R) and the last one starting before te is
+  // floor((te Gt - 1) / R)
+  const int64_t ts = J.units_start + (int64_t)tile_local * J.nterms - S, te = ts + J.nterms;
+  const int64_t glo = min(((ts + 1) * Gt - 1) / R, (int64_t)Gt - 1);
+  const int64_t ghi = min((te * Gt - 1) / R, (int64_t)Gt - 1);
+  if (ghi == glo) return;  // written directly
+  const int np = (int)(ghi - glo + 1);
+  const int first = (int)(2 * glo + (sk_bound(glo, R, Gt) == ts ? 0 : 1));
+  // slot of piece i: glo's piece, then the first slot of each later workgroup
+  auto slot_of = [&](int i) { return i == 0 ? first : (int)(2 * (glo + i)); };
   const int rowtile = tile_local % J.nrowtiles, coltile = tile_local / J.nrowtiles;
   const int rb0 = rowtile * RBT, col0 = coltile * COLS;
   const int nrows = min(RBT * 16, J.dpm - 16 * rb0);
@@ -1606,15 +1393,7 @@ __global__ __launch_bounds__(256) void k_gemm_fixup(const GemmJob *__restrict__ 
   const int jo = col0 + jt;
   if (jo >= ncols) return;
   const int tt = jo / J.nrhs, ro = jo - tt * J.nrhs;
-  int tso;
-  double *Cout = J.C;
-  if (J.colref) {
-    const ColRef cr = J.colref[tt];
-    tso = cr.slot;
-    Cout = J.colsrc[cr.rec].C;
-  } else {
-    tso = J.tgt ? ldg(J.tgt + tt) : tt;
-  }
+  const int tso = J.tgt ? ldg(J.tgt + tt) : tt;
   const int64_t obase = ((int64_t)tso * J.nrhs + ro) * J.dpm + 16 * rb0;
   for (int e = slice * SLICE + (int)threadIdx.x; e < (slice + 1) * SLICE; e += 256) {
     const int rt = e / COLS;
@@ -1631,7 +1410,7 @@ __global__ __launch_bounds__(256) void k_gemm_fixup(const GemmJob *__restrict__ 
     for (; i < np; ++i) v += ldg(ws + (size_t)slot_of(i) * TILE + e);
     const int64_t o = obase + rt;
     if (J.mode == MODE_L2L) v += ldg(J.Cadd + o);
-    stg(Cout + o, v);
+    stg(J.C + o, v);
     if (J.C32) stg(J.C32 + o, (float)v);
   }
 }
@@ -1910,7 +1689,7 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
     int tiles = 0;
     jt.m2l_first = (int)h.size();
     const LevelHost &F = P.lh[depth];
-    jt.m2l_rbt = mixed ? pick_rbt((F.r ? F.rp : F.dpB) / 16) : pick_m2l8((F.r ? F.rp : F.dpB) / 16);
+    jt.m2l_rbt = (mixed ? pick_m2l32 : pick_m2l8)((F.r ? F.rp : F.dpB) / 16);
     for (int k = depth; k >= 2; --k) {
       if (uses_m2l2(P, k)) continue;  // the factored M2L below
       const bool cz = P.lh[k].r > 0;
@@ -1925,7 +1704,7 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
         if (mixed) {
           J.A = P.ld[k].kfrag32;
           J.Bsrc = cz ? P.ld[k].Whp32 : P.ld[k].Wh32;
-          J.a_stride = (int64_t)dm * dk;
+          J.a_stride = (int64_t)dm * dk * sizeof(float);
         } else {
           J.A = P.ld[k].k8;
           J.Bsrc = P.ld[k].w8;
@@ -1946,7 +1725,7 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
         J.cls = c;
         J.mode = MODE_M2L;
         J.nrhs = nrhs;
-        finish_job(J, tiles, jt.m2l_rbt, mixed ? 0 : m2l8_cols(jt.m2l_rbt));
+        finish_job(J, tiles, jt.m2l_rbt, mixed ? kM2l32Cols : m2l8_cols(jt.m2l_rbt));
         h.push_back(J);
       }
     }
@@ -2142,53 +1921,41 @@ namespace {
 // ws holds ws_len doubles: the pieces of the Stream-K tail, TILE doubles each, 2
 // per tail workgroup, so the tail is split over at most ws_len / (2 TILE)
 // workgroups (G itself for the plan's own workspace, fewer for a smaller one)
-template <typename T, int MODE, int RBT>
+template <int MODE, int RBT>
 void launch_gemm_rbt(const GemmJob *jobs, int n, int tiles, int64_t units, int gmax,
-                     double *ws, size_t ws_len, const int8_t *dvec, hipStream_t s) {
+                     double *ws, size_t ws_len, hipStream_t s) {
   const size_t TILE = (size_t)RBT * 16 * gemm_cols(RBT);
-  int *ctr = (int *)(ws + ws_len - kCounterDoubles);
   const size_t len = ws_len - kCounterDoubles;  // pieces
   const int G = (int)std::min<int64_t>(units, gmax);
   const int GT = (int)std::min<size_t>((size_t)G, len / (2 * TILE));
   const int rest = tiles - (tiles / G) * G;
-  // the counter's split of the remaining tiles (M2L, when its pieces fit)
-  int dyn = 0;
-  int parts = 0;
-  if (MODE == MODE_M2L && G > 1 && rest > 0) {
-    // (an M2L job has 189 terms, more than kMaxTailParts)
-    parts = (int)std::min<size_t>(kMaxTailParts, len / ((size_t)rest * TILE));
-    if (parts >= 2) dyn = rest * parts;
-  }
-  constexpr bool fold = sizeof(T) == 4;
-  hipLaunchKernelGGL((k_gemm<T, MODE, fold, RBT>), dim3(G), dim3(256), 0, s, jobs, n, tiles,
-                     units, G, GT, ws, dvec, dyn, parts, ctr);
+  hipLaunchKernelGGL((k_gemm<MODE, RBT>), dim3(G), dim3(256), 0, s, jobs, n, tiles, units, G, GT,
+                     ws);
   if (G > 1 && rest > 0)
     hipLaunchKernelGGL((k_gemm_fixup<RBT>), dim3(rest * kFixupSplit), dim3(256), 0, s, jobs, n,
-                       tiles, units, G, GT, ws, dyn, parts, ctr);
+                       tiles, units, G, GT, ws);
 }
 
-template <typename T, int MODE>
+template <int MODE>
 void launch_gemm_tab(const GemmJob *jobs, int n, int tiles, int64_t units, int rbt, int gmax,
-                     double *ws, size_t ws_len, const int8_t *dvec, hipStream_t s) {
+                     double *ws, size_t ws_len, hipStream_t s) {
   if (n == 0 || tiles == 0 || units == 0) return;
   switch (rbt) {
-    case 4: launch_gemm_rbt<T, MODE, 4>(jobs, n, tiles, units, gmax, ws, ws_len, dvec, s); break;
-    case 3: launch_gemm_rbt<T, MODE, 3>(jobs, n, tiles, units, gmax, ws, ws_len, dvec, s); break;
-    case 5: launch_gemm_rbt<T, MODE, 5>(jobs, n, tiles, units, gmax, ws, ws_len, dvec, s); break;
-
-    default: launch_gemm_rbt<T, MODE, 6>(jobs, n, tiles, units, gmax, ws, ws_len, dvec, s); break;
+    case 4: launch_gemm_rbt<MODE, 4>(jobs, n, tiles, units, gmax, ws, ws_len, s); break;
+    case 3: launch_gemm_rbt<MODE, 3>(jobs, n, tiles, units, gmax, ws, ws_len, s); break;
+    case 5: launch_gemm_rbt<MODE, 5>(jobs, n, tiles, units, gmax, ws, ws_len, s); break;
+    default: launch_gemm_rbt<MODE, 6>(jobs, n, tiles, units, gmax, ws, ws_len, s); break;
   }
 }
 
 // a plan's launch: its Stream-K workspace, or the one its caller lends for this
 // pass (P.run_ws, P.run_ws_len)
-template <typename T, int MODE>
+template <int MODE>
 void launch_gemm(Plan &P, int first, int n, int tiles, int64_t units, hipStream_t s,
                  int rbt = 6) {
   double *ws = P.run_ws ? P.run_ws : P.sk_ws;
   const size_t len = P.run_ws ? P.run_ws_len : stream_k_ws_len(P.sk_groups);
-  launch_gemm_tab<T, MODE>(P.job_dev + first, n, tiles, units, rbt, P.sk_groups, ws, len, P.dvec,
-                           s);
+  launch_gemm_tab<MODE>(P.job_dev + first, n, tiles, units, rbt, P.sk_groups, ws, len, s);
 }
 
 void launch_gemm_fused(const FusedGemm &F, int mode, bool fp32, int gmax, double *ws,
@@ -2196,21 +1963,17 @@ void launch_gemm_fused(const FusedGemm &F, int mode, bool fp32, int gmax, double
   const size_t len = stream_k_ws_len(gmax);
   switch (mode) {
     case MODE_M2M:
-      launch_gemm_tab<double, MODE_M2M>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, dvec,
-                                        s);
+      launch_gemm_tab<MODE_M2M>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, s);
       break;
     case MODE_L2L:
-      launch_gemm_tab<double, MODE_L2L>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, dvec,
-                                        s);
+      launch_gemm_tab<MODE_L2L>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, s);
       break;
     case MODE_PROJ:
-      launch_gemm_tab<double, MODE_PROJ>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, dvec,
-                                         s);
+      launch_gemm_tab<MODE_PROJ>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, s);
       break;
     default:
       if (fp32)
-        launch_gemm_tab<float, MODE_M2L>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, dvec,
-                                         s);
+        launch_m2l32(F.dev, F.n, F.tiles, F.rbt, F.dk, gmax / 2, ws, len, dvec, s);
       else
         launch_m2l8(F.dev, F.n, F.tiles, F.rbt, gmax / 2, ws, len, dvec, s);
   }
@@ -2397,7 +2160,7 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
   {
     Timer tm(P, s, EIFMM_PH_M2M);
     for (int k = depth - 1; k >= 2; --k)
-      launch_gemm<double, MODE_M2M>(P, P.jobs.m2m_first[k], P.jobs.m2m_n[k], P.jobs.m2m_tiles[k],
+      launch_gemm<MODE_M2M>(P, P.jobs.m2m_first[k], P.jobs.m2m_n[k], P.jobs.m2m_tiles[k],
                                     P.jobs.m2m_units[k], s, P.jobs.m2m_rbt[k]);
   }
   // step 3: What = Delta W = B^{-T} Gamma^{-1} W on uncompressed levels; on
@@ -2432,15 +2195,17 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
   // step 4: M2L (with the compression projections around it when enabled)
   if (P.jobs.pre_n) {
     Timer tm(P, s, EIFMM_PH_PROJ);
-    launch_gemm<double, MODE_PROJ>(P, P.jobs.pre_first, P.jobs.pre_n, P.jobs.pre_tiles,
+    launch_gemm<MODE_PROJ>(P, P.jobs.pre_first, P.jobs.pre_n, P.jobs.pre_tiles,
                                    P.jobs.pre_units, s, P.jobs.pre_rbt);
   }
   if (fork_late) hipEventRecord(P.ev_fork, s);
   {
     Timer tm(P, s, EIFMM_PH_M2L);
+    double *ws = P.run_ws ? P.run_ws : P.sk_ws;
+    const size_t ws_len = P.run_ws ? P.run_ws_len : stream_k_ws_len(P.sk_groups);
     if (mixed)
-      launch_gemm<float, MODE_M2L>(P, P.jobs.m2l_first, P.jobs.m2l_n, P.jobs.m2l_tiles,
-                                   P.jobs.m2l_units, s, P.jobs.m2l_rbt);
+      launch_m2l32(P.job_dev + P.jobs.m2l_first, P.jobs.m2l_n, P.jobs.m2l_tiles, P.jobs.m2l_rbt,
+                   HL.r > 0 ? HL.rp : HL.dp, P.sk_groups / 2, ws, ws_len, P.dvec, s);
     else if (P.jobs.m2l_n) {
       DigitDesc dd[kMaxLevels];
       int nd = 0, blk = 0;
@@ -2451,8 +2216,7 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
       }
       launch_digits(dd, nd, blk, s);
       launch_m2l8(P.job_dev + P.jobs.m2l_first, P.jobs.m2l_n, P.jobs.m2l_tiles, P.jobs.m2l_rbt,
-                  P.sk_groups / 2, P.run_ws ? P.run_ws : P.sk_ws,
-                  P.run_ws ? P.run_ws_len : stream_k_ws_len(P.sk_groups), P.dvec, s);
+                  P.sk_groups / 2, ws, ws_len, P.dvec, s);
     }
     for (const M2l2Launch &L : P.m2l2_launch) launch_m2l2(P.m2l2_dev, L, P.dvec, P.m2l2_ws, s);
   }
@@ -2467,14 +2231,14 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
   }
   if (P.jobs.post_n) {
     Timer tm(P, s, EIFMM_PH_PROJ);
-    launch_gemm<double, MODE_PROJ>(P, P.jobs.post_first, P.jobs.post_n, P.jobs.post_tiles,
+    launch_gemm<MODE_PROJ>(P, P.jobs.post_first, P.jobs.post_n, P.jobs.post_tiles,
                                    P.jobs.post_units, s, P.jobs.post_rbt);
   }
   // step 5: l^2 = g^2, then L2L downwards
   {
     Timer tm(P, s, EIFMM_PH_L2L);
     for (int k = 3; k <= depth; ++k)
-      launch_gemm<double, MODE_L2L>(P, P.jobs.l2l_first[k], P.jobs.l2l_n[k], P.jobs.l2l_tiles[k],
+      launch_gemm<MODE_L2L>(P, P.jobs.l2l_first[k], P.jobs.l2l_n[k], P.jobs.l2l_tiles[k],
                                     P.jobs.l2l_units[k], s, P.jobs.l2l_rbt[k]);
   }
   // step 6: lhat = Delta^{J_0,I_0} l on the leaf level (Delta^T l with one EIM)
@@ -2772,7 +2536,7 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, bool mixed
           GemmJob J{};
           J.A = A;
           J.terms = P.dlist + 189 * c;
-          J.a_stride = (int64_t)dm * dk * (mixed ? 1 : kDigits);
+          J.a_stride = (int64_t)dm * dk * (mixed ? sizeof(float) : kDigits);
           J.rscale = P.ld[k].rscale;
           J.nterms = 189;
           J.dpm = dm;
@@ -2789,7 +2553,7 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, bool mixed
     }
   }
   F = FusedGemm{};
-  F.rbt = rbt > 0 ? rbt : mixed ? pick_rbt(dmax / 16) : pick_m2l8(dmax / 16);
+  F.rbt = rbt > 0 ? rbt : (mixed ? pick_m2l32 : pick_m2l8)(dmax / 16);
   if (jobs.empty()) return EIFMM_OK;
   // finest level first (as in a plan's own launch), then operator set and class
   std::vector<int> order(jobs.size());
@@ -2815,11 +2579,12 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, bool mixed
   for (size_t j = 0; j < h.size(); ++j) {
     h[j].colsrc = srcs_dev;
     h[j].colref = refs_dev + off[j];
-    finish_job(h[j], tiles, F.rbt, mixed ? 0 : m2l8_cols(F.rbt));
+    finish_job(h[j], tiles, F.rbt, mixed ? kM2l32Cols : m2l8_cols(F.rbt));
   }
   F.units = finish_units(h, 0);
   F.tiles = tiles;
   F.n = (int)h.size();
+  F.dk = h[0].dpk;
   return bupload(&F.dev, h, track);
 }
 

@@ -73,7 +73,8 @@ struct LevelHost {
 
 // Device copy of one level's tables.
 struct LevelDev {
-  // M2L operators: FP32 fragments (mixed), or digit fragments and row scales (FP64)
+  // M2L operators: FP32 fragments, 4 k per lane (mixed), or digit fragments and row
+  // scales (FP64)
   float *kfrag32 = nullptr;
   int8_t *k8 = nullptr;
   double *rscale = nullptr;
@@ -138,7 +139,7 @@ struct GemmJob {
   const ColRef *colref;  // packed M2L: per target column (tgt, tgt_keys, src_slot,
   const ColSrc *colsrc;  // Bsrc and C unused); null otherwise
   // FP64 M2L: scale of each source column and of each operator row (A and Bsrc hold
-  // digits, dpk is the padded column length, a_stride is in bytes)
+  // digits, dpk is the padded column length).  a_stride of both M2Ls is in bytes
   const double *bscale, *rscale;
 };
 
@@ -181,6 +182,7 @@ struct IoDesc {
 struct FusedGemm {
   GemmJob *dev = nullptr;
   int n = 0, tiles = 0, rbt = 6;
+  int dk = 0;  // columns of the first job's operators (M2L)
   int64_t units = 0;
 };
 
@@ -408,6 +410,11 @@ int pick_rbt(int nrb);
 int pick_m2l8(int nrb);
 int upload_digit_operators(const std::vector<double> &frag, int rows, int cols, int8_t *dig,
                            double *scale);
+// mixed M2L (m2l32.hip)
+constexpr int kM2l32Cols = 128;  // columns of its tiles
+int pick_m2l32(int nrb);
+void launch_m2l32(const GemmJob *jobs, int n, int tiles, int height, int dk, int cus, double *ws,
+                  size_t ws_len, const int8_t *dvec, hipStream_t s);
 int digit_blocks(int ncols);
 void launch_digits(const DigitDesc *lv, int nlev, int blocks, hipStream_t s);
 void launch_digits_list(const DigitDesc *dev, int n, int blocks, hipStream_t s);
