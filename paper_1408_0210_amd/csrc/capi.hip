@@ -313,6 +313,14 @@ int setup_workspaces(eifmm_plan h, double *shared_ws) {
     else
       TRY(dalloc(&D.l, mb, tr));
   }
+  // (a batch's plans share their tables and run every level's M2L packed)
+  if (!shared_ws && depth >= 2 && depth <= kFewDepth && !uses_m2l2(P, 2)) {
+    const LevelHost &H = P.lh[2];
+    const size_t bytes = m2l_few_bytes(H.r > 0 ? H.rp : H.dpB, mixed);
+    unsigned long long *fw = nullptr;
+    TRY(dalloc(&fw, bytes / sizeof(unsigned long long) + 1, tr));
+    P.few_ws = fw;
+  }
   P.sk_groups = stream_k_groups(P.device);
   if (shared_ws)
     P.sk_ws = shared_ws;

@@ -1692,6 +1692,7 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
     jt.m2l_rbt = (mixed ? pick_m2l32 : pick_m2l8)((F.r ? F.rp : F.dpB) / 16);
     for (int k = depth; k >= 2; --k) {
       if (uses_m2l2(P, k)) continue;  // the factored M2L below
+      if (m2l_by_offset(P, k, nrhs)) continue;
       const bool cz = P.lh[k].r > 0;
       // rows: g (the second EIM's size); columns: What
       // (FP64: whole 64-element chunks)
@@ -1738,6 +1739,17 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
     for (int j = jt.m2l_first; j < jt.m2l_first + jt.m2l_n; ++j)
       fx += 2.0 * (double)h[j].nrowtiles * 16 * jt.m2l_rbt * h[j].dpk * (double)h[j].ntgt *
             h[j].nrhs * h[j].nterms;
+    if (depth >= 2 && m2l_by_offset(P, 2, nrhs) && P.nact[2] > 0) {
+      // whole 16-column blocks of the (4 - |dx|) (4 - |dy|) (4 - |dz|) targets of an offset
+      const LevelHost &H = P.lh[2];
+      double cols = 0;
+      for (int x = -3; x <= 3; ++x)
+        for (int y = -3; y <= 3; ++y)
+          for (int z = -3; z <= 3; ++z)
+            if (std::max({std::abs(x), std::abs(y), std::abs(z)}) > 1)
+              cols += ((4 - std::abs(x)) * (4 - std::abs(y)) * (4 - std::abs(z)) + 15) / 16 * 16;
+      fx += 2.0 * cols * (H.r ? H.rp : H.dpB) * (H.r ? H.rp : H.dp);
+    }
     P.m2l_flops_exec = fx;
     // factored M2L levels: one job per child class, grouped by rp; algorithmic
     // flops 2 (r s_o + s_o r) per interaction pair, with the mean s_o over the
@@ -2203,10 +2215,11 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
     Timer tm(P, s, EIFMM_PH_M2L);
     double *ws = P.run_ws ? P.run_ws : P.sk_ws;
     const size_t ws_len = P.run_ws ? P.run_ws_len : stream_k_ws_len(P.sk_groups);
+    const bool few = m2l_by_offset(P, 2, nrhs) && P.nact[2] > 0;
     if (mixed)
       launch_m2l32(P.job_dev + P.jobs.m2l_first, P.jobs.m2l_n, P.jobs.m2l_tiles, P.jobs.m2l_rbt,
                    HL.r > 0 ? HL.rp : HL.dp, P.sk_groups / 2, ws, ws_len, P.dvec, s);
-    else if (P.jobs.m2l_n) {
+    else if (P.jobs.m2l_n || few) {
       DigitDesc dd[kMaxLevels];
       int nd = 0, blk = 0;
       for (int k = depth; k >= 2; --k) {
@@ -2217,6 +2230,15 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
       launch_digits(dd, nd, blk, s);
       launch_m2l8(P.job_dev + P.jobs.m2l_first, P.jobs.m2l_n, P.jobs.m2l_tiles, P.jobs.m2l_rbt,
                   P.sk_groups / 2, ws, ws_len, P.dvec, s);
+    }
+    if (few) {
+      const LevelHost &H = P.lh[2];
+      const LevelDev &L2 = P.ld[2];
+      const bool cz = H.r > 0;
+      const void *B = !mixed ? (const void *)L2.w8
+                             : cz ? (const void *)L2.Whp32 : (const void *)L2.Wh32;
+      launch_m2l_few(L2, mixed, B, cz ? H.rp : H.dpB, cz ? H.rp : H.dp, cz ? L2.gp : L2.g,
+                     P.few_ws, P.dlist, P.dvec, s);
     }
     for (const M2l2Launch &L : P.m2l2_launch) launch_m2l2(P.m2l2_dev, L, P.dvec, P.m2l2_ws, s);
   }

@@ -369,6 +369,7 @@ struct Plan {
   // a Stream-K workspace lent for one pass (null: sk_ws), run_ws_len doubles
   double *run_ws = nullptr;
   size_t run_ws_len = 0;
+  void *few_ws = nullptr;  // products of level 2 by offset (null: not taken)
   double m2l_flops = 0, proj_flops = 0;
   double m2l_flops_exec = 0;  // what the M2L MFMAs execute (padding, empty sources)
 
@@ -415,6 +416,15 @@ constexpr int kM2l32Cols = 128;  // columns of its tiles
 int pick_m2l32(int nrb);
 void launch_m2l32(const GemmJob *jobs, int n, int tiles, int height, int dk, int cus, double *ws,
                   size_t ws_len, const int8_t *dvec, hipStream_t s);
+// level 2 by offset (m2l_few.hip): trees of at most this depth (deeper ones hide the
+// level's few tiles among the others), one right-hand side, plans with their own tables
+constexpr int kFewDepth = 3;
+inline bool m2l_by_offset(const Plan &P, int k, int nrhs) {
+  return k == 2 && nrhs == 1 && P.few_ws != nullptr;
+}
+size_t m2l_few_bytes(int dm, bool mixed);
+void launch_m2l_few(const LevelDev &D, bool mixed, const void *B, int dm, int dk, double *C,
+                    void *ws, const int16_t *terms, const int8_t *dvec, hipStream_t s);
 int digit_blocks(int ncols);
 void launch_digits(const DigitDesc *lv, int nlev, int blocks, hipStream_t s);
 void launch_digits_list(const DigitDesc *dev, int n, int blocks, hipStream_t s);
