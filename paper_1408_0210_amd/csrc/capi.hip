@@ -179,6 +179,13 @@ int setup_tables(eifmm_plan h) {
       for (size_t q = 0; q < f32.size(); ++q)
         f32[(q & ~(size_t)255) + (q & 63) * 4 + ((q >> 6) & 3)] = (float)H.kfrag[q];
       TRY(upload(&D.kfrag32, f32.data(), f32.size(), tr));
+    } else if (!P.shared_tables && H.sp2.empty() &&
+               std::max(H.r > 0 ? H.rp : H.dpB, H.r > 0 ? H.rp : H.dp) <= kSmallM2l) {
+      // (a batch packs problems of any operator size into the digit kernel's jobs)
+      const int dm = H.r > 0 ? H.rp : H.dpB, dk = H.r > 0 ? H.rp : H.dp;
+      const std::vector<double> a =
+          m2l_small_operators(H.kfrag, dm, dk, m2l_small_steps(H.r > 0 ? H.r : H.d));
+      TRY(upload(&D.ksmall, a.data(), a.size(), tr));
     } else if (P.shared_tables || H.sp2.empty()) {
       const int dm = H.r > 0 ? H.rp : H.dpB, dk = H.r > 0 ? H.rp : H.dp;
       TRY(dalloc(&D.k8, (size_t)kNumOffsets * dm * digit_bytes(dk), tr));
@@ -300,7 +307,7 @@ int setup_workspaces(eifmm_plan h, double *shared_ws) {
     } else if (mixed) {
       TRY(dalloc(&D.Wh32, m, tr));
     }
-    if (!mixed && !uses_m2l2(P, k)) {
+    if (!mixed && !D.ksmall && !uses_m2l2(P, k)) {
       const int dk = P.lh[k].r > 0 ? P.lh[k].rp : P.lh[k].dp;
       TRY(dalloc(&D.w8, D.cap * (size_t)R * digit_bytes(dk), tr));
       TRY(dalloc(&D.wscale, D.cap * (size_t)R, tr));
@@ -314,7 +321,7 @@ int setup_workspaces(eifmm_plan h, double *shared_ws) {
       TRY(dalloc(&D.l, mb, tr));
   }
   // (a batch's plans share their tables and run every level's M2L packed)
-  if (!shared_ws && depth >= 2 && depth <= kFewDepth && !uses_m2l2(P, 2)) {
+  if (!shared_ws && depth >= 2 && depth <= kFewDepth && !uses_m2l2(P, 2) && !P.ld[2].ksmall) {
     const LevelHost &H = P.lh[2];
     const size_t bytes = m2l_few_bytes(H.r > 0 ? H.rp : H.dpB, mixed);
     unsigned long long *fw = nullptr;

@@ -4,6 +4,8 @@
 #include <climits>
 #include <type_traits>
 
+#include <vector>
+
 #include "devutil.hpp"
 #include "plan.hpp"
 
@@ -104,12 +106,37 @@ __device__ inline double *tile_output(const GemmJob &J, int jo) {
   return Cout + ((int64_t)tso * J.nrhs + ro) * J.dpm;
 }
 
+// One wave: the terms in [term0, term1) that reach inside the domain from some box of
+// [lo, hi], in order into sdel (LDS), packed (dx+3) | (dy+3) << 3 | (dz+3) << 6 | id << 9;
+// returns their number.  Offset delta reaches inside when hi + delta >= 0 and
+// lo + delta < side on every axis.
+__device__ inline int list_terms(const GemmJob &J, int term0, int term1, const int (&lo)[3],
+                                 const int (&hi)[3], const int8_t *__restrict__ dvec, int *sdel) {
+  const int lane = threadIdx.x & 63;
+  const int side = 1 << J.level;
+  const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  int nk = 0;
+  for (int b = term0; b < term1; b += 64) {
+    const int i = b + lane;
+    bool keep = false;
+    int pk = 0;
+    if (i < term1) {
+      const int id = ldg(J.terms + i);
+      const int d0 = dvec[3 * id], d1 = dvec[3 * id + 1], d2 = dvec[3 * id + 2];
+      pk = (d0 + 3) | ((d1 + 3) << 3) | ((d2 + 3) << 6) | (id << 9);
+      keep = hi[0] + d0 >= 0 && lo[0] + d0 < side && hi[1] + d1 >= 0 && lo[1] + d1 < side &&
+             hi[2] + d2 >= 0 && lo[2] + d2 < side;
+    }
+    const uint64_t m = __ballot(keep);
+    if (keep) sdel[nk + (int)__popcll(m & below)] = pk;
+    nk += (int)__popcll(m);
+  }
+  return nk;
+}
+
 // The terms in [term0, term1) of an 8-wave tile whose source box lies inside the domain
-// for some of its columns, in order into sdel (LDS), packed (dx+3) | (dy+3) << 3 |
-// (dz+3) << 6 | id << 9; returns their number.  bb: the box of this lane's column (16
-// columns per wave, equal in lanes 16 apart).  The tile's boxes span [lo, hi] per axis,
-// and offset delta reaches inside when hi + delta >= 0 and lo + delta < side on every
-// axis.  Two workgroup barriers.
+// for some of its columns (list_terms).  bb: the box of this lane's column (16 columns
+// per wave, equal in lanes 16 apart).  Two workgroup barriers.
 __device__ inline int tile_terms(const GemmJob &J, int term0, int term1, int (&bb)[6],
                                  const int8_t *__restrict__ dvec, int *sdel) {
   __shared__ int sbox[8][6];
@@ -140,24 +167,7 @@ __device__ inline int tile_terms(const GemmJob &J, int term0, int term1, int (&b
         hi[a] = max(hi[a], sbox[q][3 + a]);
       }
     }
-    const int side = 1 << J.level;
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    int nk = 0;
-    for (int b = term0; b < term1; b += 64) {
-      const int i = b + lane;
-      bool keep = false;
-      int pk = 0;
-      if (i < term1) {
-        const int id = ldg(J.terms + i);
-        const int d0 = dvec[3 * id], d1 = dvec[3 * id + 1], d2 = dvec[3 * id + 2];
-        pk = (d0 + 3) | ((d1 + 3) << 3) | ((d2 + 3) << 6) | (id << 9);
-        keep = hi[0] + d0 >= 0 && lo[0] + d0 < side && hi[1] + d1 >= 0 && lo[1] + d1 < side &&
-               hi[2] + d2 >= 0 && lo[2] + d2 < side;
-      }
-      const uint64_t m = __ballot(keep);
-      if (keep) sdel[nk + (int)__popcll(m & below)] = pk;
-      nk += (int)__popcll(m);
-    }
+    const int nk = list_terms(J, term0, term1, lo, hi, dvec, sdel);
     if (lane == 0) snk = nk;
   }
   lds_barrier();

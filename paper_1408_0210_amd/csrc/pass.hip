@@ -1688,16 +1688,22 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
   {
     int tiles = 0;
     jt.m2l_first = (int)h.size();
-    const LevelHost &F = P.lh[depth];
+    int kf = depth;  // the tile height serves the finest level of this launch
+    while (kf > 2 && P.ld[kf].ksmall) --kf;
+    const LevelHost &F = P.lh[kf];
     jt.m2l_rbt = (mixed ? pick_m2l32 : pick_m2l8)((F.r ? F.rp : F.dpB) / 16);
+    std::vector<GemmJob> small_jobs;  // levels of small operators: a launch of their own
+    int small_tiles = 0;
     for (int k = depth; k >= 2; --k) {
       if (uses_m2l2(P, k)) continue;  // the factored M2L below
       if (m2l_by_offset(P, k, nrhs)) continue;
+      const bool small = P.ld[k].ksmall != nullptr;
       const bool cz = P.lh[k].r > 0;
       // rows: g (the second EIM's size); columns: What
       // (FP64: whole 64-element chunks)
       const int dm = cz ? P.lh[k].rp : P.lh[k].dpB;
-      const int dk = mixed ? (cz ? P.lh[k].rp : P.lh[k].dp) : digit_kp(cz ? P.lh[k].rp : P.lh[k].dp);
+      const int dc = cz ? P.lh[k].rp : P.lh[k].dp;
+      const int dk = mixed || small ? dc : digit_kp(dc);
       for (int c = 0; c < 8; ++c) {
         const int64_t nt = P.cls_off[k][c + 1] - P.cls_off[k][c];
         if (nt == 0) continue;
@@ -1706,6 +1712,10 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
           J.A = P.ld[k].kfrag32;
           J.Bsrc = cz ? P.ld[k].Whp32 : P.ld[k].Wh32;
           J.a_stride = (int64_t)dm * dk * sizeof(float);
+        } else if (small) {
+          J.A = P.ld[k].ksmall;
+          J.Bsrc = cz ? P.ld[k].Whp : P.ld[k].Wh;
+          J.ksteps = m2l_small_steps(cz ? P.lh[k].r : P.lh[k].d);
         } else {
           J.A = P.ld[k].k8;
           J.Bsrc = P.ld[k].w8;
@@ -1726,19 +1736,31 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
         J.cls = c;
         J.mode = MODE_M2L;
         J.nrhs = nrhs;
+        if (small) {
+          finish_job(J, small_tiles, kSmallM2l / 16, kSmallM2lCols);
+          small_jobs.push_back(J);
+          continue;
+        }
         finish_job(J, tiles, jt.m2l_rbt, mixed ? kM2l32Cols : m2l8_cols(jt.m2l_rbt));
         h.push_back(J);
       }
     }
     jt.m2l_n = (int)h.size() - jt.m2l_first;
     jt.m2l_tiles = tiles;
-    jt.m2l_units = finish_units(h, jt.m2l_first);
     // executed work: every column walks all terms of its class, over whole row
     // tiles of the padded operators
     double fx = 0;
     for (int j = jt.m2l_first; j < jt.m2l_first + jt.m2l_n; ++j)
       fx += 2.0 * (double)h[j].nrowtiles * 16 * jt.m2l_rbt * h[j].dpk * (double)h[j].ntgt *
             h[j].nrhs * h[j].nterms;
+    jt.small_first = (int)h.size();
+    jt.small_n = (int)small_jobs.size();
+    jt.small_grid = 0;
+    for (const GemmJob &J : small_jobs) {
+      jt.small_grid += (J.ncoltiles + 7) / 8 * 8;
+      fx += 2.0 * (double)J.dpm * 4 * J.ksteps * (double)J.ntgt * J.nrhs * J.nterms;
+      h.push_back(J);
+    }
     if (depth >= 2 && m2l_by_offset(P, 2, nrhs) && P.nact[2] > 0) {
       // whole 16-column blocks of the (4 - |dx|) (4 - |dy|) (4 - |dz|) targets of an offset
       const LevelHost &H = P.lh[2];
@@ -2223,7 +2245,7 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
       DigitDesc dd[kMaxLevels];
       int nd = 0, blk = 0;
       for (int k = depth; k >= 2; --k) {
-        if (P.nact[k] == 0 || uses_m2l2(P, k)) continue;
+        if (P.nact[k] == 0 || uses_m2l2(P, k) || P.ld[k].ksmall) continue;
         dd[nd] = digit_desc(P, k, nrhs, blk);
         blk += digit_blocks(dd[nd++].ncols);
       }
@@ -2231,6 +2253,7 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
       launch_m2l8(P.job_dev + P.jobs.m2l_first, P.jobs.m2l_n, P.jobs.m2l_tiles, P.jobs.m2l_rbt,
                   P.sk_groups / 2, ws, ws_len, P.dvec, s);
     }
+    launch_m2l_small(P.job_dev + P.jobs.small_first, P.jobs.small_n, P.jobs.small_grid, P.dvec, s);
     if (few) {
       const LevelHost &H = P.lh[2];
       const LevelDev &L2 = P.ld[2];

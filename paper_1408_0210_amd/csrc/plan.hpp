@@ -78,6 +78,7 @@ struct LevelDev {
   float *kfrag32 = nullptr;
   int8_t *k8 = nullptr;
   double *rscale = nullptr;
+  double *ksmall = nullptr;  // or, of at most 32 x 32, FP64 fragments (m2l_small.hip)
   double *m2m = nullptr, *l2l = nullptr;
   double *tri[4] = {nullptr, nullptr, nullptr, nullptr};
   double *X = nullptr;   // d x 3 (leaf level: P2M)
@@ -141,6 +142,7 @@ struct GemmJob {
   // FP64 M2L: scale of each source column and of each operator row (A and Bsrc hold
   // digits, dpk is the padded column length).  a_stride of both M2Ls is in bytes
   const double *bscale, *rscale;
+  int ksteps;  // m2l_small.hip: k-steps of 4 in A (A and Bsrc are FP64 there)
 };
 
 // One problem's leaf level as the near-field, P2M and L2P kernels read it.
@@ -268,8 +270,9 @@ struct JobTables {
   int l2l_first[kMaxLevels] = {}, l2l_n[kMaxLevels] = {}, l2l_tiles[kMaxLevels] = {};
   int m2m_rbt[kMaxLevels] = {}, l2l_rbt[kMaxLevels] = {};
   int64_t m2m_units[kMaxLevels] = {}, l2l_units[kMaxLevels] = {};
-  int64_t m2l_units = 0, pre_units = 0, post_units = 0;
+  int64_t pre_units = 0, post_units = 0;
   int m2l_first = 0, m2l_n = 0, m2l_tiles = 0, m2l_rbt = 6;
+  int small_first = 0, small_n = 0, small_grid = 0;  // M2L of levels of small operators
   int pre_first = 0, pre_n = 0, pre_tiles = 0, pre_rbt = 6;     // What' = U^T B^{-T} z
   int post_first = 0, post_n = 0, post_tiles = 0, post_rbt = 6; // g = U g'
 };
@@ -416,6 +419,12 @@ constexpr int kM2l32Cols = 128;  // columns of its tiles
 int pick_m2l32(int nrb);
 void launch_m2l32(const GemmJob *jobs, int n, int tiles, int height, int dk, int cus, double *ws,
                   size_t ws_len, const int8_t *dvec, hipStream_t s);
+// FP64 M2L of small operators (m2l_small.hip)
+constexpr int kSmallM2l = 32;  // most rows and columns (padded): the tile in registers
+constexpr int kSmallM2lCols = 32;  // columns of a tile
+int m2l_small_steps(int d);
+std::vector<double> m2l_small_operators(const std::vector<double> &frag, int rows, int cols, int ks);
+void launch_m2l_small(const GemmJob *jobs, int n, int grid, const int8_t *dvec, hipStream_t s);
 // level 2 by offset (m2l_few.hip): trees of at most this depth (deeper ones hide the
 // level's few tiles among the others), one right-hand side, plans with their own tables
 constexpr int kFewDepth = 3;
