@@ -1415,6 +1415,141 @@ __global__ __launch_bounds__(256) void k_gemm_fixup(const GemmJob *__restrict__ 
   }
 }
 
+// The same products for launches too small to fill the chip with the tiles above (a tile
+// walks 18 chunks of k with 24 products each at d = 287, and the upper levels have a few
+// dozen of them): a wave takes 48 rows of 16 columns and one term, operators and columns
+// straight to registers two chunks ahead, no barrier.  M2M: the 8 children of a parent by
+// the 8 waves of a workgroup, summed in their order; else 4 waves of neighbouring items.  A
+// term's products are in the order of the tiles, so L2L and PROJ give the same bits.
+// Bound by the latency of its loads and, on the lower levels, the FP64 matrix cores.  10^5
+// uniform points, depth 4, rank 128: L2L 33 -> 27 us and projections 25 -> 19 us a level,
+// M2M (beside the near field) 54 with its fixup -> 51, the pass 850 -> 798 us; 2^20 points,
+// depth 5: 4230 -> 4090 us.
+constexpr int kFewRows = 3;  // row blocks of a wave
+__host__ __device__ constexpr int few_waves(int mode) { return mode == MODE_M2M ? 8 : 4; }
+
+template <int MODE>
+__global__ __launch_bounds__(64 * few_waves(MODE), 2) void k_gemm_few(
+    const GemmJob *__restrict__ jobs, int njobs) {
+  constexpr int R = kFewRows;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int item = MODE == MODE_M2M ? (int)blockIdx.x : (int)blockIdx.x * 4 + w;
+  // the job of the item: a lane per job, items column block by column block
+  int nrg = 1, count = 0;
+  if (lane < njobs) {
+    const GemmJob &Q = jobs[lane];
+    nrg = (ldg(&Q.dpm) / 16 + R - 1) / R;
+    count = nrg * ((ldg(&Q.ntgt) * ldg(&Q.nrhs) + 15) / 16);
+  }
+  int end = count;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(end, o);
+    if (lane >= o) end += v;
+  }
+  const unsigned long long after = __ballot(end > item);
+  if (after == 0) return;  // (M2M: the whole workgroup)
+  const int j = __builtin_ctzll(after);
+  const int local = __builtin_amdgcn_readfirstlane(__shfl(item - (end - count), j));
+  nrg = __builtin_amdgcn_readfirstlane(__shfl(nrg, j));
+  const GemmJob J = jobs[j];
+  const int rb0 = local % nrg * R, col0 = local / nrg * 16;
+  const int nrb = J.dpm >> 4, nks = J.dpk >> 2, nkc = J.dpk >> 4;
+  const int term = MODE == MODE_M2M ? w : 0;
+  // this lane's column
+  const int jc = col0 + (lane & 15);
+  const bool valid = jc < J.ntgt * J.nrhs;
+  int tsl = 0, r = 0, slot = -1;
+  if (valid) {
+    const int tt = jc / J.nrhs;
+    r = jc - tt * J.nrhs;
+    tsl = J.tgt ? ldg(J.tgt + tt) : tt;
+    if constexpr (MODE == MODE_PROJ)
+      slot = tsl;
+    else
+      slot = ldg(gemm_source_addr<MODE>(term, true, ldg(J.tgt_keys + tsl), J.src_slot, 0));
+  }
+  const double *col = gemm_source_ptr(J, slot, r, (const double *)J.Bsrc);
+  const bool some = col != nullptr;
+  col = (some ? col : g_gemm_zero) + 4 * (lane >> 4);
+  const double *A[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+    A[i] = gemm_operand<MODE>(J, term) + (int64_t)min(rb0 + i, nrb - 1) * nks * 64 + lane;
+  d4v acc[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) acc[i] = d4v{0, 0, 0, 0};
+  struct Set {
+    double a[R][4];
+    d2v b[2];
+  } S0, S1, S2;
+  auto load = [&](Set &S, int kc) {
+    kc = min(kc, nkc - 1);
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) S.a[i][ks] = ldg(A[i] + (4 * kc + ks) * 64);
+    S.b[0] = ldg((const d2v *)(col + 16 * kc));
+    S.b[1] = ldg((const d2v *)(col + 16 * kc + 2));
+  };
+  auto products = [&](const Set &S) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int i = 0; i < R; ++i) acc[i] = mfma_f64(S.a[i][ks], S.b[ks >> 1][ks & 1], acc[i]);
+  };
+  if (__ballot(some) != 0) {
+    load(S0, 0);
+    load(S1, 1);
+    for (int kc = 0; kc < nkc; kc += 3) {
+      load(S2, kc + 2);
+      products(S0);
+      if (kc + 1 >= nkc) break;
+      load(S0, kc + 3);
+      products(S1);
+      if (kc + 2 >= nkc) break;
+      load(S1, kc + 4);
+      products(S2);
+    }
+  }
+  int i0 = 0, i1 = R;  // row blocks that this wave stores
+  if constexpr (MODE == MODE_M2M) {
+    __shared__ double part[8][R * 256];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) part[w][(4 * i + q) * 64 + lane] = acc[i][q];
+    __syncthreads();
+    if (w >= R) return;
+    i0 = w;
+    i1 = w + 1;
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        double v = 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += part[u][(4 * w + q) * 64 + lane];
+        acc[i][q] = v;
+      }
+  }
+  if (!valid) return;
+  const int64_t cbase = ((int64_t)tsl * J.nrhs + r) * J.dpm + (lane >> 4);
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    if (i < i0 || i >= i1 || rb0 + i >= nrb) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t o = cbase + 16 * (rb0 + i) + 4 * q;
+      double v = acc[i][q];
+      if constexpr (MODE == MODE_L2L) v += ldg(J.Cadd + o);
+      stg(J.C + o, v);
+      if (J.C32) stg(J.C32 + o, (float)v);
+    }
+  }
+}
+
 // ------------------------------------------------------------------ factored M2L
 // Second compression stage (Sec. 4.2): per offset o the r x r matrix C^delta is
 // the product Ut_o Vt_o of an r x s_o and an s_o x r factor, so a column's
@@ -1970,10 +2105,19 @@ void launch_gemm_rbt(const GemmJob *jobs, int n, int tiles, int64_t units, int g
                        tiles, units, G, GT, ws);
 }
 
+// few: the launch may take the form for few columns (k_gemm_few).  It does when the tiles
+// leave compute units idle: fewer (tile, term) pairs than workgroups.
 template <int MODE>
 void launch_gemm_tab(const GemmJob *jobs, int n, int tiles, int64_t units, int rbt, int gmax,
-                     double *ws, size_t ws_len, hipStream_t s) {
+                     double *ws, size_t ws_len, bool few, hipStream_t s) {
   if (n == 0 || tiles == 0 || units == 0) return;
+  if (few && n <= 64 && units < gmax) {
+    // at most this many items (a job's last tiles may hold fewer; the rest return)
+    const int items = tiles * ((rbt + kFewRows - 1) / kFewRows) * (gemm_cols(rbt) / 16);
+    const int waves = few_waves(MODE), grid = MODE == MODE_M2M ? items : (items + 3) / 4;
+    hipLaunchKernelGGL(k_gemm_few<MODE>, dim3(grid), dim3(64 * waves), 0, s, jobs, n);
+    return;
+  }
   switch (rbt) {
     case 4: launch_gemm_rbt<MODE, 4>(jobs, n, tiles, units, gmax, ws, ws_len, s); break;
     case 3: launch_gemm_rbt<MODE, 3>(jobs, n, tiles, units, gmax, ws, ws_len, s); break;
@@ -1989,7 +2133,10 @@ void launch_gemm(Plan &P, int first, int n, int tiles, int64_t units, hipStream_
                  int rbt = 6) {
   double *ws = P.run_ws ? P.run_ws : P.sk_ws;
   const size_t len = P.run_ws ? P.run_ws_len : stream_k_ws_len(P.sk_groups);
-  launch_gemm_tab<MODE>(P.job_dev + first, n, tiles, units, rbt, P.sk_groups, ws, len, s);
+  // (mixed precision rounds the solved expansions to FP32, which would show an M2M sum in
+  // another order)
+  const bool few = MODE != MODE_M2M || P.cfg.precision == EIFMM_PREC_FP64;
+  launch_gemm_tab<MODE>(P.job_dev + first, n, tiles, units, rbt, P.sk_groups, ws, len, few, s);
 }
 
 void launch_gemm_fused(const FusedGemm &F, int mode, bool fp32, int gmax, double *ws,
@@ -1997,13 +2144,13 @@ void launch_gemm_fused(const FusedGemm &F, int mode, bool fp32, int gmax, double
   const size_t len = stream_k_ws_len(gmax);
   switch (mode) {
     case MODE_M2M:
-      launch_gemm_tab<MODE_M2M>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, s);
+      launch_gemm_tab<MODE_M2M>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, false, s);
       break;
     case MODE_L2L:
-      launch_gemm_tab<MODE_L2L>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, s);
+      launch_gemm_tab<MODE_L2L>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, true, s);
       break;
     case MODE_PROJ:
-      launch_gemm_tab<MODE_PROJ>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, s);
+      launch_gemm_tab<MODE_PROJ>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, true, s);
       break;
     default:
       if (fp32)
