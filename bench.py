@@ -10,8 +10,9 @@ Also reported on the same line:
                 launch (2 r_k^2 per interaction pair per right-hand side, summed
                 over levels, r_k the Sec. 4.2 rank) over its mean launch time from
                 HIP events recorded around it in the timed steps, on the stream the
-                library launches on, against the MFMA peak of its dtype; traffic
-                from the committed rocprofv3 counter summary;
+                library launches on, against the MFMA peak of the path (FP64: the
+                INT8 peak over the 28 digit products of a product; mixed: FP32);
+                traffic from the committed rocprofv3 counter summary;
   phase_roofline every phase against the roofline of the unit that bounds it,
                 from as many steps again with every phase's events on, and the
                 composite T_roof / t;
@@ -44,6 +45,9 @@ sys.path.insert(0, ROOT)
 
 METRIC = "effective interactions/s (N²/t) at rel-L2 err 1e-6, 1e6 pts; batched/FP32 vs plain"
 PEAK_TFLOPS = {"fp64": 78.6, "mixed": 157.3}  # dense MFMA peaks, FP64 and FP32
+# The M2L: FP64 operands as 7 digits of 8 bits, 28 INT8 products (5033 TOP/s dense) per
+# FP64 product; mixed on the FP32 matrix cores.
+M2L_PEAK_TFLOPS = {"fp64": 5033.2 / 28, "mixed": 157.3}
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "m2l_traffic.json")
 
 
@@ -583,7 +587,7 @@ def phase_roofline(st, n, ms_step, precision, kernel):
     what = sum(2.0 * d[k] ** 2 * nact[k] for k in range(2, depth + 1) if not r[k])
     lhat = 2.0 * d[depth] ** 2 * nact[depth]
     mfma64 = PEAK_TFLOPS["fp64"] * 1e12
-    m2l_peak = PEAK_TFLOPS[precision] * 1e12
+    m2l_peak = M2L_PEAK_TFLOPS[precision] * 1e12
     rows = {
         "tree": (TREE_BYTES_PER_POINT * n, "B", "hbm", HBM_PEAK),
         "m2m": (m2m, "flop", "mfma", mfma64),
@@ -716,20 +720,18 @@ def main():
           file=sys.stderr, flush=True)
     m2l_ms = r["m2l_ms"]  # HIP events around the M2L launch in the timed steps
     achieved = st["m2l_flops"] / (m2l_ms * 1e-3) / 1e12
-    peak = PEAK_TFLOPS[args.precision]
+    peak = M2L_PEAK_TFLOPS[args.precision]
     traffic = None
     if os.path.exists(PROFILE_TRAFFIC):
         import hashlib
         tr = json.load(open(PROFILE_TRAFFIC))
         key = f"{args.workload}:{args.precision}"
-        src = open(os.path.join(ROOT, "paper_1408_0210_amd", "csrc", "pass.hip")).read()
-        # the gathered-GEMM kernel source (M2L runs in it): counters taken on another
-        # version of this kernel do not describe it
-        rule = "// ------------------------------------------------------------------ "
-        a = src.index(rule + "gathered GEMM")
-        b = src.index(rule, a + len(rule))  # the next section
-        cur = hashlib.sha256(src[a:b].encode()).hexdigest()
-        if (key in tr and tr[key].get("valid", False) and tr[key].get("gemm_source_sha256") == cur
+        # counters taken on another version of the M2L kernel do not describe it
+        csrc = os.path.join(ROOT, "paper_1408_0210_amd", "csrc")
+        names = ["m2l_tile.hpp", "m2l.hip" if args.precision == "fp64" else "m2l32.hip"]
+        cur = hashlib.sha256(b"".join(open(os.path.join(csrc, q), "rb").read()
+                                      for q in names)).hexdigest()
+        if (key in tr and tr[key].get("valid", False) and tr[key].get("m2l_source_sha256") == cur
                 and tr[key].get("compress_tol") == r["compress_tol"] and not args.tau
                 and not args.depth):
             traffic = tr[key]["bytes_per_launch"]
@@ -747,7 +749,8 @@ def main():
                    "step": "set_points + evaluate", "phase_ms": phases},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": traffic,
-                     "kernel": "k_gemm M2L (all levels, one launch)",
+                     "kernel": ("k_m2l8" if args.precision == "fp64" else "k_m2l32") +
+                               " (M2L of all levels, one launch, and the sum of split tiles)",
                      "flops_per_launch": st["m2l_flops"], "ms_per_launch": m2l_ms,
                      "rank_filtered": st["rank"], "rank_used": st["rpad"],
                      "flops_executed": st["m2l_flops_exec"],

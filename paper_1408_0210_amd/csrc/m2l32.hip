@@ -10,12 +10,11 @@
 // products.  The order of the products of an offset, k by k in the table's order, is the
 // one the accumulation of a single chain has, whatever the chunks.
 //
-// Bound by the FP32 matrix cores (4 products of 32 cycles a fragment), then by the
-// wait at a chunk's barrier.  2^20 points, 64 right-hand sides, d = 287 (18 row
-// blocks, 9 per tile, chunks of 3): 189.9 ms as 3- and 4-block tiles of 4 waves with the
-// operators passed through registers to LDS, 141.7 ms now (114 of the 155 TFLOP/s the
-// instruction reaches).  2^20 points, one right-hand side, rank 128: 2.2 -> 1.9 ms with
-// the near field beside it, the pass 3.93 -> 3.63 ms.
+// Bound by the FP32 matrix cores (32 cycles a product; a bare probe reaches 155 TFLOP/s),
+// then by the wait at a chunk's barrier.  2^20 points, 64 right-hand sides, rank 144 (9 row
+// blocks, one tile, chunks of 3): 189.9 ms as 3-block tiles of 4 waves with the operators
+// passed through registers to LDS, 141.7 ms now (114 TFLOP/s).  10^6 points, one right-hand
+// side, rank 128, the near field beside it: the pass 3.93 -> 3.63 ms.
 #include <algorithm>
 #include <vector>
 
