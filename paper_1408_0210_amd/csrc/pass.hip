@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "devutil.hpp"
+#include "m2l_tile.hpp"
 #include "plan.hpp"
 
 namespace eifmm {
@@ -1550,6 +1551,125 @@ __global__ __launch_bounds__(64 * few_waves(MODE), 2) void k_gemm_few(
   }
 }
 
+// L2L and the projections of many columns: a workgroup of 4 waves computes 16 RB rows (5 to
+// 9 blocks) of 64 columns, each wave every row of its 16.  The operator passes through LDS
+// in 16-k chunks, loaded straight to it one chunk ahead in two buffers, the source columns
+// a chunk ahead in registers; with 4 RB products of 64 cycles a chunk, two workgroups per CU
+// cover the loads.  The products of a result are in the order of the tiles above: same bits.
+// Bound by the FP64 matrix cores, at 64 right-hand sides half by memory too (the columns in,
+// the added l and the result out).  2^20 points, d = 287, rank 144: L2L 9.8 -> 8.3 ms and the
+// projections 10.4 -> 9.3 at 64 right-hand sides; at one, L2L of the leaf level 180 -> 164 us,
+// projections 171 -> 153.
+template <int MODE, int RB>
+__global__ __launch_bounds__(256, 2) void k_gemm_tall(const GemmJob *__restrict__ jobs, int njobs) {
+  static_assert(MODE != MODE_M2M, "one term");
+  __shared__ __align__(16) double As[2][RB * 256];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // the tile: a lane per job counts its tiles, those of one XCD (workgroup mod 8) contiguous
+  int nrg = 1, count = 0;
+  if (lane < njobs) {
+    const GemmJob &Q = jobs[lane];
+    nrg = (ldg(&Q.dpm) / 16 + RB - 1) / RB;
+    count = nrg * ((ldg(&Q.ntgt) * ldg(&Q.nrhs) + 63) / 64);
+  }
+  int end = count;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(end, o);
+    if (lane >= o) end += v;
+  }
+  const int total = __builtin_amdgcn_readfirstlane(__shfl(end, 63));
+  const int x = blockIdx.x % 8, xi = blockIdx.x / 8;
+  if (xi >= total / 8 + (x < total % 8 ? 1 : 0)) return;
+  const int tile = x * (total / 8) + min(x, total % 8) + xi;
+  const int j = __builtin_ctzll(__ballot(end > tile));
+  const int local = __builtin_amdgcn_readfirstlane(__shfl(tile - (end - count), j));
+  nrg = __builtin_amdgcn_readfirstlane(__shfl(nrg, j));
+  const GemmJob J = jobs[j];
+  const int rb0 = local % nrg * RB, col0 = local / nrg * 64;
+  const int nrb = J.dpm >> 4, nkc = J.dpk >> 4, nv = min(RB, nrb - rb0);
+  // this lane's column
+  const int jc = col0 + 16 * w + (lane & 15);
+  const bool valid = jc < J.ntgt * J.nrhs;
+  int tsl = 0, r = 0, slot = -1;
+  if (valid) {
+    const int tt = jc / J.nrhs;
+    r = jc - tt * J.nrhs;
+    tsl = J.tgt ? ldg(J.tgt + tt) : tt;
+    if constexpr (MODE == MODE_PROJ)
+      slot = tsl;
+    else
+      slot = ldg(gemm_source_addr<MODE>(0, true, ldg(J.tgt_keys + tsl), J.src_slot, 0));
+  }
+  const double *col = gemm_source_ptr(J, slot, r, (const double *)J.Bsrc);
+  col = (col ? col : g_gemm_zero) + 4 * (lane >> 4);
+  const char *Abase = (const char *)(gemm_operand<MODE>(J, 0) + (int64_t)rb0 * nkc * 256);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) double *)&As[0][0];
+  const uint32_t lane16 = 16u * (uint32_t)lane;
+  auto load_a = [&](int buf, int kc) {  // a row block's 2 KB per wave and turn
+#pragma unroll
+    for (int i = 0; i < (RB + 3) / 4; ++i) {
+      const int blk = w + 4 * i;
+      if (blk >= nv) continue;
+      const uint64_t src = uniform64((uint64_t)(Abase + ((int64_t)blk * nkc + kc) * 2048));
+      const uint32_t dst =
+          __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(buf * (RB * 2048) + blk * 2048));
+      fragment_to_lds<0>(src, dst, lane16);
+      fragment_to_lds<1024>(src, dst, lane16);
+    }
+  };
+  d4v acc[RB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i) acc[i] = d4v{0, 0, 0, 0};
+  auto step = [&](int kc, const d2v(&B)[2], d2v(&Bn)[2]) {
+    // what this wave issued in the last step has arrived, after the barrier the others'
+    // too, and nobody reads the buffer that the next loads overwrite
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    lds_barrier();
+    if (kc + 1 < nkc) {
+      load_a((kc + 1) & 1, kc + 1);
+      Bn[0] = ldg((const d2v *)(col + 16 * (kc + 1)));
+      Bn[1] = ldg((const d2v *)(col + 16 * (kc + 1) + 2));
+    }
+    const double *Ap = &As[kc & 1][lane];
+    double a[2][RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) a[0][i] = Ap[i * 256];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      if (ks < 3) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i) a[(ks + 1) & 1][i] = Ap[i * 256 + (ks + 1) * 64];
+      }
+#pragma unroll
+      for (int i = 0; i < RB; ++i) acc[i] = mfma_f64(a[ks & 1][i], B[ks >> 1][ks & 1], acc[i]);
+    }
+  };
+  d2v B0[2], B1[2];
+  load_a(0, 0);
+  B0[0] = B1[0] = ldg((const d2v *)col);
+  B0[1] = B1[1] = ldg((const d2v *)(col + 2));
+  for (int kc = 0; kc < nkc; kc += 2) {
+    step(kc, B0, B1);
+    if (kc + 1 < nkc) step(kc + 1, B1, B0);
+  }
+  if (!valid) return;
+  const int64_t cbase = ((int64_t)tsl * J.nrhs + r) * J.dpm + 16 * rb0 + (lane >> 4);
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    if (i >= nv) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t o = cbase + 16 * i + 4 * q;
+      double v = acc[i][q];
+      if constexpr (MODE == MODE_L2L) v += ldg(J.Cadd + o);
+      stg(J.C + o, v);
+      if (J.C32) stg(J.C32 + o, (float)v);
+    }
+  }
+}
+
 // ------------------------------------------------------------------ factored M2L
 // Second compression stage (Sec. 4.2): per offset o the r x r matrix C^delta is
 // the product Ut_o Vt_o of an r x s_o and an s_o x r factor, so a column's
@@ -2105,11 +2225,25 @@ void launch_gemm_rbt(const GemmJob *jobs, int n, int tiles, int64_t units, int g
                        tiles, units, G, GT, ws);
 }
 
+template <int MODE, int RB>
+void launch_tall(const GemmJob *jobs, int n, int grid, hipStream_t s) {
+  hipLaunchKernelGGL((k_gemm_tall<MODE, RB>), dim3(grid), dim3(256), 0, s, jobs, n);
+}
+// row blocks of a tall tile: the fewest idle ones, the taller on a tie
+int pick_tall(int nrb) {
+  int best = 9;
+  for (int h = 8; h >= 5; --h)
+    if ((nrb + h - 1) / h * h < (nrb + best - 1) / best * best) best = h;
+  return best;
+}
+
 // few: the launch may take the form for few columns (k_gemm_few).  It does when the tiles
 // leave compute units idle: fewer (tile, term) pairs than workgroups.
+// nrb: row blocks of the finest level's operators; more than 4 take the tall tiles (L2L and
+// the projections; below that a tile of 3 or 4 blocks and 128 columns is as good).
 template <int MODE>
 void launch_gemm_tab(const GemmJob *jobs, int n, int tiles, int64_t units, int rbt, int gmax,
-                     double *ws, size_t ws_len, bool few, hipStream_t s) {
+                     double *ws, size_t ws_len, bool few, int nrb, hipStream_t s) {
   if (n == 0 || tiles == 0 || units == 0) return;
   if (few && n <= 64 && units < gmax) {
     // at most this many items (a job's last tiles may hold fewer; the rest return)
@@ -2117,6 +2251,21 @@ void launch_gemm_tab(const GemmJob *jobs, int n, int tiles, int64_t units, int r
     const int waves = few_waves(MODE), grid = MODE == MODE_M2M ? items : (items + 3) / 4;
     hipLaunchKernelGGL(k_gemm_few<MODE>, dim3(grid), dim3(64 * waves), 0, s, jobs, n);
     return;
+  }
+  if constexpr (MODE != MODE_M2M) {
+    if (n <= 64 && nrb > 4) {
+      // at most this many 64-column tiles (the row tiles are no fewer at rbt <= 6 blocks
+      // than at 6 and more; at 5 at most twice as few): the rest return
+      const int cols = tiles * (gemm_cols(rbt) / 64);
+      switch (pick_tall(nrb)) {
+        case 9: launch_tall<MODE, 9>(jobs, n, cols, s); break;
+        case 8: launch_tall<MODE, 8>(jobs, n, cols, s); break;
+        case 7: launch_tall<MODE, 7>(jobs, n, cols, s); break;
+        case 6: launch_tall<MODE, 6>(jobs, n, cols, s); break;
+        default: launch_tall<MODE, 5>(jobs, n, 2 * cols, s); break;
+      }
+      return;
+    }
   }
   switch (rbt) {
     case 4: launch_gemm_rbt<MODE, 4>(jobs, n, tiles, units, gmax, ws, ws_len, s); break;
@@ -2130,13 +2279,13 @@ void launch_gemm_tab(const GemmJob *jobs, int n, int tiles, int64_t units, int r
 // pass (P.run_ws, P.run_ws_len)
 template <int MODE>
 void launch_gemm(Plan &P, int first, int n, int tiles, int64_t units, hipStream_t s,
-                 int rbt = 6) {
+                 int rbt, int nrb) {
   double *ws = P.run_ws ? P.run_ws : P.sk_ws;
   const size_t len = P.run_ws ? P.run_ws_len : stream_k_ws_len(P.sk_groups);
   // (mixed precision rounds the solved expansions to FP32, which would show an M2M sum in
   // another order)
   const bool few = MODE != MODE_M2M || P.cfg.precision == EIFMM_PREC_FP64;
-  launch_gemm_tab<MODE>(P.job_dev + first, n, tiles, units, rbt, P.sk_groups, ws, len, few, s);
+  launch_gemm_tab<MODE>(P.job_dev + first, n, tiles, units, rbt, P.sk_groups, ws, len, few, nrb, s);
 }
 
 void launch_gemm_fused(const FusedGemm &F, int mode, bool fp32, int gmax, double *ws,
@@ -2144,13 +2293,13 @@ void launch_gemm_fused(const FusedGemm &F, int mode, bool fp32, int gmax, double
   const size_t len = stream_k_ws_len(gmax);
   switch (mode) {
     case MODE_M2M:
-      launch_gemm_tab<MODE_M2M>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, false, s);
+      launch_gemm_tab<MODE_M2M>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, false, 0, s);
       break;
     case MODE_L2L:
-      launch_gemm_tab<MODE_L2L>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, true, s);
+      launch_gemm_tab<MODE_L2L>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, true, 0, s);
       break;
     case MODE_PROJ:
-      launch_gemm_tab<MODE_PROJ>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, true, s);
+      launch_gemm_tab<MODE_PROJ>(F.dev, F.n, F.tiles, F.units, F.rbt, gmax, ws, len, true, 0, s);
       break;
     default:
       if (fp32)
@@ -2342,7 +2491,7 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
     Timer tm(P, s, EIFMM_PH_M2M);
     for (int k = depth - 1; k >= 2; --k)
       launch_gemm<MODE_M2M>(P, P.jobs.m2m_first[k], P.jobs.m2m_n[k], P.jobs.m2m_tiles[k],
-                                    P.jobs.m2m_units[k], s, P.jobs.m2m_rbt[k]);
+                                    P.jobs.m2m_units[k], s, P.jobs.m2m_rbt[k], 0);
   }
   // step 3: What = Delta W = B^{-T} Gamma^{-1} W on uncompressed levels; on
   // compressed ones z = Gamma^{-1} W (the projection applies U^T B^{-T}), or
@@ -2377,7 +2526,7 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
   if (P.jobs.pre_n) {
     Timer tm(P, s, EIFMM_PH_PROJ);
     launch_gemm<MODE_PROJ>(P, P.jobs.pre_first, P.jobs.pre_n, P.jobs.pre_tiles,
-                                   P.jobs.pre_units, s, P.jobs.pre_rbt);
+                                   P.jobs.pre_units, s, P.jobs.pre_rbt, HL.rp / 16);
   }
   if (fork_late) hipEventRecord(P.ev_fork, s);
   {
@@ -2424,14 +2573,14 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
   if (P.jobs.post_n) {
     Timer tm(P, s, EIFMM_PH_PROJ);
     launch_gemm<MODE_PROJ>(P, P.jobs.post_first, P.jobs.post_n, P.jobs.post_tiles,
-                                   P.jobs.post_units, s, P.jobs.post_rbt);
+                                   P.jobs.post_units, s, P.jobs.post_rbt, HL.dpB / 16);
   }
   // step 5: l^2 = g^2, then L2L downwards
   {
     Timer tm(P, s, EIFMM_PH_L2L);
     for (int k = 3; k <= depth; ++k)
       launch_gemm<MODE_L2L>(P, P.jobs.l2l_first[k], P.jobs.l2l_n[k], P.jobs.l2l_tiles[k],
-                                    P.jobs.l2l_units[k], s, P.jobs.l2l_rbt[k]);
+                                    P.jobs.l2l_units[k], s, P.jobs.l2l_rbt[k], P.lh[k].dpB / 16);
   }
   // step 6: lhat = Delta^{J_0,I_0} l on the leaf level (Delta^T l with one EIM)
   {
