@@ -333,7 +333,7 @@ int setup_workspaces(eifmm_plan h, double *shared_ws) {
     P.sk_ws = shared_ws;
   else
     TRY(dalloc(&P.sk_ws, stream_k_ws_len(P.sk_groups), tr));
-  // the gathered GEMM's tail counter, at the end of the workspace, starts at zero
+  // the M2L's tail counter, at the end of the workspace, starts at zero
   if (!shared_ws &&
       hipMemset(P.sk_ws + stream_k_ws_len(P.sk_groups) - kCounterDoubles, 0,
                 kCounterDoubles * sizeof(double)) != hipSuccess)

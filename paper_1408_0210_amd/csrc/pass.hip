@@ -63,6 +63,18 @@ template <int KIND>
 struct KF {
   static constexpr bool singular = (KIND == EIFMM_K_LAPLACE || KIND == EIFMM_K_YUKAWA ||
                                      KIND == EIFMM_K_COSR || KIND == EIFMM_K_ADVDIFF);
+  // the library's exponential where it shows (what_rounded)
+  static constexpr bool exponential =
+      (KIND == EIFMM_K_YUKAWA || KIND == EIFMM_K_GAUSS || KIND == EIFMM_K_ADVDIFF);
+  __device__ static inline double eval_lib(double r2, double zx, double p) {
+    const double ri = KIND == EIFMM_K_GAUSS ? 0.0 : rsq_refined(r2);
+    if constexpr (KIND == EIFMM_K_YUKAWA)
+      return exp(-p * (r2 * ri)) * ri;
+    else if constexpr (KIND == EIFMM_K_GAUSS)
+      return exp(-r2 * p);
+    else
+      return exp(p * (zx - r2 * ri)) * ri;
+  }
   // k at z with r2 = |z|^2 and zx its first component (read by the kernel that
   // is not radial); p: Yukawa a, Gauss 1/h2, cos(w r)/r w, multiquadric c,
   // advection-diffusion a
@@ -492,6 +504,7 @@ __global__ __launch_bounds__(64) void k_p2p32(LeafDesc one, const LeafDesc *__re
 // (32 problems with four clusters each and d = 433 spent 4.5 ms on the workgroups of a
 // few leaves of 1e4 sources).  A leaf's first segment writes W, the others their sums
 // to w_ext (extra i of the leaves before it and of its own), which k_p2m_ext adds.
+// (Where the solved What is rounded to FP32, what_rounded, a leaf is one segment.)
 // Rows are taken in groups of 4 NT, thread t
 // owning rows m0 + t + NT u, u < 4, of group m0.  NT = 0: the launch's block size
 // (one right-hand side on leaves of many points: a whole number of waves
@@ -499,7 +512,7 @@ __global__ __launch_bounds__(64) void k_p2p32(LeafDesc one, const LeafDesc *__re
 // waits at the batch barriers for a wave with two); otherwise 256 threads
 // (several right-hand sides: their registers rule out 1024-thread blocks), or
 // one wave when d_p <= 64.
-template <int KIND, int RB, bool BATCH, int NT>
+template <int KIND, int RB, bool BATCH, int NT, bool LIB>
 __global__ __launch_bounds__(NT ? NT : 1024) void k_p2m(LeafDesc one,
                                                         const LeafDesc *__restrict__ many,
                                                         int nmany) {
@@ -523,8 +536,8 @@ __global__ __launch_bounds__(NT ? NT : 1024) void k_p2m(LeafDesc one,
   const double *__restrict__ xyz = D.xyz;
   const double *__restrict__ sig = D.sig;
   const uint32_t key = D.act[j];
-  const int a = D.ls[key] + kSegSources * seg;
-  const int b = RB == 1 ? min(D.se[key], a + kSegSources) : D.se[key];
+  const int a = D.ls[key] + D.seg_len * seg;
+  const int b = RB == 1 ? min(D.se[key], a + D.seg_len) : D.se[key];
   const double cx = D.lo0 + ((double)morton_axis(key, 0) + 0.5) * D.h;
   const double cy = D.lo1 + ((double)morton_axis(key, 1) + 0.5) * D.h;
   const double cz = D.lo2 + ((double)morton_axis(key, 2) + 0.5) * D.h;
@@ -565,7 +578,12 @@ __global__ __launch_bounds__(NT ? NT : 1024) void k_p2m(LeafDesc one,
             // are stored as zeros)
             if (u < nu && m0 + nt * u + (t & ~63) < d) {
               const double dx = xm[u] - px[q], dy = ym[u] - py[q], dz = zm[u] - pz[q];
-              const double kv = KF<KIND>::eval(dx * dx + dy * dy + dz * dz, dx, D.p);
+              const double r2 = dx * dx + dy * dy + dz * dz;
+              double kv;
+              if constexpr (LIB)
+                kv = KF<KIND>::eval_lib(r2, dx, D.p);
+              else
+                kv = KF<KIND>::eval(r2, dx, D.p);
 #pragma unroll
               for (int rr = 0; rr < RB; ++rr) acc[u][rr] += ps[q * RB + rr] * kv;
             }
@@ -2335,30 +2353,42 @@ void launch_p2p(bool mixed, int nrhs, int64_t nchunk, const LeafDesc &one, const
 // spends its time in the batch loop (1e6 clustered points at depth 5: P2M 2.95
 // -> 2.66 ms); on leaves of a few dozen points the 256-thread form is faster
 // (1e6 uniform points at depth 5: 0.21 against 0.25 ms)
-template <int KIND, bool BATCH>
-void launch_p2m(int nrhs, unsigned grid, int dpmax, const LeafDesc &one, const LeafDesc *many,
-                int nmany, hipStream_t s, bool crowded = false) {
+template <int KIND, bool BATCH, bool LIB>
+void launch_p2m_exp(int nrhs, unsigned grid, int dpmax, const LeafDesc &one, const LeafDesc *many,
+                int nmany, hipStream_t s, bool crowded) {
   if (grid == 0) return;
   if (dpmax <= 64) {  // one row per thread: a 64-lane workgroup wastes no lanes on small d
     if (nrhs == 1)
-      hipLaunchKernelGGL((k_p2m<KIND, 1, BATCH, 64>), dim3(grid), dim3(64), 0, s, one, many,
+      hipLaunchKernelGGL((k_p2m<KIND, 1, BATCH, 64, LIB>), dim3(grid), dim3(64), 0, s, one, many,
                          nmany);
     else
-      hipLaunchKernelGGL((k_p2m<KIND, 8, BATCH, 64>), dim3(grid), dim3(64), 0, s, one, many,
+      hipLaunchKernelGGL((k_p2m<KIND, 8, BATCH, 64, LIB>), dim3(grid), dim3(64), 0, s, one, many,
                          nmany);
   } else {
     if (nrhs == 1 && crowded) {
       const int nt = std::min(1024, (dpmax + 63) / 64 * 64);
-      hipLaunchKernelGGL((k_p2m<KIND, 1, BATCH, 0>), dim3(grid), dim3(nt), 0, s, one, many,
+      hipLaunchKernelGGL((k_p2m<KIND, 1, BATCH, 0, LIB>), dim3(grid), dim3(nt), 0, s, one, many,
                          nmany);
     } else if (nrhs == 1) {
-      hipLaunchKernelGGL((k_p2m<KIND, 1, BATCH, 256>), dim3(grid), dim3(256), 0, s, one, many,
+      hipLaunchKernelGGL((k_p2m<KIND, 1, BATCH, 256, LIB>), dim3(grid), dim3(256), 0, s, one, many,
                          nmany);
     } else {
-      hipLaunchKernelGGL((k_p2m<KIND, 8, BATCH, 256>), dim3(grid), dim3(256), 0, s, one, many,
+      hipLaunchKernelGGL((k_p2m<KIND, 8, BATCH, 256, LIB>), dim3(grid), dim3(256), 0, s, one, many,
                          nmany);
     }
   }
+}
+// lib_exp: P2M by the library's exponential (what_rounded)
+template <int KIND, bool BATCH>
+void launch_p2m(int nrhs, unsigned grid, int dpmax, const LeafDesc &one, const LeafDesc *many,
+                int nmany, hipStream_t s, bool lib_exp, bool crowded = false) {
+  if constexpr (KF<KIND>::exponential) {
+    if (lib_exp) {
+      launch_p2m_exp<KIND, BATCH, true>(nrhs, grid, dpmax, one, many, nmany, s, crowded);
+      return;
+    }
+  }
+  launch_p2m_exp<KIND, BATCH, false>(nrhs, grid, dpmax, one, many, nmany, s, crowded);
 }
 
 size_t l2p_shm(int nrhs, int dpmax) {
@@ -2394,6 +2424,7 @@ LeafDesc leaf_desc(const Plan &P, int nrhs) {
   D.seg_ptr = P.seg_ptr;
   D.seg_leaf = P.seg_leaf;
   D.w_ext = P.w_ext;
+  D.seg_len = seg_len(P);
   D.perm = P.idx;
   D.xyz = P.xyz;
   D.X = P.ld[depth].X;
@@ -2480,7 +2511,7 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
   if (nleafa > 0) {
     Timer tm(P, s, EIFMM_PH_P2M);
     launch_p2m<KIND, false>(nrhs, (unsigned)(nrhs == 1 ? P.nseg : nleafa), HL.dp, LD, nullptr, 0, s,
-                            n > 64 * (int64_t)nleafa);
+                            what_rounded(P), n > 64 * (int64_t)nleafa);
     if (nrhs == 1 && P.nseg > nleafa)
       hipLaunchKernelGGL((k_p2m_ext<false>), dim3((unsigned)P.nseg), dim3(256), 0, s, LD, nullptr,
                          0);
@@ -2938,7 +2969,7 @@ void run_group(const BatchExec &B, const BatchGroup &g, int phase, hipStream_t s
     launch_p2p<KIND, true>(B.mixed, 1, g.nchunk, none, many, g.count, s);
   else if (phase == 1)
   {
-    launch_p2m<KIND, true>(1, (unsigned)g.nseg, g.dpmax, none, many, g.count, s);
+    launch_p2m<KIND, true>(1, (unsigned)g.nseg, g.dpmax, none, many, g.count, s, B.mixed);
     if (g.nseg > g.nleaf)
       hipLaunchKernelGGL((k_p2m_ext<true>), dim3((unsigned)g.nseg), dim3(256), 0, s, none, many,
                          g.count);

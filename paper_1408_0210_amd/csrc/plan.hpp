@@ -167,6 +167,7 @@ struct LeafDesc {
   int64_t nsrc;             // input indices below nsrc are sources (sigma rows)
   int64_t toff;             // target t has input index toff + t (f row t)
   int nleaf, nrhs, d, dp, depth;
+  int seg_len;              // most sources of a P2M segment
   int dL, dpL;              // size of lhat (L2P)
   double lo0, lo1, lo2, h, p;  // domain corner, leaf width, device kernel parameter
   int64_t chunk_base, seg_base, pt_base;  // batch launches: first chunk / segment / element
@@ -419,6 +420,17 @@ constexpr int kM2l32Cols = 128;  // columns of its tiles
 int pick_m2l32(int nrb);
 void launch_m2l32(const GemmJob *jobs, int n, int tiles, int height, int dk, int cus, double *ws,
                   size_t ws_len, const int8_t *dvec, hipStream_t s);
+// Whether the pass rounds a solved What to FP32: mixed, some level not compressed.  The
+// solve's condition (1e7 and more) carries a last-bit difference of W into that rounding
+// (6e-9 of f on 777 points), so P2M keeps there the library's exponential and the one sum
+// per leaf.  A compressed level rounds U^T What, where it does not show.
+inline bool what_rounded(const Plan &P) {
+  if (P.cfg.precision != EIFMM_PREC_MIXED) return false;
+  for (int k = 2; k <= P.depth; ++k)
+    if (P.lh[k].r == 0) return true;
+  return false;
+}
+inline int seg_len(const Plan &P) { return what_rounded(P) ? 1 << 30 : kSegSources; }
 // FP64 M2L of small operators (m2l_small.hip)
 constexpr int kSmallM2l = 32;  // most rows and columns (padded): the tile in registers
 constexpr int kSmallM2lCols = 32;  // columns of a tile

@@ -221,6 +221,7 @@ struct ActLevels {
   int *chunk_ptr;               // first chunk of each active leaf, and their number
   int *chunk_leaf;              // active leaf of each chunk
   int *seg_ptr, *seg_leaf;      // the same for the P2M segments
+  int seg_len;  // most sources of a P2M segment
 };
 
 // 32-target chunks of leaf b
@@ -232,8 +233,8 @@ __device__ inline int leaf_chunks(const int *__restrict__ ls, const int *__restr
 // P2M segments of active leaf b (at least one, which clears the expansion of a leaf
 // without sources)
 __device__ inline int leaf_segments(const int *__restrict__ ls, const int *__restrict__ se,
-                                    int64_t b) {
-  return max(1, (se[b] - ls[b] + kSegSources - 1) / kSegSources);
+                                    int seg_len, int64_t b) {
+  return max(1, (se[b] - ls[b] + seg_len - 1) / seg_len);
 }
 
 __device__ inline int act_level(const ActLevels &L, int blk) {
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(256) void k_act_count(const int *__restrict__ ls, A
     atomicAdd(&c[b & 7], 1);
     if (q == L.leaf) {
       atomicAdd(&c[9], leaf_chunks(ls, L.tb, b));
-      atomicAdd(&c[10], leaf_segments(ls, L.se, b));
+      atomicAdd(&c[10], leaf_segments(ls, L.se, L.seg_len, b));
     }
   }
   __syncthreads();
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(256) void k_act_scatter(const int *__restrict__ ls,
   // chunks and segments of the boxes before this one in its wave
   const bool leaf = q == L.leaf;
   const int ch = leaf && a ? leaf_chunks(ls, L.tb, b) : 0;
-  const int sg = leaf && a ? leaf_segments(ls, L.se, b) : 0;
+  const int sg = leaf && a ? leaf_segments(ls, L.se, L.seg_len, b) : 0;
   int rch = 0, rsg = 0;
   if (leaf) {
     int v = ch, x = sg;
@@ -593,6 +594,7 @@ void build_active(Plan &P, int k0, int k1, hipStream_t s) {
   L.chunk_ptr = P.chunk_ptr;
   L.chunk_leaf = P.chunk_leaf;
   L.se = P.nt ? P.tgt_begin : P.leaf_start + 1;
+  L.seg_len = seg_len(P);
   L.seg_ptr = P.seg_ptr;
   L.seg_leaf = P.seg_leaf;
   int blk = 0;
