@@ -176,8 +176,12 @@ int setup_tables(eifmm_plan h) {
     if (mixed) {
       // four k-steps of a lane side by side: [..][16-k sub-chunk][lane][k-step]
       std::vector<float> f32(H.kfrag.size());
-      for (size_t q = 0; q < f32.size(); ++q)
-        f32[(q & ~(size_t)255) + (q & 63) * 4 + ((q >> 6) & 3)] = (float)H.kfrag[q];
+      for (size_t b = 0; b < f32.size(); b += 256) {
+        const double *in = H.kfrag.data() + b;
+        float *out = f32.data() + b;
+        for (int l = 0; l < 64; ++l)
+          for (int ks = 0; ks < 4; ++ks) out[4 * l + ks] = (float)in[64 * ks + l];
+      }
       TRY(upload(&D.kfrag32, f32.data(), f32.size(), tr));
     } else if (!P.shared_tables && H.sp2.empty() &&
                std::max(H.r > 0 ? H.rp : H.dpB, H.r > 0 ? H.rp : H.dp) <= kSmallM2l) {
