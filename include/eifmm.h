@@ -72,8 +72,11 @@ extern "C" {
                              not symmetric, so two EIMs per level (Sec. 3.1)     */
 
 /* precision of the pass */
-#define EIFMM_PREC_FP64 0  /* every step in FP64 (the M2L as exact products of the
-                              8-bit digits of its FP64 operands, summed in FP64)  */
+#define EIFMM_PREC_FP64 0  /* every step in FP64.  The M2L splits its FP64 operands
+                              into 8-bit digits, 56 bits below the largest entry
+                              of an operator's row or of a source column (64 where
+                              the kernel falls steeply across a pair of boxes),
+                              multiplies those exactly and sums in FP64            */
 #define EIFMM_PREC_MIXED 1 /* M2L on FP32 MFMA (FP32 products, each offset's
                               contribution added in FP64); P2P with FP64
                               coordinate differences, FP32 kernel values and

@@ -192,9 +192,10 @@ int setup_tables(eifmm_plan h) {
       TRY(upload(&D.ksmall, a.data(), a.size(), tr));
     } else if (P.shared_tables || H.sp2.empty()) {
       const int dm = H.r > 0 ? H.rp : H.dpB, dk = H.r > 0 ? H.rp : H.dp;
-      TRY(dalloc(&D.k8, (size_t)kNumOffsets * dm * digit_bytes(dk), tr));
-      TRY(dalloc(&D.rscale, (size_t)dm, tr));
-      TRY(upload_digit_operators(H.kfrag, dm, dk, D.k8, D.rscale));
+      D.nd = H.spread > kSteep ? kDigitsSteep : kDigits;
+      TRY(dalloc(&D.k8, (size_t)kNumOffsets * dm * digit_bytes(dk, D.nd), tr));
+      TRY(dalloc(&D.kexp, (size_t)kNumOffsets * dm, tr));
+      TRY(upload_digit_operators(H.kfrag, dm, dk, D.nd, D.k8, D.kexp));
     }
     std::vector<double>().swap(H.kfrag);
     for (int q = 0; q < 4; ++q) TRY(upload(&D.tri[q], H.tri[q].data(), H.tri[q].size(), tr));
@@ -313,7 +314,7 @@ int setup_workspaces(eifmm_plan h, double *shared_ws) {
     }
     if (!mixed && !D.ksmall && !uses_m2l2(P, k)) {
       const int dk = P.lh[k].r > 0 ? P.lh[k].rp : P.lh[k].dp;
-      TRY(dalloc(&D.w8, D.cap * (size_t)R * digit_bytes(dk), tr));
+      TRY(dalloc(&D.w8, D.cap * (size_t)R * digit_bytes(dk, D.nd), tr));
       TRY(dalloc(&D.wscale, D.cap * (size_t)R, tr));
     }
     // g and l have the second EIM's size (the first's with one EIM)
@@ -445,7 +446,8 @@ int shared_plan(eifmm_batch b, int p, int depth, eifmm_plan *out) {
     LevelDev &D = P.ld[k];
     const LevelDev &TD = T.ld[k];
     D.k8 = TD.k8;
-    D.rscale = TD.rscale;
+    D.kexp = TD.kexp;
+    D.nd = TD.nd;
     D.kfrag32 = TD.kfrag32;
     D.m2m = TD.m2m;
     D.l2l = TD.l2l;

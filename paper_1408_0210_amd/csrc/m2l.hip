@@ -3,14 +3,28 @@
 // C[:, col] = sum over the 189 offsets o of the column's child class of A_o b(o, col),
 // A_o the K^delta or C^delta of the level and b the source expansion at that offset.
 // The FP64 MFMA runs at 1/56 of the int8 one on gfx950 (75 TFLOP/s against 4.0 POP/s
-// measured), so every operand is split into 7 signed 8-bit digits (56 bits) and the
-// product is summed from the digit products, which are exact in 32-bit integers:
+// measured), so every operand is split into 7 signed 8-bit digits (56 bits; 8 on steep
+// levels, below) and the product is summed from the digit products, which are exact in
+// 32-bit integers:
 //   a = 2^ea sum_i da_i 256^-(i+1),  b = 2^eb sum_j db_j 256^-(j+1),  -128 <= d <= 127,
 //   sum_k a_k b_k = 2^(ea + eb - 16) sum_s 256^-s S_s,  S_s = sum_{i+j=s} sum_k da_ik db_jk.
-// One exponent per operator row (of the level) and one per source column.  Digit
+// One exponent per operator row of each offset and one per source column.  Digit
 // pairs with i + j > 6 lie below 2^-56 of the largest product and are left out: 28
 // products instead of 49.  The seven sums S_s of an offset are joined and scaled in
-// FP64 and added to an FP64 sum over the offsets.  Measured against an 80-bit
+// FP64 and added to an FP64 sum over the offsets.
+// An entry keeps 56 bits below the largest of its row or column, so an offset's product
+// is off by about d^1/2 2^-56 max_k |a_k| max_k |b_k|, where a chain of FP64 FMAs is off by
+// some 2^-53 of its partial sums.  (Were a row's exponent one for all offsets, a far
+// offset of a decaying kernel would keep what its entries have above 2^-56 of the nearest
+// ones': g in the corner opposite to the sources, level 2, would be off by 1e-5 of itself for
+// e^-30r/r and wholly for e^-60r/r, as against 6e-15 and 6e-13.)  Where the kernel falls so
+// far across one pair of boxes that this is more than the chain's error (kSteep), operands
+// have 8 digits (64 bits) and take 36 products, s to 7.  Error of single offsets' products
+// over that of the chain, offsets (2,0,0) to (3,3,3), level 2, tau 1e-5, against extended
+// precision, uncompressed: 1/r 0.2-0.3, cos(20 r)/r 0.3-0.5, e^-r^2 0.4-0.6, e^-8r/r
+// 0.5-0.8, e^-12r/r 0.8-1.5, e^(-r^2/0.1) 0.7-1.9, e^-30r/r 0.9-4.7, e^-60r/r 0.4-18 with
+// 7 digits, and 0.01-0.2 with 8 for all of these; compressed: 1/r 0.6-1.0, cos(20 r)/r
+// 1.3-1.9, e^(-r^2/0.01) 4.4-8.4, and 0.04-0.1 with 8.  Measured against an 80-bit
 // evaluation with the operators and sources of the pass (tau 1e-6, random boxes): 1/r
 // at rank 128 1.1e-15 relative against 5.3e-15 for the chain of FP64 FMAs, e^-r/r
 // 0.8e-15 / 3.9e-15, cos(20 r)/r 1.1e-15 / 6.9e-15, 1/r uncompressed (d = 287) 0.6e-15 /
@@ -34,12 +48,11 @@ namespace eifmm {
 namespace {
 
 typedef int i4v __attribute__((ext_vector_type(4)));
-constexpr int ND = kDigits;  // digits of an operand
 constexpr int kFrag = 1024;  // bytes of one 16 x 64 operand fragment (64 lanes x 16)
 
-// zeros, read in place of a missing source column (7 digits of 1024 elements) and,
+// zeros, read in place of a missing source column (digits of 1024 elements) and,
 // as a double, of its scale
-__device__ i4v g_digit_zero[7 * 1024 / 16];
+__device__ i4v g_digit_zero[kDigitsSteep * 1024 / 16];
 
 // the exponent e of the smallest power of two with m 2^-e <= 0.498, so that the top
 // digit of every |x| <= m stays within [-127, 127]; m > 0 and finite
@@ -50,6 +63,7 @@ __device__ inline int digit_exponent(double m) {
 }
 
 // the digits of x 2^-e, most significant first
+template <int ND>
 __device__ inline void digits_of(double x, int e, int8_t (&d)[ND]) {
   long long q = __double2ll_rn(ldexp(x, 8 * ND - e));
 #pragma unroll
@@ -59,59 +73,56 @@ __device__ inline void digits_of(double x, int e, int8_t (&d)[ND]) {
   }
 }
 
-// largest |entry| of each operator row over all offsets, as the bits of a double
-// (the table in FP64 fragment order, setup.cpp: lane l of a fragment holds row l % 16)
-__global__ __launch_bounds__(256) void k_op_rowmax(const double *__restrict__ frag, int nrb,
-                                                   int nks, unsigned long long *__restrict__ mx) {
-  const int rb = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// The operators' digit fragments, [offset][row block][64-k chunk][digit][lane][16 k],
+// lane l holding row l % 16 and k = 16 (l / 16) .. + 15 of the chunk, and the exponent of
+// each row of each offset, [offset][row]: value = 2^exponent * (source scale) *
+// sum_s 256^-s S_s.  frag is the table in FP64 fragment order (setup.cpp: lane l of a
+// fragment holds row l % 16).  One workgroup per (offset, row block).  A row holding an
+// infinity or a NaN gets the digit 1 everywhere and an exponent that makes its results
+// infinite.
+template <int ND>
+__global__ __launch_bounds__(256) void k_op_digits(const double *__restrict__ frag, int nrb, int nks,
+                                                   int nkc, int8_t *__restrict__ out,
+                                                   int *__restrict__ kexp) {
+  __shared__ double mx[4][16];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const double *F = frag + (size_t)blockIdx.x * nks * 64;
   double m = 0.0;
-  for (int o = blockIdx.y; o < kNumOffsets; o += gridDim.y)
-    for (int ks = w; ks < nks; ks += 4)
-      m = fmax(m, fabs(frag[(((size_t)o * nrb + rb) * nks + ks) * 64 + lane]));
+  bool bad = false;
+  for (int ks = w; ks < nks; ks += 4) {
+    const double x = fabs(F[(size_t)ks * 64 + lane]);
+    bad = bad || !(x < INFINITY);
+    m = fmax(m, x);
+  }
+  if (bad) m = INFINITY;
   m = fmax(m, __shfl_xor(m, 16));
   m = fmax(m, __shfl_xor(m, 32));
-  if (lane < 16) atomicMax(&mx[16 * rb + lane], (unsigned long long)__double_as_longlong(m));
-}
-
-// the operators' digit fragments: [offset][row block][64-k chunk][digit][lane][16 k],
-// lane l holding row l % 16 and k = 16 (l / 16) .. + 15 of the chunk; one block of 64
-// lanes per (offset, row block, chunk)
-__global__ __launch_bounds__(64) void k_op_digits(const double *__restrict__ frag, int nrb, int nks,
-                                                  int nkc,
-                                                  const unsigned long long *__restrict__ mx,
-                                                  int8_t *__restrict__ out) {
-  const int lane = threadIdx.x;
-  const int kc = blockIdx.x % nkc, rb = (blockIdx.x / nkc) % nrb, o = blockIdx.x / (nkc * nrb);
-  const double m = __longlong_as_double((long long)mx[16 * rb + (lane & 15)]);
-  const int e = m > 0.0 && m < INFINITY ? digit_exponent(m) : 0;
-  const int c16 = kc * 4 + (lane >> 4);  // 16-column chunk of the table
-  union {
-    int8_t b[16];
-    i4v v;
-  } dig[ND];
+  if (lane < 16) mx[w][lane] = m;
+  __syncthreads();
+  const int row = lane & 15;
+  m = fmax(fmax(mx[0][row], mx[1][row]), fmax(mx[2][row], mx[3][row]));
+  bad = !(m < INFINITY);
+  const int e = !bad && m > 0.0 ? digit_exponent(m) : 0;
+  if (threadIdx.x < 16) kexp[(size_t)blockIdx.x * 16 + row] = bad ? 1 << 20 : e - 16;
+  for (int kc = w; kc < nkc; kc += 4) {
+    const int c16 = kc * 4 + (lane >> 4);  // 16-column chunk of the table
+    union {
+      int8_t b[16];
+      i4v v;
+    } dig[ND];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    double x = 0.0;
-    if (4 * c16 < nks)
-      x = frag[(((size_t)o * nrb + rb) * nks + 4 * c16 + (k & 3)) * 64 + 16 * (k >> 2) +
-               (lane & 15)];
-    int8_t d[ND] = {0, 0, 0, 0, 0, 0, 0};
-    if (m < INFINITY) digits_of(x, e, d);
+    for (int k = 0; k < 16; ++k) {
+      double x = 0.0;
+      if (4 * c16 < nks) x = F[(size_t)(4 * c16 + (k & 3)) * 64 + 16 * (k >> 2) + row];
+      int8_t d[ND] = {1};
+      if (!bad) digits_of<ND>(x, e, d);
 #pragma unroll
-    for (int s = 0; s < ND; ++s) dig[s].b[k] = d[s];
+      for (int s = 0; s < ND; ++s) dig[s].b[k] = d[s];
+    }
+    int8_t *o = out + ((size_t)blockIdx.x * nkc + kc) * (ND * kFrag) + 16 * lane;
+#pragma unroll
+    for (int s = 0; s < ND; ++s) *(i4v *)(o + s * kFrag) = dig[s].v;
   }
-#pragma unroll
-  for (int s = 0; s < ND; ++s)
-    *(i4v *)(out + ((size_t)blockIdx.x * ND + s) * kFrag + 16 * lane) = dig[s].v;
-}
-
-// scale of each operator row: value = scale * (source scale) * sum_s 256^-s S_s
-__global__ void k_op_scale(const unsigned long long *__restrict__ mx, int rows,
-                           double *__restrict__ scale) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
-  const double m = __longlong_as_double((long long)mx[r]);
-  scale[r] = !(m < INFINITY) ? (double)INFINITY : m > 0.0 ? ldexp(1.0, digit_exponent(m) - 16) : 0.0;
 }
 
 // Source columns into digits: 16 lanes per column, 4 consecutive k per lane and
@@ -120,7 +131,8 @@ __global__ void k_op_scale(const unsigned long long *__restrict__ mx, int rows,
 // are those of the column with its first entry that is not zero made positive, and the
 // scale carries the sign: the digits of x and -x differ otherwise (a digit of -128 has
 // no counterpart), and a pass of -sigma would not be exactly the negative one.
-// Bound by memory (8 bytes read and 7 written per element).
+// Bound by memory (8 bytes read and 7 or 8 written per element).
+template <int ND>
 __device__ inline void digit_column(const DigitDesc &D, int col) {
   const int li = threadIdx.x & 15;
   const double *in = D.in + (int64_t)col * D.ld;
@@ -159,11 +171,11 @@ __device__ inline void digit_column(const DigitDesc &D, int col) {
       v[2] = b.x;
       v[3] = b.y;
     }
-    uint32_t pk[ND] = {0, 0, 0, 0, 0, 0, 0};
+    uint32_t pk[ND] = {};
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       int8_t d[ND];
-      digits_of(neg ? -v[q] : v[q], e, d);
+      digits_of<ND>(neg ? -v[q] : v[q], e, d);
 #pragma unroll
       for (int s = 0; s < ND; ++s) pk[s] |= (uint32_t)(uint8_t)d[s] << (8 * q);
     }
@@ -172,6 +184,13 @@ __device__ inline void digit_column(const DigitDesc &D, int col) {
     for (int s = 0; s < ND; ++s) stg((uint32_t *)(o + 64 * s), pk[s]);
   }
   if (li == 0) stg(D.scale + col, bad ? (double)NAN : use ? ldexp(neg ? -1.0 : 1.0, e) : 0.0);
+}
+
+__device__ inline void digit_column_of(const DigitDesc &D, int col) {
+  if (D.nd == kDigitsSteep)
+    digit_column<kDigitsSteep>(D, col);
+  else
+    digit_column<kDigits>(D, col);
 }
 
 struct DigitArgs {
@@ -186,7 +205,7 @@ __global__ __launch_bounds__(256) void k_digits(DigitArgs A) {
     if ((int)blockIdx.x >= A.lv[q].blk_start) li = q;
   const DigitDesc &D = A.lv[li];
   const int col = ((int)blockIdx.x - D.blk_start) * kDigitCols + (int)(threadIdx.x >> 4);
-  if (col < D.ncols) digit_column(D, col);
+  if (col < D.ncols) digit_column_of(D, col);
 }
 
 // a batch: every (problem, level), descriptors in device memory
@@ -195,23 +214,25 @@ __global__ __launch_bounds__(256) void k_digits_list(const DigitDesc *__restrict
       find_last_le(n, blockIdx.x, [&](int m) { return (int64_t)L[m].blk_start; });
   const DigitDesc D = L[li];
   const int col = ((int)blockIdx.x - D.blk_start) * kDigitCols + (int)(threadIdx.x >> 4);
-  if (col < D.ncols) digit_column(D, col);
+  if (col < D.ncols) digit_column_of(D, col);
 }
 
 // Terms [term0, term1) of one tile of 16 RB RG rows and 128 / RG columns: the result,
 // or a piece (part).  8 waves, RG groups of rows by 8 / RG groups of 16 columns; a wave
-// holds RB row blocks of its 16 columns.  The operator fragments of a 64-k chunk go
+// holds RB row blocks of its 16 columns; operands of ND digits.  The operator fragments of a 64-k chunk go
 // to LDS one chunk ahead, in two buffers; the source digits (16 columns and 64 k are
 // one fragment per digit) one chunk ahead too, in one buffer that every wave copies
 // to registers at the start of the chunk.  Both are direct loads, which need no
-// registers: the digit sums and the FP64 sums take 144 of a lane's 256.  The slots of
-// the sources are read one term ahead.  A step waits for all of them at its start, a
+// registers: the digit sums and the FP64 sums take 144 of a lane's 256.  The rows'
+// exponents of a term go to LDS with its first chunk, in three buffers: a wave may still
+// join the sums of the term before the last one written.  The slots of the sources are
+// read one term ahead.  A step waits for all of them at its start, a
 // whole chunk of products (RB x 28 MFMAs per wave) after they were issued.
-template <int RB, int RG>
+template <int ND, int RB, int RG>
 __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, int term1,
                                  double *__restrict__ part, const int8_t *__restrict__ dvec,
-                                 int8_t (*As)[RB * RG * ND * kFrag], int8_t *Bs, TileCol *cst,
-                                 int *sdel) {
+                                 int8_t (*As)[RB * RG * ND * kFrag], int8_t *Bs,
+                                 int (*Es)[16 * RB * RG], TileCol *cst, int *sdel) {
   constexpr int CG = 8 / RG, H = RB * RG, COLS = 16 * CG;
   const int t = threadIdx.x, lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -248,6 +269,8 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
     // the last one loaded (q)
     double scn = 0.0, scq = 0.0;
     bool haven = false, haveq = false;
+    int en = 0;          // a row's exponent of the term aimed at (the first 16 H threads)
+    int ew = 0, er = 2;  // buffer of exponents: the next one to write, the current term's
     int fq = 0, fk = 0;  // next chunk to load: term, chunk
     // the addresses of the next chunk to load, if it starts a term; runs a step ahead of
     // that load, behind the products, since its chain of reads is long
@@ -259,13 +282,15 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
       srcp = (sl < 0 ? (const int8_t *)g_digit_zero : (const int8_t *)c.B + col * colbytes) + 16 * (lane >> 4);
       scn = ldg(sl < 0 ? (const double *)g_digit_zero : c.bs + col);
       haven = __ballot(sl >= 0) != 0;
-      At = Abase + (int64_t)(__builtin_amdgcn_readfirstlane(sdel[fq]) >> 9) * J.a_stride;
+      const int o = __builtin_amdgcn_readfirstlane(sdel[fq]) >> 9;
+      At = Abase + (int64_t)o * J.a_stride;
+      if (64 * w < 16 * H) en = ldg(J.kexp + (int64_t)o * J.dpm + min(16 * rb0 + t, J.dpm - 1));
       slotn = ldg(source_slot(J, c, fq + 1, nt, sdel));
     };
     // The loads of the next chunk, operators to LDS buffer `buf` and sources to Bs, are
     // issued one at a time between the products: a burst of them would hold up the
-    // wave.  A column group's seven digits are shared out to its RG waves; a row block's
-    // seven operator fragments make two pieces (4 and 3), dealt to the waves.
+    // wave.  A column group's digits are shared out to its RG waves; a row block's
+    // operator fragments make two pieces (4 and the rest), dealt to the waves.
     constexpr int NB = RG == 2 ? 4 : ND, NP = (2 * H + 7) / 8, NL = NB + 4 * NP;
     static_assert(NL <= ND * RB, "a load per fragment of the products");
     bool live = false;
@@ -279,6 +304,8 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
       if (fk == 0) {
         scq = scn;
         haveq = haven;
+        if (t < 16 * H) Es[ew][t] = en;
+        ew = ew == 2 ? 0 : ew + 1;
       }
       sp = srcp + fk * (64 * ND) + (RG == 2 ? rg * 256 : 0);
 #pragma unroll
@@ -298,15 +325,15 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
       constexpr int n = decltype(N)::value;
       if (!live) return;
       if constexpr (n < NB) {
-        if (RG == 1 || n < 3 || rg == 0) column_to_lds<64 * n>(sp, ldsw + n * kFrag);
+        if (RG == 1 || n < ND - 4 || rg == 0) column_to_lds<64 * n>(sp, ldsw + n * kFrag);
       } else if constexpr (n < NL) {
         constexpr int i = (n - NB) / 4, j = (n - NB) % 4;
-        if ((w >> 1) + 4 * i < nv && (j < 3 || half == 0))
+        if ((w >> 1) + 4 * i < nv && (j < ND - 4 || half == 0))
           fragment_to_lds<j * kFrag>(ap[i], lp[i], lane16);
       }
     };
     auto fetch_all = [&](auto N0) { for_each_from<decltype(N0)::value, NL>(fetch_one); };
-    // The 28 digit products of each of the wave's row blocks [i0, i1) in one chunk, the
+    // The 28 (36) digit products of each of the wave's row blocks [i0, i1) in one chunk, the
     // operator fragments read three ahead of their products (blocks past the tile's
     // rows multiply what the buffer holds; their sums are not stored).  first: the
     // term's first chunk, whose sums start at zero.
@@ -326,7 +353,7 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
               __builtin_amdgcn_mfma_i32_16x16x64_i8(a[f % AHEAD], b[db], c, 0, 0, 0);
         }
         if (f + AHEAD < NF) a[f % AHEAD] = *(const i4v *)(Ap + (f + AHEAD) * kFrag);
-        constexpr int SP = 2 * NL <= NF ? 2 : 1;
+        constexpr int SP = 2 * NL + 4 <= NF ? 2 : 1;  // (the last loads early enough)
         if constexpr (f % SP == 0) fetch_one(std::integral_constant<int, f / SP>{});
         __builtin_amdgcn_sched_barrier(0);
       };
@@ -336,12 +363,13 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
     auto fold = [&](double scf) {
 #pragma unroll
       for (int i = 0; i < RB; ++i) {
+        const i4v ex = *(const i4v *)&Es[er][16 * (rg * RB + i) + 4 * (lane >> 4)];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           double v = (double)acc[i][ND - 1][q];
 #pragma unroll
           for (int s = ND - 2; s >= 0; --s) v = fma(v, 1.0 / 256.0, (double)acc[i][s][q]);
-          sum[i][q] = fma(v, scf, sum[i][q]);
+          sum[i][q] = fma(ldexp(v, ex[q]), scf, sum[i][q]);
         }
       }
     };
@@ -375,6 +403,7 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
       const bool fst = kc == 0;
       if (fst) {
         sc = scq;
+        er = er == 2 ? 0 : er + 1;
         have = haveq && nw > 0;
       }
       fetch_begin(buf ^ 1);
@@ -419,8 +448,8 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
 #pragma unroll
       for (int q = 0; q < 4; q += 2) {
         d2v v;
-        v.x = sum[i][q] * ldg(J.rscale + 16 * rb0 + rt + q);
-        v.y = sum[i][q + 1] * ldg(J.rscale + 16 * rb0 + rt + q + 1);
+        v.x = sum[i][q];
+        v.y = sum[i][q + 1];
         stg((d2v *)(out + rt + q), v);
       }
     }
@@ -432,7 +461,7 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
 // contiguous); the others are cut into `parts` term ranges each, taken in order from
 // a counter and summed by k_m2l_sum, so that workgroups whose tiles dropped terms
 // take more of them.  A workgroup that reads a value outside [0, items) stops.
-template <int RB, int RG>
+template <int ND, int RB, int RG>
 __global__ __launch_bounds__(512, 2) void k_m2l8(const GemmJob *__restrict__ jobs, int njobs,
                                                  int G, int full, int items, int parts,
                                                  double *__restrict__ ws,
@@ -441,6 +470,7 @@ __global__ __launch_bounds__(512, 2) void k_m2l8(const GemmJob *__restrict__ job
   constexpr int H = RB * RG, TILE = H * 16 * (128 / RG);
   __shared__ __align__(16) int8_t As[2][H * ND * kFrag];
   __shared__ __align__(16) int8_t Bs[(8 / RG) * ND * kFrag];
+  __shared__ __align__(16) int Es[3][16 * H];
   __shared__ TileCol cst[128 / RG];
   __shared__ int sdel[189];
   __shared__ int item_sh;
@@ -448,7 +478,7 @@ __global__ __launch_bounds__(512, 2) void k_m2l8(const GemmJob *__restrict__ job
   const int gx = (G % 8 == 0) ? (g % 8) * (G / 8) + g / 8 : g;
   for (int tile = gx; tile < full; tile += G) {
     const GemmJob J = jobs[job_of_tile(jobs, njobs, tile)];
-    m2l8_tile<RB, RG>(J, tile - J.tiles_start, 0, J.nterms, nullptr, dvec, As, Bs, cst, sdel);
+    m2l8_tile<ND, RB, RG>(J, tile - J.tiles_start, 0, J.nterms, nullptr, dvec, As, Bs, Es, cst, sdel);
   }
   if (items <= 0) return;
   for (;;) {
@@ -459,19 +489,19 @@ __global__ __launch_bounds__(512, 2) void k_m2l8(const GemmJob *__restrict__ job
     if ((unsigned)item >= (unsigned)items) return;
     const int tile = full + item / parts, q = item % parts;
     const GemmJob J = jobs[job_of_tile(jobs, njobs, tile)];
-    m2l8_tile<RB, RG>(J, tile - J.tiles_start, q * J.nterms / parts, (q + 1) * J.nterms / parts,
-                      ws + (size_t)item * TILE, dvec, As, Bs, cst, sdel);
+    m2l8_tile<ND, RB, RG>(J, tile - J.tiles_start, q * J.nterms / parts, (q + 1) * J.nterms / parts,
+                          ws + (size_t)item * TILE, dvec, As, Bs, Es, cst, sdel);
   }
 }
 
-template <int RB, int RG>
+template <int ND, int RB, int RG>
 void launch(const GemmJob *jobs, int n, int tiles, int cus, double *ws, size_t ws_len,
             const int8_t *dvec, hipStream_t s) {
   constexpr int H = RB * RG;
   // one workgroup per CU (its operator buffers take most of the LDS)
   const TileSplit T = split_tiles(tiles, cus, (size_t)H * 16 * (128 / RG), ws_len);
   int *ctr = (int *)(ws + ws_len - kCounterDoubles);
-  hipLaunchKernelGGL((k_m2l8<RB, RG>), dim3(T.grid), dim3(512), 0, s, jobs, n, T.grid, T.full,
+  hipLaunchKernelGGL((k_m2l8<ND, RB, RG>), dim3(T.grid), dim3(512), 0, s, jobs, n, T.grid, T.full,
                      T.rest * T.parts, T.parts, ws, dvec, ctr);
   if (T.rest > 0)
     hipLaunchKernelGGL(k_m2l_sum, dim3(T.rest * kSumSplit), dim3(256), 0, s, jobs, n, tiles, T.full,
@@ -481,10 +511,13 @@ void launch(const GemmJob *jobs, int n, int tiles, int cus, double *ws, size_t w
 }  // namespace
 
 // The tile height that leaves the fewest idle row blocks, the taller one on a tie.
-// 8 and 6 blocks are 64 columns wide, the lower ones 128.
-int pick_m2l8(int nrb) {
+// 8 and 6 blocks are 64 columns wide, the lower ones 128.  Eight digits leave LDS for
+// at most 6; there 4 take 2.97 ms where 3 take 3.70 and 6 (20 % idle) 3.71 (32 problems,
+// half of them e^(-r^2 / 0.01), 20 row blocks), and 2 serve operators of no more.
+int pick_m2l8(int nrb, int nd) {
   int best = 8, waste = 1 << 30;
   for (int h : {8, 6, 4, 3, 2}) {
+    if (nd == kDigitsSteep && (h == 8 || h == 3 || (h == 2 && nrb > 2))) continue;
     const int w = (nrb + h - 1) / h * h - nrb;
     if (w < waste) {
       waste = w;
@@ -494,15 +527,25 @@ int pick_m2l8(int nrb) {
   return best;
 }
 
-void launch_m2l8(const GemmJob *jobs, int n, int tiles, int height, int cus, double *ws,
+void launch_m2l8(const GemmJob *jobs, int n, int tiles, int height, int nd, int cus, double *ws,
                  size_t ws_len, const int8_t *dvec, hipStream_t s) {
   if (n == 0 || tiles == 0) return;
+  if (nd == kDigitsSteep) {
+    constexpr int N = kDigitsSteep;
+    switch (height) {
+      case 6: launch<N, 3, 2>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+      case 4: launch<N, 4, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+      default: launch<N, 2, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+    }
+    return;
+  }
+  constexpr int N = kDigits;
   switch (height) {
-    case 8: launch<4, 2>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
-    case 6: launch<3, 2>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
-    case 4: launch<4, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
-    case 3: launch<3, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
-    default: launch<2, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+    case 8: launch<N, 4, 2>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+    case 6: launch<N, 3, 2>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+    case 4: launch<N, 4, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+    case 3: launch<N, 3, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+    default: launch<N, 2, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
   }
 }
 
@@ -521,29 +564,23 @@ void launch_digits_list(const DigitDesc *dev, int n, int blocks, hipStream_t s) 
   hipLaunchKernelGGL(k_digits_list, dim3(blocks), dim3(256), 0, s, dev, n);
 }
 
-// The digit fragments and row scales of one level's M2L operators (rows x cols, both
-// multiples of 16) from their FP64 fragments on the host.
-int upload_digit_operators(const std::vector<double> &frag, int rows, int cols, int8_t *dig,
-                           double *scale) {
+// The digit fragments of one level's M2L operators (rows x cols, both multiples of 16) and
+// the exponents of their rows, from their FP64 fragments on the host.
+int upload_digit_operators(const std::vector<double> &frag, int rows, int cols, int nd,
+                           int8_t *dig, int *kexp) {
   const int nrb = rows / 16, nks = cols / 4, nkc = digit_kp(cols) / 64;
   double *tab = nullptr;
-  unsigned long long *mx = nullptr;
   hipError_t e = hipMalloc(&tab, sizeof(double) * std::max<size_t>(frag.size(), 1));
-  if (e == hipSuccess) e = hipMalloc(&mx, sizeof(unsigned long long) * rows);
   if (e == hipSuccess)
     e = hipMemcpy(tab, frag.data(), sizeof(double) * frag.size(), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemset(mx, 0, sizeof(unsigned long long) * rows);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_op_rowmax, dim3(nrb, 32), dim3(256), 0, nullptr, tab, nrb, nks, mx);
-    hipLaunchKernelGGL(k_op_digits, dim3(kNumOffsets * nrb * nkc), dim3(64), 0, nullptr, tab, nrb,
-                       nks, nkc, mx, dig);
-    hipLaunchKernelGGL(k_op_scale, dim3((rows + 255) / 256), dim3(256), 0, nullptr, mx, rows,
-                       scale);
+    hipLaunchKernelGGL(nd == kDigitsSteep ? k_op_digits<kDigitsSteep> : k_op_digits<kDigits>,
+                       dim3(kNumOffsets * nrb), dim3(256), 0, nullptr, tab, nrb, nks, nkc, dig,
+                       kexp);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipDeviceSynchronize();
   hipFree(tab);
-  hipFree(mx);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return e == hipErrorOutOfMemory ? EIFMM_ENOMEM : EIFMM_EHIP;

@@ -20,7 +20,6 @@ namespace {
 
 typedef int i4v __attribute__((ext_vector_type(4)));
 typedef float f4v __attribute__((ext_vector_type(4)));
-constexpr int ND = kDigits;
 constexpr int kFrag = 1024;   // bytes of an operand fragment: 64 lanes x 16
 constexpr int kFewCols = 32;  // most targets of an offset (delta = 2 along one axis)
 
@@ -28,7 +27,8 @@ struct FewArgs {
   const void *A;            // operators: FP32 fragments, or digits
   const int *slot;          // slot map of level 2
   const void *B;            // source columns: FP32, or digits
-  const double *bscale, *rscale;
+  const double *bscale;     // digits: scale of each source column,
+  const int *kexp;          // exponent of each row of each offset
   void *prod;               // [316][32][dm]: FP32 or FP64
   unsigned long long *mask; // [316] targets of each offset
   double *C;                // result [slot][dm]
@@ -36,7 +36,8 @@ struct FewArgs {
   int dm, dk;               // rows, columns (FP32: padded to 16, digits: to 64)
 };
 
-template <bool DIGITS>
+// ND: digits per operand, 0 for FP32
+template <int ND>
 __global__ __launch_bounds__(256) void k_few_products(FewArgs F, const int8_t *__restrict__ dvec) {
   __shared__ int tgt[64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -61,7 +62,7 @@ __global__ __launch_bounds__(256) void k_few_products(FewArgs F, const int8_t *_
   // (a column past the last reads the last's source; its result is not stored)
   const int s0 = tgt[min(c0, n - 1)], s1 = tgt[min(c1, n - 1)];
   const bool two = n > 16;
-  if constexpr (DIGITS) {
+  if constexpr (ND > 0) {
     const int nkc = F.dk >> 6;
     const int64_t cb = (int64_t)F.dk * ND;
     const int8_t *b0 = (const int8_t *)F.B + s0 * cb + 16 * (lane >> 4);
@@ -103,12 +104,13 @@ __global__ __launch_bounds__(256) void k_few_products(FewArgs F, const int8_t *_
       if (c >= n) continue;
       const double sc = F.bscale[sl];
       double *P = (double *)F.prod + ((int64_t)o * kFewCols + c) * F.dm + row;
+      const int *ex = F.kexp + (int64_t)o * F.dm + row;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         double v = (double)acc[j][ND - 1][q];
 #pragma unroll
         for (int s = ND - 2; s >= 0; --s) v = fma(v, 1.0 / 256.0, (double)acc[j][s][q]);
-        P[q] = v * sc;  // (the row's scale with the sum)
+        P[q] = ldexp(v, ldg(ex + q)) * sc;
       }
     }
   } else {
@@ -175,7 +177,6 @@ __global__ __launch_bounds__(256) void k_few_sum(FewArgs F, const int8_t *__rest
   __syncthreads();
   if (w == 0 && ok) {
     v = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
-    if (F.rscale) v *= ldg(F.rscale + row);
     F.C[(int64_t)ts * F.dm + row] = v;
   }
 }
@@ -194,7 +195,7 @@ void launch_m2l_few(const LevelDev &D, bool mixed, const void *B, int dm, int dk
   F.slot = D.slot;
   F.B = B;
   F.bscale = D.wscale;
-  F.rscale = mixed ? nullptr : D.rscale;
+  F.kexp = D.kexp;
   F.mask = (unsigned long long *)ws;
   F.prod = F.mask + kNumOffsets;
   F.C = C;
@@ -203,10 +204,13 @@ void launch_m2l_few(const LevelDev &D, bool mixed, const void *B, int dm, int dk
   F.dk = mixed ? dk : digit_kp(dk);
   const dim3 gp(kNumOffsets, (dm / 16 + 3) / 4), gs(64, (dm + 63) / 64);
   if (mixed) {
-    hipLaunchKernelGGL(k_few_products<false>, gp, dim3(256), 0, s, F, dvec);
+    hipLaunchKernelGGL(k_few_products<0>, gp, dim3(256), 0, s, F, dvec);
     hipLaunchKernelGGL(k_few_sum<float>, gs, dim3(256), 0, s, F, dvec);
   } else {
-    hipLaunchKernelGGL(k_few_products<true>, gp, dim3(256), 0, s, F, dvec);
+    if (D.nd == kDigitsSteep)
+      hipLaunchKernelGGL(k_few_products<kDigitsSteep>, gp, dim3(256), 0, s, F, dvec);
+    else
+      hipLaunchKernelGGL(k_few_products<kDigits>, gp, dim3(256), 0, s, F, dvec);
     hipLaunchKernelGGL(k_few_sum<double>, gs, dim3(256), 0, s, F, dvec);
   }
 }

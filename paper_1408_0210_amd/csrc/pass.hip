@@ -1962,11 +1962,15 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
     int tiles = 0;
     jt.m2l_first = (int)h.size();
     int kf = depth;  // the tile height serves the finest level of this launch
-    while (kf > 2 && P.ld[kf].ksmall) --kf;
-    const LevelHost &F = P.lh[kf];
-    jt.m2l_rbt = (mixed ? pick_m2l32 : pick_m2l8)((F.r ? F.rp : F.dpB) / 16);
-    std::vector<GemmJob> small_jobs;  // levels of small operators: a launch of their own
-    int small_tiles = 0;
+    while (kf > 2 && (P.ld[kf].ksmall || P.ld[kf].nd == kDigitsSteep)) --kf;
+    int ks = depth;  // (the same of the steep levels)
+    while (ks > 2 && P.ld[ks].nd != kDigitsSteep) --ks;
+    auto row_blocks = [&](int k) { return (P.lh[k].r ? P.lh[k].rp : P.lh[k].dpB) / 16; };
+    jt.m2l_rbt = mixed ? pick_m2l32(row_blocks(kf)) : pick_m2l8(row_blocks(kf), kDigits);
+    jt.steep_rbt = pick_m2l8(row_blocks(ks), kDigitsSteep);
+    // levels of small operators and steep levels: launches of their own
+    std::vector<GemmJob> small_jobs, steep_jobs;
+    int small_tiles = 0, steep_tiles = 0;
     for (int k = depth; k >= 2; --k) {
       if (uses_m2l2(P, k)) continue;  // the factored M2L below
       if (m2l_by_offset(P, k, nrhs)) continue;
@@ -1993,8 +1997,8 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
           J.A = P.ld[k].k8;
           J.Bsrc = P.ld[k].w8;
           J.bscale = P.ld[k].wscale;
-          J.rscale = P.ld[k].rscale;
-          J.a_stride = (int64_t)dm * dk * kDigits;
+          J.kexp = P.ld[k].kexp;
+          J.a_stride = (int64_t)dm * dk * P.ld[k].nd;
         }
         J.C = cz ? P.ld[k].gp : P.ld[k].g;
         J.tgt = (P.ld[k].ord ? P.ld[k].ord : P.ld[k].cls) + P.cls_off[k][c];
@@ -2014,6 +2018,11 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
           small_jobs.push_back(J);
           continue;
         }
+        if (P.ld[k].nd == kDigitsSteep) {
+          finish_job(J, steep_tiles, jt.steep_rbt, m2l8_cols(jt.steep_rbt));
+          steep_jobs.push_back(J);
+          continue;
+        }
         finish_job(J, tiles, jt.m2l_rbt, mixed ? kM2l32Cols : m2l8_cols(jt.m2l_rbt));
         h.push_back(J);
       }
@@ -2026,6 +2035,13 @@ int build_jobs(Plan &P, int nrhs, hipStream_t s) {
     for (int j = jt.m2l_first; j < jt.m2l_first + jt.m2l_n; ++j)
       fx += 2.0 * (double)h[j].nrowtiles * 16 * jt.m2l_rbt * h[j].dpk * (double)h[j].ntgt *
             h[j].nrhs * h[j].nterms;
+    jt.steep_first = (int)h.size();
+    jt.steep_n = (int)steep_jobs.size();
+    jt.steep_tiles = steep_tiles;
+    for (const GemmJob &J : steep_jobs) {
+      fx += 2.0 * (double)J.nrowtiles * 16 * jt.steep_rbt * J.dpk * (double)J.ntgt * J.nrhs * J.nterms;
+      h.push_back(J);
+    }
     jt.small_first = (int)h.size();
     jt.small_n = (int)small_jobs.size();
     jt.small_grid = 0;
@@ -2323,7 +2339,7 @@ void launch_gemm_fused(const FusedGemm &F, int mode, bool fp32, int gmax, double
       if (fp32)
         launch_m2l32(F.dev, F.n, F.tiles, F.rbt, F.dk, gmax / 2, ws, len, dvec, s);
       else
-        launch_m2l8(F.dev, F.n, F.tiles, F.rbt, gmax / 2, ws, len, dvec, s);
+        launch_m2l8(F.dev, F.n, F.tiles, F.rbt, F.nd, gmax / 2, ws, len, dvec, s);
   }
 }
 
@@ -2461,6 +2477,7 @@ DigitDesc digit_desc(const Plan &P, int k, int nrhs, int blk_start) {
   D.ncols = (int)(P.nact[k] * nrhs);
   D.ld = cz ? P.lh[k].rp : P.lh[k].dp;
   D.kp = digit_kp(D.ld);
+  D.nd = P.ld[k].nd;
   D.blk_start = blk_start;
   return D;
 }
@@ -2568,7 +2585,7 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
     if (mixed)
       launch_m2l32(P.job_dev + P.jobs.m2l_first, P.jobs.m2l_n, P.jobs.m2l_tiles, P.jobs.m2l_rbt,
                    HL.r > 0 ? HL.rp : HL.dp, P.sk_groups / 2, ws, ws_len, P.dvec, s);
-    else if (P.jobs.m2l_n || few) {
+    else if (P.jobs.m2l_n || P.jobs.steep_n || few) {
       DigitDesc dd[kMaxLevels];
       int nd = 0, blk = 0;
       for (int k = depth; k >= 2; --k) {
@@ -2578,7 +2595,9 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
       }
       launch_digits(dd, nd, blk, s);
       launch_m2l8(P.job_dev + P.jobs.m2l_first, P.jobs.m2l_n, P.jobs.m2l_tiles, P.jobs.m2l_rbt,
-                  P.sk_groups / 2, ws, ws_len, P.dvec, s);
+                  kDigits, P.sk_groups / 2, ws, ws_len, P.dvec, s);
+      launch_m2l8(P.job_dev + P.jobs.steep_first, P.jobs.steep_n, P.jobs.steep_tiles,
+                  P.jobs.steep_rbt, kDigitsSteep, P.sk_groups / 2, ws, ws_len, P.dvec, s);
     }
     launch_m2l_small(P.job_dev + P.jobs.small_first, P.jobs.small_n, P.jobs.small_grid, P.dvec, s);
     if (few) {
@@ -2860,9 +2879,11 @@ int fuse_jobs(FusedGemm &F, const std::vector<Plan *> &plans,
 
 // Packed M2L: one job per (operator set, level, child class) whose columns are
 // the targets of that class in every problem using the set, so the coarse
-// levels of small problems (a few boxes per class each) fill whole tiles.
-int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, bool mixed,
+// levels of small problems (a few boxes per class each) fill whole tiles.  nd: the
+// digits of the levels to take (0: mixed, every level).
+int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, int nd,
              std::vector<void *> &track) {
+  const bool mixed = nd == 0;
   struct Key {
     const void *A;
     int k, c;
@@ -2877,7 +2898,7 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, bool mixed
     const Plan &P = *Pp;
     for (int k = P.depth; k >= 2; --k) {
       const int64_t na = P.nact[k];
-      if (na == 0) continue;
+      if (na == 0 || P.ld[k].nd != nd) continue;
       cls.resize(na);
       if (hipMemcpy(cls.data(), P.ld[k].cls, sizeof(int) * na, hipMemcpyDeviceToHost) !=
           hipSuccess)
@@ -2908,8 +2929,8 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, bool mixed
           GemmJob J{};
           J.A = A;
           J.terms = P.dlist + 189 * c;
-          J.a_stride = (int64_t)dm * dk * (mixed ? sizeof(float) : kDigits);
-          J.rscale = P.ld[k].rscale;
+          J.a_stride = (int64_t)dm * dk * (mixed ? sizeof(float) : nd);
+          J.kexp = P.ld[k].kexp;
           J.nterms = 189;
           J.dpm = dm;
           J.dpk = dk;
@@ -2925,7 +2946,8 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, bool mixed
     }
   }
   F = FusedGemm{};
-  F.rbt = rbt > 0 ? rbt : (mixed ? pick_m2l32 : pick_m2l8)(dmax / 16);
+  F.rbt = rbt > 0 ? rbt : mixed ? pick_m2l32(dmax / 16) : pick_m2l8(dmax / 16, nd);
+  F.nd = nd;
   if (jobs.empty()) return EIFMM_OK;
   // finest level first (as in a plan's own launch), then operator set and class
   std::vector<int> order(jobs.size());
@@ -3127,7 +3149,8 @@ int batch_prepare(BatchExec &B, const std::vector<Plan *> &plans_in, int m2l_rbt
   }
   for (int q = 0; q < nq; ++q) r[q] = {plans[q]->jobs.pre_first, plans[q]->jobs.pre_n};
   if ((st = fuse_jobs(B.pre, plans, r, 0, B.track))) return st;
-  if ((st = pack_m2l(B.m2l, plans, m2l_rbt, B.mixed, B.track))) return st;
+  if ((st = pack_m2l(B.m2l, plans, m2l_rbt, B.mixed ? 0 : kDigits, B.track))) return st;
+  if (!B.mixed && (st = pack_m2l(B.m2l_steep, plans, 0, kDigitsSteep, B.track))) return st;
   for (int q = 0; q < nq; ++q) r[q] = {plans[q]->jobs.post_first, plans[q]->jobs.post_n};
   if ((st = fuse_jobs(B.post, plans, r, 0, B.track))) return st;
   for (int k = 3; k <= B.maxdepth; ++k) {
@@ -3146,6 +3169,7 @@ int batch_prepare(BatchExec &B, const std::vector<Plan *> &plans_in, int m2l_rbt
 
 void batch_run_m2l(const BatchExec &B, hipStream_t s) {
   launch_gemm_fused(B.m2l, MODE_M2L, B.mixed, B.sk_groups, B.sk_ws, B.dvec, s);
+  launch_gemm_fused(B.m2l_steep, MODE_M2L, false, B.sk_groups, B.sk_ws, B.dvec, s);
 }
 
 int batch_marks(const BatchExec &B) { return 9 + 3 * (int)B.groups.size(); }

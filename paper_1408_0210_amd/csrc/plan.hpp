@@ -20,12 +20,17 @@ constexpr int kM2l2RbMin = 4, kM2l2RbMax = 16;  // 16-row blocks of r the factor
 constexpr int kSortBits = 9;   // most bits of a radix-sort digit
 constexpr int kActCols = 11;   // counts per block of the active-box compaction (tree.hip)
 constexpr int kSegSources = 256;  // sources of a P2M segment
-// FP64 M2L on the int8 matrix cores (m2l.hip): digits per operand, and the columns'
-// length padded to whole 64-element chunks
-constexpr int kDigits = 7;
+// FP64 M2L on the int8 matrix cores (m2l.hip): digits per operand (kDigitsSteep on levels
+// where the kernel is steep), and the columns' length padded to whole 64-element chunks
+constexpr int kDigits = 7, kDigitsSteep = 8;
+// A level is steep above this LevelHost::spread.  An offset's product by 7 digits is off by
+// 0.5 to 0.8 times what a chain of FP64 FMAs is at a spread of 2^6 (e^-8r/r, level 2), 0.8 to
+// 1.5 times at 2^8.5 (e^-12r/r), up to 18 times at 2^38; 8 digits, a third more products,
+// stay below 0.2 times.
+constexpr double kSteep = 128.0;
 constexpr int kDigitCols = 16;  // columns per workgroup of the digit kernels
 inline int digit_kp(int d) { return (d + 63) / 64 * 64; }
-inline size_t digit_bytes(int d) { return (size_t)kDigits * digit_kp(d); }
+inline size_t digit_bytes(int d, int nd) { return (size_t)nd * digit_kp(d); }
 // columns of an M2L tile of `height` row blocks
 __host__ __device__ inline int m2l8_cols(int height) { return height >= 6 ? 64 : 128; }
 
@@ -43,6 +48,9 @@ struct LevelHost {
   std::vector<double> B, G;     // d x d row-major: unit-lower B and lower Gamma
   // operator tables, padded to dp and laid out for the device (see setup.cpp)
   std::vector<double> kfrag;    // 316 M2L matrices K^delta, fragment order (host only)
+  // the largest ratio, over the offsets, of two rows' largest |K^delta| (before the
+  // compression): how far the kernel falls across a pair of boxes
+  double spread = 1;
   std::vector<double> m2m;      // level k < depth: 8 ops d_k x d_{k+1}, fragment order
   std::vector<double> l2l;      // level k < depth: 8 ops d_{k+1} x d_k, fragment order
   std::vector<double> tri[4];   // solve tables: Gamma, B^T, B, Gamma^T (setup.cpp)
@@ -73,11 +81,12 @@ struct LevelHost {
 
 // Device copy of one level's tables.
 struct LevelDev {
-  // M2L operators: FP32 fragments, 4 k per lane (mixed), or digit fragments and row
-  // scales (FP64)
+  // M2L operators: FP32 fragments, 4 k per lane (mixed), or digit fragments and the
+  // exponents of the rows of each offset (FP64)
   float *kfrag32 = nullptr;
   int8_t *k8 = nullptr;
-  double *rscale = nullptr;
+  int nd = 0;  // their digits per operand (0: no digits)
+  int *kexp = nullptr;
   double *ksmall = nullptr;  // or, of at most 32 x 32, FP64 fragments (m2l_small.hip)
   double *m2m = nullptr, *l2l = nullptr;
   double *tri[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -139,9 +148,10 @@ struct GemmJob {
   int64_t units_start;  // first (tile, term) unit of the job within its launch
   const ColRef *colref;  // packed M2L: per target column (tgt, tgt_keys, src_slot,
   const ColSrc *colsrc;  // Bsrc and C unused); null otherwise
-  // FP64 M2L: scale of each source column and of each operator row (A and Bsrc hold
-  // digits, dpk is the padded column length).  a_stride of both M2Ls is in bytes
-  const double *bscale, *rscale;
+  // FP64 M2L: scale of each source column, exponent of each operator row by offset (A and
+  // Bsrc hold digits, dpk is the padded column length).  a_stride of both M2Ls is in bytes
+  const double *bscale;
+  const int *kexp;
   int ksteps;  // m2l_small.hip: k-steps of 4 in A (A and Bsrc are FP64 there)
 };
 
@@ -186,6 +196,7 @@ struct FusedGemm {
   GemmJob *dev = nullptr;
   int n = 0, tiles = 0, rbt = 6;
   int dk = 0;  // columns of the first job's operators (M2L)
+  int nd = 0;  // FP64 M2L: digits per operand
   int64_t units = 0;
 };
 
@@ -206,7 +217,7 @@ struct DigitDesc {
   const double *in;
   int8_t *out;
   double *scale;
-  int ncols, ld, kp, blk_start;
+  int ncols, ld, kp, nd, blk_start;
 };
 
 // Problems of one kernel kind inside a batch (contiguous descriptor range).
@@ -233,7 +244,7 @@ struct BatchExec {
   size_t what_shm = 0, lhat_shm = 0;
   DigitDesc *digit_dev = nullptr;
   int digit_n = 0, digit_blk = 0;
-  FusedGemm m2m[kMaxLevels], l2l[kMaxLevels], pre, m2l, post;
+  FusedGemm m2m[kMaxLevels], l2l[kMaxLevels], pre, m2l, m2l_steep, post;
   int sk_groups = 0;
   double *sk_ws = nullptr;
   const int8_t *dvec = nullptr;
@@ -273,6 +284,8 @@ struct JobTables {
   int64_t m2m_units[kMaxLevels] = {}, l2l_units[kMaxLevels] = {};
   int64_t pre_units = 0, post_units = 0;
   int m2l_first = 0, m2l_n = 0, m2l_tiles = 0, m2l_rbt = 6;
+  // FP64 M2L of steep levels (operands of kDigitsSteep digits)
+  int steep_first = 0, steep_n = 0, steep_tiles = 0, steep_rbt = 6;
   int small_first = 0, small_n = 0, small_grid = 0;  // M2L of levels of small operators
   int pre_first = 0, pre_n = 0, pre_tiles = 0, pre_rbt = 6;     // What' = U^T B^{-T} z
   int post_first = 0, post_n = 0, post_tiles = 0, post_rbt = 6; // g = U g'
@@ -412,9 +425,9 @@ int eim_iterate_gpu(const std::vector<double> &R, int64_t nx, int64_t ny, double
                     double abs_scale, int dmax, EimResult &res);
 int pick_rbt(int nrb);
 // FP64 M2L (m2l.hip)
-int pick_m2l8(int nrb);
-int upload_digit_operators(const std::vector<double> &frag, int rows, int cols, int8_t *dig,
-                           double *scale);
+int pick_m2l8(int nrb, int nd);
+int upload_digit_operators(const std::vector<double> &frag, int rows, int cols, int nd,
+                           int8_t *dig, int *kexp);
 // mixed M2L (m2l32.hip)
 constexpr int kM2l32Cols = 128;  // columns of its tiles
 int pick_m2l32(int nrb);
@@ -449,7 +462,7 @@ void launch_m2l_few(const LevelDev &D, bool mixed, const void *B, int dm, int dk
 int digit_blocks(int ncols);
 void launch_digits(const DigitDesc *lv, int nlev, int blocks, hipStream_t s);
 void launch_digits_list(const DigitDesc *dev, int n, int blocks, hipStream_t s);
-void launch_m2l8(const GemmJob *jobs, int n, int tiles, int height, int cus, double *ws,
+void launch_m2l8(const GemmJob *jobs, int n, int tiles, int height, int nd, int cus, double *ws,
                  size_t ws_len, const int8_t *dvec, hipStream_t s);
 
 // device-side entry points (tree.hip, pass.hip)

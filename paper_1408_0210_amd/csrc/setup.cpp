@@ -860,10 +860,19 @@ int build_tables(Plan &P) {
     if (r > 0 && c.compress_tol2 > 0) lv.s2.assign(kNumOffsets, 0);
     std::vector<std::vector<double>> fUt(lv.s2.empty() ? 0 : kNumOffsets),
         fVt(lv.s2.empty() ? 0 : kNumOffsets);
+    std::vector<double> spread(kNumOffsets, 1.0);
     parallel_for(kNumOffsets, [&](int64_t o0, int64_t o1) {
       std::vector<double> A((size_t)dB * d), KU, C;
       for (int64_t o = o0; o < o1; ++o) {
         kdelta((int)o, A);
+        double hi = 0.0, lo = INFINITY;
+        for (int i = 0; i < dB; ++i) {
+          double m = 0.0;
+          for (int j = 0; j < d; ++j) m = std::max(m, std::fabs(A[(size_t)i * d + j]));
+          hi = std::max(hi, m);
+          lo = std::min(lo, m);
+        }
+        if (hi > 0.0) spread[o] = hi / lo;
         if (r == 0) {
           to_fragments(A.data(), dB, d, dpB, dp, &lv.kfrag[(size_t)o * dpB * dp]);
           continue;
@@ -904,6 +913,7 @@ int build_tables(Plan &P) {
         to_fragments(C.data(), r, r, rp, rp, &lv.kfrag[(size_t)o * rp * rp]);
       }
     });
+    lv.spread = *std::max_element(spread.begin(), spread.end());
     if (!lv.s2.empty()) {
       // pack the factors in fragment order; a level whose ranks exceed the
       // kernel's bound (kMaxRank2) keeps only the dense product
