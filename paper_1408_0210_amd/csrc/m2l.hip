@@ -51,7 +51,7 @@ typedef int i4v __attribute__((ext_vector_type(4)));
 constexpr int kFrag = 1024;  // bytes of one 16 x 64 operand fragment (64 lanes x 16)
 
 // zeros, read in place of a missing source column (digits of 1024 elements) and,
-// as a double, of its scale
+// as a ColScale, of its scale
 __device__ i4v g_digit_zero[kDigitsSteep * 1024 / 16];
 
 // the exponent e of the smallest power of two with m 2^-e <= 0.498, so that the top
@@ -126,8 +126,7 @@ __global__ __launch_bounds__(256) void k_op_digits(const double *__restrict__ fr
 }
 
 // Source columns into digits: 16 lanes per column, 4 consecutive k per lane and
-// 64-k chunk; out: [column][chunk][digit][64 k] bytes, scale: one power of two per
-// column (0 for a zero column, NaN for one holding an infinity or a NaN).  The digits
+// 64-k chunk; out: [column][chunk][digit][64 k] bytes, scale: ColScale.  The digits
 // are those of the column with its first entry that is not zero made positive, and the
 // scale carries the sign: the digits of x and -x differ otherwise (a digit of -128 has
 // no counterpart), and a pass of -sigma would not be exactly the negative one.
@@ -183,7 +182,10 @@ __device__ inline void digit_column(const DigitDesc &D, int col) {
 #pragma unroll
     for (int s = 0; s < ND; ++s) stg((uint32_t *)(o + 64 * s), pk[s]);
   }
-  if (li == 0) stg(D.scale + col, bad ? (double)NAN : use ? ldexp(neg ? -1.0 : 1.0, e) : 0.0);
+  if (li == 0) {
+    D.scale[col].sign = bad ? NAN : !use ? 0.0f : neg ? -1.0f : 1.0f;
+    D.scale[col].e = e;
+  }
 }
 
 __device__ inline void digit_column_of(const DigitDesc &D, int col) {
@@ -267,7 +269,7 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
     const int8_t *srcp = nullptr, *At = nullptr;
     // scale of the source and whether the wave has any: of the term aimed at (n), of
     // the last one loaded (q)
-    double scn = 0.0, scq = 0.0;
+    ColScale scn{}, scq{};
     bool haven = false, haveq = false;
     int en = 0;          // a row's exponent of the term aimed at (the first 16 H threads)
     int ew = 0, er = 2;  // buffer of exponents: the next one to write, the current term's
@@ -280,7 +282,8 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
       const int sl = slotn;
       const int64_t col = (int64_t)sl * J.nrhs + c.r;
       srcp = (sl < 0 ? (const int8_t *)g_digit_zero : (const int8_t *)c.B + col * colbytes) + 16 * (lane >> 4);
-      scn = ldg(sl < 0 ? (const double *)g_digit_zero : c.bs + col);
+      const ColScale *bs = sl < 0 ? (const ColScale *)g_digit_zero : c.bs + col;
+      scn = ColScale{ldg(&bs->sign), ldg(&bs->e)};
       haven = __ballot(sl >= 0) != 0;
       const int o = __builtin_amdgcn_readfirstlane(sdel[fq]) >> 9;
       At = Abase + (int64_t)o * J.a_stride;
@@ -359,8 +362,10 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
       };
       for_each_from<0, NF>(group);
     };
-    // a term's digit sums, joined in FP64 and scaled, added to the tile's sums
-    auto fold = [&](double scf) {
+    // a term's digit sums, joined in FP64 and scaled (by the sum of the exponents, so that
+    // nothing but the product itself has to lie in range), added to the tile's sums
+    auto fold = [&](ColScale scf) {
+      const double sign = scf.sign;
 #pragma unroll
       for (int i = 0; i < RB; ++i) {
         const i4v ex = *(const i4v *)&Es[er][16 * (rg * RB + i) + 4 * (lane >> 4)];
@@ -369,7 +374,7 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
           double v = (double)acc[i][ND - 1][q];
 #pragma unroll
           for (int s = ND - 2; s >= 0; --s) v = fma(v, 1.0 / 256.0, (double)acc[i][s][q]);
-          sum[i][q] = fma(ldexp(v, ex[q]), scf, sum[i][q]);
+          sum[i][q] = fma(ldexp(v, ex[q] + scf.e), sign, sum[i][q]);
         }
       }
     };
@@ -382,7 +387,7 @@ __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, in
       __builtin_amdgcn_s_setprio(1);
     else
       __builtin_amdgcn_s_setprio(0);
-    double sc = 0.0;
+    ColScale sc{};
     bool have = false, pend = false;  // pend: the last term's sums are not joined yet
     int kc = 0;                       // chunk of the current term
     auto step = [&](int buf) {

@@ -27,7 +27,7 @@ struct FewArgs {
   const void *A;            // operators: FP32 fragments, or digits
   const int *slot;          // slot map of level 2
   const void *B;            // source columns: FP32, or digits
-  const double *bscale;     // digits: scale of each source column,
+  const ColScale *bscale;   // digits: scale of each source column,
   const int *kexp;          // exponent of each row of each offset
   void *prod;               // [316][32][dm]: FP32 or FP64
   unsigned long long *mask; // [316] targets of each offset
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(256) void k_few_products(FewArgs F, const int8_t *_
     for (int j = 0; j < 2; ++j) {
       const int c = j ? c1 : c0, sl = j ? s1 : s0;
       if (c >= n) continue;
-      const double sc = F.bscale[sl];
+      const ColScale sc = F.bscale[sl];
       double *P = (double *)F.prod + ((int64_t)o * kFewCols + c) * F.dm + row;
       const int *ex = F.kexp + (int64_t)o * F.dm + row;
 #pragma unroll
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256) void k_few_products(FewArgs F, const int8_t *_
         double v = (double)acc[j][ND - 1][q];
 #pragma unroll
         for (int s = ND - 2; s >= 0; --s) v = fma(v, 1.0 / 256.0, (double)acc[j][s][q]);
-        P[q] = ldexp(v, ldg(ex + q)) * sc;
+        P[q] = ldexp(v, ldg(ex + q) + sc.e) * sc.sign;
       }
     }
   } else {

@@ -55,7 +55,7 @@ __device__ int g_no_slot = -1;  // the slot of a missing source
 struct TileCol {
   const int *slot_map;  // slot map of the level
   const void *B;        // source columns
-  const double *bs;     // their scales (FP64)
+  const ColScale *bs;   // their scales (FP64)
   uint32_t tkey;        // target key
   int r, valid;
 };

@@ -34,6 +34,13 @@ inline size_t digit_bytes(int d, int nd) { return (size_t)nd * digit_kp(d); }
 // columns of an M2L tile of `height` row blocks
 __host__ __device__ inline int m2l8_cols(int height) { return height >= 6 ? 64 : 128; }
 
+// scale of a digit column: sign 2^e (two numbers, since 2^e may lie outside the range).  The
+// sign is 0 for a zero column and NaN for one holding an infinity or a NaN.
+struct ColScale {
+  float sign;
+  int e;
+};
+
 // Host copy of one level's EIM data (Algorithm 1 and the factors of eq. (5)).
 struct LevelHost {
   int d = 0;   // number of interpolation points d_k
@@ -113,7 +120,7 @@ struct LevelDev {
   float *Whp32 = nullptr;
   // FP64 M2L: the digits and the scale of each source column (What or What')
   int8_t *w8 = nullptr;
-  double *wscale = nullptr;
+  ColScale *wscale = nullptr;
 };
 
 // Packed M2L jobs of a batch: the columns of one job belong to several problems
@@ -123,7 +130,7 @@ struct ColSrc {
   const int *slot;       // slot map of the level
   const void *B;         // source expansions (What or What')
   double *C;             // output (g or g')
-  const double *bscale;  // FP64: scale of each source column (B holds digits)
+  const ColScale *bscale;  // FP64: scale of each source column (B holds digits)
 };
 struct ColRef {
   int rec;   // ColSrc record
@@ -150,7 +157,7 @@ struct GemmJob {
   const ColSrc *colsrc;  // Bsrc and C unused); null otherwise
   // FP64 M2L: scale of each source column, exponent of each operator row by offset (A and
   // Bsrc hold digits, dpk is the padded column length).  a_stride of both M2Ls is in bytes
-  const double *bscale;
+  const ColScale *bscale;
   const int *kexp;
   int ksteps;  // m2l_small.hip: k-steps of 4 in A (A and Bsrc are FP64 there)
 };
@@ -216,7 +223,7 @@ struct SolveDesc {
 struct DigitDesc {
   const double *in;
   int8_t *out;
-  double *scale;
+  ColScale *scale;
   int ncols, ld, kp, nd, blk_start;
 };
 
