@@ -515,20 +515,17 @@ void launch(const GemmJob *jobs, int n, int tiles, int cus, double *ws, size_t w
 
 }  // namespace
 
-// The tile height that leaves the fewest idle row blocks, the taller one on a tie.
-// 8 and 6 blocks are 64 columns wide, the lower ones 128.  Eight digits leave LDS for
-// at most 6; there 4 take 2.97 ms where 3 take 3.70 and 6 (20 % idle) 3.71 (32 problems,
-// half of them e^(-r^2 / 0.01), 20 row blocks), and 2 serve operators of no more.
+// The tile height that leaves the fewest idle row blocks, the taller one on a tie (with 8
+// digits the lower one).  8 and 6 blocks are 64 columns wide, the lower ones 128.  Eight
+// digits leave LDS for at most 6; there 4 take 2.97 ms where 3 take 3.70 and 6 (20 % idle)
+// 3.71 (32 problems, half of them e^(-r^2 / 0.01), 20 row blocks), and 2 serve operators of
+// no more.
 int pick_m2l8(int nrb, int nd) {
-  int best = 8, waste = 1 << 30;
-  for (int h : {8, 6, 4, 3, 2}) {
-    if (nd == kDigitsSteep && (h == 8 || h == 3 || (h == 2 && nrb > 2))) continue;
-    const int w = (nrb + h - 1) / h * h - nrb;
-    if (w < waste) {
-      waste = w;
-      best = h;
-    }
-  }
+  auto waste = [&](int h) { return (nrb + h - 1) / h * h - nrb; };
+  if (nd == kDigitsSteep) return nrb <= 2 ? 2 : waste(6) < waste(4) ? 6 : 4;
+  int best = 8;
+  for (int h : {6, 4, 3, 2})
+    if (waste(h) < waste(best)) best = h;
   return best;
 }
 
