@@ -183,9 +183,8 @@ int setup_tables(eifmm_plan h) {
           for (int ks = 0; ks < 4; ++ks) out[4 * l + ks] = (float)in[64 * ks + l];
       }
       TRY(upload(&D.kfrag32, f32.data(), f32.size(), tr));
-    } else if (!P.shared_tables && H.sp2.empty() &&
+    } else if ((P.shared_tables || H.sp2.empty()) &&
                std::max(H.r > 0 ? H.rp : H.dpB, H.r > 0 ? H.rp : H.dp) <= kSmallM2l) {
-      // (a batch packs problems of any operator size into the digit kernel's jobs)
       const int dm = H.r > 0 ? H.rp : H.dpB, dk = H.r > 0 ? H.rp : H.dp;
       const std::vector<double> a =
           m2l_small_operators(H.kfrag, dm, dk, m2l_small_steps(H.r > 0 ? H.r : H.d));
@@ -448,6 +447,7 @@ int shared_plan(eifmm_batch b, int p, int depth, eifmm_plan *out) {
     D.k8 = TD.k8;
     D.kexp = TD.kexp;
     D.nd = TD.nd;
+    D.ksmall = TD.ksmall;
     D.kfrag32 = TD.kfrag32;
     D.m2m = TD.m2m;
     D.l2l = TD.l2l;

@@ -2879,11 +2879,17 @@ int fuse_jobs(FusedGemm &F, const std::vector<Plan *> &plans,
 
 // Packed M2L: one job per (operator set, level, child class) whose columns are
 // the targets of that class in every problem using the set, so the coarse
-// levels of small problems (a few boxes per class each) fill whole tiles.  nd: the
-// digits of the levels to take (0: mixed, every level).
-int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, int nd,
+// levels of small problems (a few boxes per class each) fill whole tiles.  kind: the
+// levels to take (of a mixed batch all).
+enum M2lKind { kM2lMixed, kM2lDigits, kM2lSteep, kM2lSmall };
+M2lKind m2l_kind(const Plan &P, int k) {
+  if (P.cfg.precision == EIFMM_PREC_MIXED) return kM2lMixed;
+  return P.ld[k].ksmall ? kM2lSmall : P.ld[k].nd == kDigitsSteep ? kM2lSteep : kM2lDigits;
+}
+int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, M2lKind kind,
              std::vector<void *> &track) {
-  const bool mixed = nd == 0;
+  const bool mixed = kind == kM2lMixed, small = kind == kM2lSmall;
+  const int nd = kind == kM2lSteep ? kDigitsSteep : kind == kM2lDigits ? kDigits : 0;
   struct Key {
     const void *A;
     int k, c;
@@ -2893,25 +2899,30 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, int nd,
   std::vector<std::vector<ColRef>> refs;
   std::vector<ColSrc> srcs;
   std::vector<int> cls;
-  int dmax = 16;
+  int dmax = 16, kmax = 0;
   for (Plan *Pp : plans) {
     const Plan &P = *Pp;
     for (int k = P.depth; k >= 2; --k) {
       const int64_t na = P.nact[k];
-      if (na == 0 || P.ld[k].nd != nd) continue;
+      if (na == 0 || m2l_kind(P, k) != kind) continue;
       cls.resize(na);
       if (hipMemcpy(cls.data(), P.ld[k].cls, sizeof(int) * na, hipMemcpyDeviceToHost) !=
           hipSuccess)
         return EIFMM_EHIP;
       const bool cz = P.lh[k].r > 0;
-      const int dm = cz ? P.lh[k].rp : P.lh[k].dp, dk = mixed ? dm : digit_kp(dm);
-      dmax = std::max(dmax, dm);
-      const void *A = mixed ? (const void *)P.ld[k].kfrag32 : (const void *)P.ld[k].k8;
+      const int dm = cz ? P.lh[k].rp : P.lh[k].dp, dk = nd == 0 ? dm : digit_kp(dm);
+      dmax = k > kmax ? dm : k == kmax ? std::max(dmax, dm) : dmax;  // of the finest level
+      kmax = std::max(kmax, k);
+      const void *A = mixed   ? (const void *)P.ld[k].kfrag32
+                      : small ? (const void *)P.ld[k].ksmall
+                              : (const void *)P.ld[k].k8;
       ColSrc cs{};
       cs.keys = P.ld[k].act;
       cs.slot = P.ld[k].slot;
       if (mixed) {
         cs.B = cz ? P.ld[k].Whp32 : P.ld[k].Wh32;
+      } else if (small) {
+        cs.B = cz ? P.ld[k].Whp : P.ld[k].Wh;
       } else {
         cs.B = P.ld[k].w8;
         cs.bscale = P.ld[k].wscale;
@@ -2931,6 +2942,7 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, int nd,
           J.terms = P.dlist + 189 * c;
           J.a_stride = (int64_t)dm * dk * (mixed ? sizeof(float) : nd);
           J.kexp = P.ld[k].kexp;
+          J.ksteps = m2l_small_steps(cz ? P.lh[k].r : P.lh[k].d);
           J.nterms = 189;
           J.dpm = dm;
           J.dpk = dk;
@@ -2946,7 +2958,10 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, int nd,
     }
   }
   F = FusedGemm{};
-  F.rbt = rbt > 0 ? rbt : mixed ? pick_m2l32(dmax / 16) : pick_m2l8(dmax / 16, nd);
+  F.rbt = rbt > 0 ? rbt
+          : mixed ? pick_m2l32(dmax / 16)
+          : small ? kSmallM2l / 16
+                  : pick_m2l8(dmax / 16, nd);
   F.nd = nd;
   if (jobs.empty()) return EIFMM_OK;
   // finest level first (as in a plan's own launch), then operator set and class
@@ -2973,7 +2988,8 @@ int pack_m2l(FusedGemm &F, const std::vector<Plan *> &plans, int rbt, int nd,
   for (size_t j = 0; j < h.size(); ++j) {
     h[j].colsrc = srcs_dev;
     h[j].colref = refs_dev + off[j];
-    finish_job(h[j], tiles, F.rbt, mixed ? kM2l32Cols : m2l8_cols(F.rbt));
+    finish_job(h[j], tiles, F.rbt,
+               mixed ? kM2l32Cols : small ? kSmallM2lCols : m2l8_cols(F.rbt));
   }
   F.units = finish_units(h, 0);
   F.tiles = tiles;
@@ -3124,7 +3140,7 @@ int batch_prepare(BatchExec &B, const std::vector<Plan *> &plans_in, int m2l_rbt
       int blk = 0;
       for (Plan *Pp : plans)
         for (int k = Pp->depth; k >= 2; --k) {
-          if (Pp->nact[k] == 0) continue;
+          if (Pp->nact[k] == 0 || Pp->ld[k].ksmall) continue;
           dd.push_back(digit_desc(*Pp, k, 1, blk));
           blk += digit_blocks(dd.back().ncols);
         }
@@ -3149,8 +3165,9 @@ int batch_prepare(BatchExec &B, const std::vector<Plan *> &plans_in, int m2l_rbt
   }
   for (int q = 0; q < nq; ++q) r[q] = {plans[q]->jobs.pre_first, plans[q]->jobs.pre_n};
   if ((st = fuse_jobs(B.pre, plans, r, 0, B.track))) return st;
-  if ((st = pack_m2l(B.m2l, plans, m2l_rbt, B.mixed ? 0 : kDigits, B.track))) return st;
-  if (!B.mixed && (st = pack_m2l(B.m2l_steep, plans, 0, kDigitsSteep, B.track))) return st;
+  if ((st = pack_m2l(B.m2l, plans, m2l_rbt, B.mixed ? kM2lMixed : kM2lDigits, B.track))) return st;
+  if (!B.mixed && (st = pack_m2l(B.m2l_steep, plans, 0, kM2lSteep, B.track))) return st;
+  if (!B.mixed && (st = pack_m2l(B.m2l_small, plans, 0, kM2lSmall, B.track))) return st;
   for (int q = 0; q < nq; ++q) r[q] = {plans[q]->jobs.post_first, plans[q]->jobs.post_n};
   if ((st = fuse_jobs(B.post, plans, r, 0, B.track))) return st;
   for (int k = 3; k <= B.maxdepth; ++k) {
@@ -3170,6 +3187,7 @@ int batch_prepare(BatchExec &B, const std::vector<Plan *> &plans_in, int m2l_rbt
 void batch_run_m2l(const BatchExec &B, hipStream_t s) {
   launch_gemm_fused(B.m2l, MODE_M2L, B.mixed, B.sk_groups, B.sk_ws, B.dvec, s);
   launch_gemm_fused(B.m2l_steep, MODE_M2L, false, B.sk_groups, B.sk_ws, B.dvec, s);
+  launch_m2l_small_packed(B.m2l_small.dev, B.m2l_small.n, B.m2l_small.tiles, B.dvec, s);
 }
 
 int batch_marks(const BatchExec &B) { return 9 + 3 * (int)B.groups.size(); }

@@ -251,7 +251,7 @@ struct BatchExec {
   size_t what_shm = 0, lhat_shm = 0;
   DigitDesc *digit_dev = nullptr;
   int digit_n = 0, digit_blk = 0;
-  FusedGemm m2m[kMaxLevels], l2l[kMaxLevels], pre, m2l, m2l_steep, post;
+  FusedGemm m2m[kMaxLevels], l2l[kMaxLevels], pre, m2l, m2l_steep, m2l_small, post;
   int sk_groups = 0;
   double *sk_ws = nullptr;
   const int8_t *dvec = nullptr;
@@ -457,6 +457,8 @@ constexpr int kSmallM2lCols = 32;  // columns of a tile
 int m2l_small_steps(int d);
 std::vector<double> m2l_small_operators(const std::vector<double> &frag, int rows, int cols, int ks);
 void launch_m2l_small(const GemmJob *jobs, int n, int grid, const int8_t *dvec, hipStream_t s);
+void launch_m2l_small_packed(const GemmJob *jobs, int n, int tiles, const int8_t *dvec,
+                             hipStream_t s);
 // level 2 by offset (m2l_few.hip): trees of at most this depth (deeper ones hide the
 // level's few tiles among the others), one right-hand side, plans with their own tables
 constexpr int kFewDepth = 3;
