@@ -3005,16 +3005,19 @@ void run_group(const BatchExec &B, const BatchGroup &g, int phase, hipStream_t s
   const IoDesc inone{};
   if (phase == 0)
     launch_p2p<KIND, true>(B.mixed, 1, g.nchunk, none, many, g.count, s);
-  else if (phase == 1)
-  {
-    launch_p2m<KIND, true>(1, (unsigned)g.nseg, g.dpmax, none, many, g.count, s, B.mixed);
-    if (g.nseg > g.nleaf)
-      hipLaunchKernelGGL((k_p2m_ext<true>), dim3((unsigned)g.nseg), dim3(256), 0, s, none, many,
-                         g.count);
-  }
-  else
+  else if (phase == 1) {
+    for (int rounded = 1; rounded >= 0; --rounded) {
+      const LeafDesc *d = rounded ? many : many + g.rounded;
+      const int n = rounded ? g.rounded : g.count - g.rounded;
+      const unsigned nseg = (unsigned)g.nseg[rounded];
+      launch_p2m<KIND, true>(1, nseg, g.dpmax, none, d, n, s, rounded);
+      if (g.nseg[rounded] > g.nleaf[rounded])
+        hipLaunchKernelGGL((k_p2m_ext<true>), dim3(nseg), dim3(256), 0, s, none, d, n);
+    }
+  } else {
     launch_l2p<KIND, true>(1, g.nchunk, g.dpmax, none, inone, many, B.io_dev + g.first, g.count,
                            s);
+  }
 }
 
 void run_groups(const BatchExec &B, int phase, hipStream_t s, const hipEvent_t *mark,
@@ -3056,40 +3059,43 @@ int batch_prepare(BatchExec &B, const std::vector<Plan *> &plans_in, int m2l_rbt
     }
     B.maxdepth = std::max(B.maxdepth, P->depth);
   }
-  // descriptor order: problems grouped by kernel kind, batch order inside a group
+  // descriptor order: problems grouped by kernel kind, in a group those whose What is
+  // rounded first, then batch order
   std::vector<Plan *> plans;
   for (int kind = EIFMM_K_LAPLACE; kind <= EIFMM_K_MQ; ++kind) {
     BatchGroup g;
     g.kind = kind;
     g.first = (int)plans.size();
-    for (int q = 0; q < np; ++q)
-      if (plans_in[q]->cfg.kernel == kind) {
-        B.order.push_back(q);
-        plans.push_back(plans_in[q]);
-      }
-    g.count = (int)plans.size() - g.first;
+    for (int rounded = 1; rounded >= 0; --rounded) {
+      for (int q = 0; q < np; ++q)
+        if (plans_in[q]->cfg.kernel == kind && what_rounded(*plans_in[q]) == (rounded == 1)) {
+          B.order.push_back(q);
+          plans.push_back(plans_in[q]);
+        }
+      g.count = (int)plans.size() - g.first;
+      if (rounded) g.rounded = g.count;
+    }
     if (g.count) B.groups.push_back(g);
   }
   std::vector<LeafDesc> leaf(np);
   int64_t pts = 0;
   for (BatchGroup &g : B.groups) {
-    int64_t ch = 0, lf = 0, sg = 0;
+    int64_t ch = 0;
     for (int q = g.first; q < g.first + g.count; ++q) {
       const Plan &P = *plans[q];
+      const int rounded = q < g.first + g.rounded ? 1 : 0;
       LeafDesc D = leaf_desc(P, 1);
       D.chunk_base = ch;
-      D.seg_base = sg;
+      D.seg_base = g.nseg[rounded];
       D.pt_base = pts;
       ch += P.nchunk;
-      lf += P.nact[P.depth];
-      sg += P.nseg;
+      g.nleaf[rounded] += P.nact[P.depth];
+      g.nseg[rounded] += P.nseg;
       pts += P.n;
       g.dpmax = std::max(g.dpmax, std::max(P.lh[P.depth].dp, P.lh[P.depth].dpB));
       leaf[q] = D;
     }
     g.nchunk = ch;
-    g.nleaf = lf;
-    g.nseg = sg;
   }
   B.total_pts = pts;
   int st = bupload(&B.leaf_dev, leaf, B.track);

@@ -227,11 +227,14 @@ struct DigitDesc {
   int ncols, ld, kp, nd, blk_start;
 };
 
-// Problems of one kernel kind inside a batch (contiguous descriptor range).
+// Problems of one kernel kind inside a batch (contiguous descriptor range).  Those whose
+// What is rounded to FP32 (what_rounded) come first: their P2M is a launch of its own.
 struct BatchGroup {
   int kind = 0;
   int first = 0, count = 0;
-  int64_t nchunk = 0, nseg = 0, nleaf = 0;
+  int rounded = 0;  // the first `rounded` of them
+  int64_t nchunk = 0;
+  int64_t nseg[2] = {0, 0}, nleaf[2] = {0, 0};  // P2M segments and leaves: [1] of those
   int dpmax = 0;
 };
 
