@@ -260,7 +260,8 @@ int setup_workspaces(eifmm_plan h, double *shared_ws) {
   TRY(dalloc(&P.keys_tmp, nn, tr));
   TRY(dalloc(&P.idx, nn, tr));
   TRY(dalloc(&P.idx_tmp, nn, tr));
-  TRY(dalloc(&P.hist, ((size_t)P.ntiles_sort << kSortBits), tr));
+  const int sort_bins = 1 << sort_width(3 * depth + (P.nt ? 1 : 0));
+  TRY(dalloc(&P.hist, (size_t)P.ntiles_sort * sort_bins, tr));
   const int64_t nleaf = (int64_t)1 << (3 * depth);
   TRY(dalloc(&P.leaf_start, nleaf + 1, tr));
   if (P.nt) {
@@ -277,7 +278,7 @@ int setup_workspaces(eifmm_plan h, double *shared_ws) {
     TRY(dalloc(&D.cls, D.cap, tr));
     if (k >= 2 && k <= kMaxOrderLevel) TRY(dalloc(&D.ord, D.cap, tr));
   }
-  const size_t scan_len = std::max<size_t>((size_t)P.ntiles_sort << kSortBits, maxcap + 2);
+  const size_t scan_len = std::max<size_t>((size_t)P.ntiles_sort * sort_bins, maxcap + 2);
   TRY(dalloc(&P.scan_tmp, scan_len / 1024 + 64, tr));
   {
     size_t blocks = 1;  // blocks of 256 boxes over the levels of the active-box compaction

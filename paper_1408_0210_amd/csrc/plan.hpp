@@ -18,6 +18,12 @@ constexpr int kMaxRank2 = 96;     // largest second-stage rank the factored M2L 
 constexpr int kM2l2RbMin = 4, kM2l2RbMax = 16;  // 16-row blocks of r the factored M2L takes
 
 constexpr int kSortBits = 9;   // most bits of a radix-sort digit
+// the digit's bits for keys of `bits` bits: as few passes as kSortBits allows, the bits
+// split evenly over them
+inline int sort_width(int bits) {
+  const int passes = (bits + kSortBits - 1) / kSortBits;
+  return passes ? (bits + passes - 1) / passes : 0;
+}
 constexpr int kActCols = 11;   // counts per block of the active-box compaction (tree.hip)
 constexpr int kSegSources = 256;  // sources of a P2M segment
 // FP64 M2L on the int8 matrix cores (m2l.hip): digits per operand (kDigitsSteep on levels

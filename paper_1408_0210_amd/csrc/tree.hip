@@ -565,8 +565,7 @@ namespace {
 int sort_points(Plan &P, hipStream_t s) {
   const int64_t n = P.n;
   const int bits = 3 * P.depth + (P.nt ? 1 : 0);
-  const int passes = (bits + kSortBits - 1) / kSortBits;
-  const int width = passes ? (bits + passes - 1) / passes : 0;
+  const int width = sort_width(bits);
   const int ntiles = (int)((n + kSortTile - 1) / kSortTile);
   uint32_t *ka = P.keys, *kb = P.keys_tmp;
   int *ia = P.idx, *ib = P.idx_tmp;
