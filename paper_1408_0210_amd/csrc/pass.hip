@@ -13,6 +13,7 @@
 //   6  lhat = Delta^T l         k_trsm
 //   7  L2P and f = f_far + f_near, input order  k_l2p  one wave per 64 targets
 #include <algorithm>
+#include <cfloat>
 #include <climits>
 #include <cstring>
 #include <type_traits>
@@ -120,8 +121,9 @@ struct KF {
   }
 };
 
-__host__ __device__ inline double dev_param(int kind, double p) {
-  return kind == EIFMM_K_GAUSS ? 1.0 / p : p;
+// (1 / h2 of a denormal h2 stays finite: 0 times infinity at r = 0 would be no number)
+inline double dev_param(int kind, double p) {
+  return kind == EIFMM_K_GAUSS ? std::min(1.0 / p, DBL_MAX) : p;
 }
 
 // ------------------------------------------------------------------ leaf level
