@@ -221,15 +221,15 @@ __global__ __launch_bounds__(256) void k_digits_list(const DigitDesc *__restrict
 
 // Terms [term0, term1) of one tile of 16 RB RG rows and 128 / RG columns: the result,
 // or a piece (part).  8 waves, RG groups of rows by 8 / RG groups of 16 columns; a wave
-// holds RB row blocks of its 16 columns; operands of ND digits.  The operator fragments of a 64-k chunk go
-// to LDS one chunk ahead, in two buffers; the source digits (16 columns and 64 k are
-// one fragment per digit) one chunk ahead too, in one buffer that every wave copies
-// to registers at the start of the chunk.  Both are direct loads, which need no
-// registers: the digit sums and the FP64 sums take 144 of a lane's 256.  The rows'
-// exponents of a term go to LDS with its first chunk, in three buffers: a wave may still
-// join the sums of the term before the last one written.  The slots of the sources are
-// read one term ahead.  A step waits for all of them at its start, a
-// whole chunk of products (RB x 28 MFMAs per wave) after they were issued.
+// holds RB row blocks of its 16 columns; operands of ND digits.  The operator fragments
+// of a 64-k chunk go to LDS one chunk ahead, in two buffers; the source digits (16 columns
+// and 64 k are one fragment per digit) one chunk ahead too, in one buffer that every wave
+// copies to registers at the start of the chunk.  Both are direct loads, which need no
+// registers: the digit sums and the FP64 sums take 144 of a lane's 256 (RB = 4, 7 digits).
+// The rows' exponents of a term go to LDS with its first chunk, in three buffers: a wave may
+// still join the sums of the term before the last one written.  The slots of the sources
+// are read one term ahead.  A step waits for all of them at its start, a whole chunk of
+// products (RB x 28 or 36 MFMAs per wave) after they were issued.
 template <int ND, int RB, int RG>
 __device__ inline void m2l8_tile(const GemmJob &J, int tile_local, int term0, int term1,
                                  double *__restrict__ part, const int8_t *__restrict__ dvec,
@@ -518,13 +518,13 @@ void launch(const GemmJob *jobs, int n, int tiles, int cus, double *ws, size_t w
 // The tile height that leaves the fewest idle row blocks, the taller one on a tie (with 8
 // digits the lower one).  8 and 6 blocks are 64 columns wide, the lower ones 128.  Eight
 // digits leave LDS for at most 6; there 4 take 2.97 ms where 3 take 3.70 and 6 (20 % idle)
-// 3.71 (32 problems, half of them e^(-r^2 / 0.01), 20 row blocks), and 2 serve operators of
-// no more.
+// 3.71 (32 problems, half of them e^(-r^2 / 0.01), 20 row blocks).  (Operators of 2 row
+// blocks and as many columns go to m2l_small.hip.)
 int pick_m2l8(int nrb, int nd) {
   auto waste = [&](int h) { return (nrb + h - 1) / h * h - nrb; };
-  if (nd == kDigitsSteep) return nrb <= 2 ? 2 : waste(6) < waste(4) ? 6 : 4;
+  if (nd == kDigitsSteep) return waste(6) < waste(4) ? 6 : 4;
   int best = 8;
-  for (int h : {6, 4, 3, 2})
+  for (int h : {6, 4, 3})
     if (waste(h) < waste(best)) best = h;
   return best;
 }
@@ -534,11 +534,10 @@ void launch_m2l8(const GemmJob *jobs, int n, int tiles, int height, int nd, int 
   if (n == 0 || tiles == 0) return;
   if (nd == kDigitsSteep) {
     constexpr int N = kDigitsSteep;
-    switch (height) {
-      case 6: launch<N, 3, 2>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
-      case 4: launch<N, 4, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
-      default: launch<N, 2, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
-    }
+    if (height == 6)
+      launch<N, 3, 2>(jobs, n, tiles, cus, ws, ws_len, dvec, s);
+    else
+      launch<N, 4, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s);
     return;
   }
   constexpr int N = kDigits;
@@ -546,8 +545,7 @@ void launch_m2l8(const GemmJob *jobs, int n, int tiles, int height, int nd, int 
     case 8: launch<N, 4, 2>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
     case 6: launch<N, 3, 2>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
     case 4: launch<N, 4, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
-    case 3: launch<N, 3, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
-    default: launch<N, 2, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
+    default: launch<N, 3, 1>(jobs, n, tiles, cus, ws, ws_len, dvec, s); break;
   }
 }
 
