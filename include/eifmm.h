@@ -230,10 +230,10 @@ int eifmm_evaluate(eifmm_plan plan, const double *sigma_dev, int32_t nrhs, int64
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same pass and arguments, with no hipMalloc, hipFree or other
  * allocating call.  The plan's expansions and tables were allocated by
- * eifmm_plan_create; the partial tiles of the Stream-K tails of the gathered-GEMM
- * launches, which eifmm_evaluate keeps in a workspace of the plan, go to a
+ * eifmm_plan_create; the pieces of the tiles that the M2L and the gathered-GEMM
+ * launches split, which eifmm_evaluate keeps in a workspace of the plan, go to a
  * device array of the library instead: 32 MiB per device, held until the
- * process ends, each launch splitting its tail over as many workgroups as fit
+ * process ends, each launch splitting its tiles into as many pieces as fit
  * it.  Every call on a device shares that array, so calls that overlap in time
  * on one device (on different streams or from different threads, any plans)
  * race and must be serialised by the caller; each launch writes every piece
@@ -346,7 +346,7 @@ int eifmm_batch_create(const eifmm_config *cfgs, int32_t nprob, eifmm_batch *out
  * the depths around log8(n_p / 32) (at most 4 of them, within 2..8), the one
  * whose evaluation runs fastest here; later calls keep it.  The first call also
  * times the fused M2L launch with tiles of 3, 4, 5 and 6 MFMA row blocks (FP64: 3, 4
- * and 6) and keeps the fastest.  Drops the captured graph.  Errors as eifmm_set_points; after
+ * and 6, for the levels whose operands have 7 digits) and keeps the fastest.  Drops the captured graph.  Errors as eifmm_set_points; after
  * an error the batch must get points again before evaluating. */
 int eifmm_batch_set_points(eifmm_batch b, const double *const *xyz, void *stream);
 

@@ -848,6 +848,9 @@ __device__ inline void trsm_body(const SolveDesc &D, double *zs) {
 // The products of a row are added in another order, which changes FP64 results in the
 // last bits; the FP32 copy of a solve (mixed precision, uncompressed levels) would
 // change in its own last bit, so the mixed pass solves for What by the one-wave form.
+// Neither order is nearer to the exact solve: this only keeps the results that the mixed
+// pass had (on every mixed plan: the compressed ones' FP32 copy is taken after the
+// projection, where the order hardly shows, but they keep it too).
 constexpr int kSolveOwn = 5;  // tiles of a wave with their operators loaded ahead
 constexpr int kSolveFew = 1024;  // 16-column groups up to which the four-wave form serves
 __device__ inline void trsm4_body(const SolveDesc &D, double *zs) {
@@ -2319,7 +2322,7 @@ void launch_gemm(Plan &P, int first, int n, int tiles, int64_t units, hipStream_
   double *ws = P.run_ws ? P.run_ws : P.sk_ws;
   const size_t len = P.run_ws ? P.run_ws_len : stream_k_ws_len(P.sk_groups);
   // (mixed precision rounds the solved expansions to FP32, which would show an M2M sum in
-  // another order)
+  // another order, no better or worse: its results stay what they were)
   const bool few = MODE != MODE_M2M || P.cfg.precision == EIFMM_PREC_FP64;
   launch_gemm_tab<MODE>(P.job_dev + first, n, tiles, units, rbt, P.sk_groups, ws, len, few, nrb, s);
 }
@@ -2496,8 +2499,9 @@ void run_kind(Plan &P, int nrhs, const IoDesc &io, hipStream_t s) {
   // near field: with a far field to compute it runs on the plan's second stream
   // and L2P waits for it. In FP64 it starts after P2M, so that it overlaps M2M,
   // the solves and the projections (small MFMA launches that leave the vector
-  // units idle); the FP64 M2L holds 230 VGPRs per lane at two waves per SIMD,
-  // which leaves no room for the near-field waves beside it. In mixed precision
+  // units idle); the FP64 M2L's workgroups hold up to 256 registers per lane at two
+  // waves per SIMD and 148 KB of LDS, which leaves no registers for near-field waves
+  // beside them. In mixed precision
   // it starts just before M2L: the FP32 M2L and FP32 near-field waves fit on a
   // SIMD together, and the near field then fills the M2L's ramp-down as well.
   // With many right-hand sides the near field is long enough to take CUs from

@@ -415,10 +415,11 @@ struct Plan {
   int last_rhs = 0;
 };
 
-// Stream-K workspace of `groups` persistent workgroups: 2 pieces of the largest
-// tile (6 x 16 x 128 doubles) each
-// (2 pieces per workgroup for the even split, and room for the M2L tail's finer
-// pieces: 4 tiles of 6 x 16 x 128 doubles per workgroup, 201 MB for 512 groups)
+// Workspace of `groups` persistent workgroups for split tiles: the gathered GEMM's even
+// split writes 2 pieces of at most 4 x 16 x 128 doubles per workgroup; the M2L cuts the tiles
+// of its last round into as many parts as fit (split_tiles), 4 tiles of 6 x 16 x 128 doubles
+// per workgroup being room for 4 items per CU of its largest tile, 9 x 16 x 128 (201 MB for
+// 512 groups)
 inline size_t stream_k_ws_len(int groups) { return (size_t)4 * groups * 6 * 16 * 128; }
 // the last doubles of a Stream-K workspace hold the gathered GEMM's tail counter
 // (zero when the workspace is made)
@@ -452,7 +453,9 @@ void launch_m2l32(const GemmJob *jobs, int n, int tiles, int height, int dk, int
 // Whether the pass rounds a solved What to FP32: mixed, some level not compressed.  The
 // solve's condition (1e7 and more) carries a last-bit difference of W into that rounding
 // (6e-9 of f on 777 points), so P2M keeps there the library's exponential and the one sum
-// per leaf.  A compressed level rounds U^T What, where it does not show.
+// per leaf.  Neither W is nearer to the exact sums: this keeps the results that such plans
+// had, and costs them the segments' gain on crowded leaves.  A compressed level rounds
+// U^T What, where it does not show (2e-13 of f and less).
 inline bool what_rounded(const Plan &P) {
   if (P.cfg.precision != EIFMM_PREC_MIXED) return false;
   for (int k = 2; k <= P.depth; ++k)
