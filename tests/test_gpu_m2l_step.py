@@ -18,11 +18,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("nrhs", [1, 3])
-@pytest.mark.parametrize("kernel,param,tau", [
-    ("laplace", 0.0, 1e-6), ("yukawa", 30.0, 1e-6), ("gauss", 0.03, 1e-6), ("yukawa", 60.0, 1e-4),
-    ("advdiff", 20.0, 1e-4)])
-def test_m2l_step_far_offsets(kernel, param, tau, nrhs, oracle_lib):
+def check_step(oracle_lib, kernel, param, tau, nrhs, unit):
     import torch
 
     from paper_1408_0210_amd import eifmm as E
@@ -61,9 +57,25 @@ def test_m2l_step_far_offsets(kernel, param, tau, nrhs, oracle_lib):
                     sizes += np.sqrt(len(Y)) * np.abs(K).max(1) * np.abs(b).max()
                     rounding += (2 + 4 * np.abs(np.log(K)).max()) * np.sqrt(K ** 2 @ b ** 2)
                     checked += 1
-                tol = 2.0 ** -55 * (sizes + 8 * np.abs(ref).astype(np.float64) + rounding)
+                tol = unit * (sizes + 8 * np.abs(ref).astype(np.float64) + rounding)
                 err = np.abs(g[box] - ref).astype(np.float64)
                 e, t = np.sqrt((err ** 2).mean()), np.sqrt((tol ** 2).mean())
                 assert e <= t, (kernel, param, k, int(box), r, e / max(t, 1e-300))
     assert checked >= 8 * nrhs
     plan.close()
+
+
+@pytest.mark.parametrize("nrhs", [1, 3])
+@pytest.mark.parametrize("kernel,param,tau", [
+    ("laplace", 0.0, 1e-6), ("yukawa", 30.0, 1e-6), ("gauss", 0.03, 1e-6), ("yukawa", 60.0, 1e-4),
+    ("advdiff", 20.0, 1e-4)])
+def test_m2l_step_far_offsets(kernel, param, tau, nrhs, oracle_lib):
+    check_step(oracle_lib, kernel, param, tau, nrhs, 2.0 ** -55)
+
+
+# one 64-element chunk and two, tiles of 3, 4, 6 and 8 row blocks, 8 digits of a few blocks:
+# fewer rows and terms average less, so the bound is the digits' own worst rounding, 2^-54
+@pytest.mark.parametrize("kernel,param,tau", [
+    ("gauss", 1.0, 1e-6), ("mq", 1.0, 1e-9), ("laplace", 0.0, 1e-3), ("gauss", 0.1, 1e-6)])
+def test_m2l_step_small_sizes(kernel, param, tau, oracle_lib):
+    check_step(oracle_lib, kernel, param, tau, 3, 2.0 ** -54)
