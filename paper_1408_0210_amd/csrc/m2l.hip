@@ -24,13 +24,16 @@
 // precision, uncompressed: 1/r 0.2-0.3, cos(20 r)/r 0.3-0.5, e^-r^2 0.4-0.6, e^-8r/r
 // 0.5-0.8, e^-12r/r 0.8-1.5, e^(-r^2/0.1) 0.7-1.9, e^-30r/r 0.9-4.7, e^-60r/r 0.4-18 with
 // 7 digits, and 0.01-0.2 with 8 for all of these; compressed: 1/r 0.6-1.0, cos(20 r)/r
-// 1.3-1.9, e^(-r^2/0.01) 4.4-8.4, and 0.04-0.1 with 8.  Measured against an 80-bit
-// evaluation with the operators and sources of the pass (tau 1e-6, random boxes): 1/r
-// at rank 128 1.1e-15 relative against 5.3e-15 for the chain of FP64 FMAs, e^-r/r
-// 0.8e-15 / 3.9e-15, cos(20 r)/r 1.1e-15 / 6.9e-15, 1/r uncompressed (d = 287) 0.6e-15 /
-// 8.0e-15, e^(-r^2 / 0.01) 7.5e-15 / 8.0e-15.
+// 1.3-1.9, e^(-r^2/0.01) 4.4-8.4, and 0.04-0.1 with 8.  Whole interaction lists (189
+// offsets, boxes of 30 random points, tau 1e-6, against an 80-bit evaluation): 1/r at rank
+// 128 0.75e-15 relative against 5.3e-15 for the chain, e^-r/r 0.6e-15 / 5.5e-15, cos(20 r)/r
+// 0.6e-15 / 6.9e-15, 1/r uncompressed (d = 287) 0.5e-15 / 8.0e-15, e^-r^2 0.5e-15 / 3.5e-15,
+// e^(-r^2/0.01) 0.4e-15 with 8 digits (1.8e-15 with 7) / 8.0e-15.
+// (The method is the splitting of Ozaki, Ogita, Oishi and Rump, "Error-free transformations
+// of matrix multiplication by using fast routines of matrix multiplication and its
+// applications", 2012, with slices of fixed width.)
 //
-// Time of the launch against tiles of FP64 MFMAs: 2.49 ms against 3.96 on 1e6 uniform
+// Time of the launch against tiles of FP64 MFMAs: 2.50 ms against 3.96 on 1e6 uniform
 // points (1/r, rank 128, levels 2..5), 2.05 against 2.88 on 2e5 points uncompressed
 // (d = 287, levels 2..4), 0.38 against 0.67 on 2000 points (d = 287, levels 2 and 3).
 // The matrix cores are busy half of the time (1.73e8 products of 16 cycles); copies that

@@ -1,5 +1,5 @@
-// m2l_tile.hpp -- what the two M2L kernels share: a tile's columns and terms, the loads
-// that go straight to LDS, and the sum of split tiles (m2l.hip, m2l32.hip).
+// m2l_tile.hpp -- what the M2L kernels share: a tile's columns and terms, the loads that go
+// straight to LDS, and the sum of split tiles.
 #pragma once
 #include <climits>
 #include <type_traits>
