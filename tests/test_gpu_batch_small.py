@@ -74,3 +74,28 @@ def test_small_operators_not_finite_potential():
     B.set_points([pts])
     assert np.isnan(B.evaluate([sig])[0].cpu().numpy()[far]).all()
     B.close()
+
+
+@pytest.mark.parametrize("kernel,param,tau,depth", [
+    ("sqdist", 0.0, 1e-6, 3), ("gauss", 0.02, 1e-4, 2), ("laplace", 0.0, 1e-3, 2)])
+def test_batch_of_one_kind_of_level(kernel, param, tau, depth):
+    """Only small operators, only steep levels, only levels of seven digits: the other
+    launches are empty."""
+    import torch
+
+    from paper_1408_0210_amd import eifmm as E
+    from paper_1408_0210_amd import workloads as W
+    ns = (1500, 700)
+    xs = [torch.from_numpy(W.uniform_points(n, 360 + n)).cuda() for n in ns]
+    ss = [torch.from_numpy(W.potentials(n, 370 + n)).cuda() for n in ns]
+    B = E.Batch([dict(kernel=kernel, param=param, n=n, tau=tau, depth=depth) for n in ns])
+    B.set_points(xs)
+    for rep in range(2):
+        fs = B.evaluate(ss)
+    for i, n in enumerate(ns):
+        plan = E.Plan(kernel, param, [0, 0, 0], 1.0, n, depth, tau)
+        plan.set_points(xs[i])
+        own = plan.evaluate(ss[i]).cpu().numpy()
+        assert rel(fs[i].cpu().numpy(), own) < 1e-12, (kernel, i)
+        plan.close()
+    B.close()
