@@ -4,14 +4,14 @@
 // rank of a non-empty box in key order; dp_k = d_k padded to 16 with zeros).
 // Steps and kernels:
 //   near field, eq. (13)        k_p2p64 / k_p2p32   one wave per 64 targets of a leaf
-//   1  P2M                      k_p2m               one workgroup per leaf
+//   1  P2M                      k_p2m               one workgroup per leaf or segment of it
 //   2  M2M (Sec. 4.1 operators) k_gemm<MODE_M2M>    MFMA, 8 children per parent
 //   3  What = Delta W           k_trsm              blocked triangular solves (MFMA)
 //   4  M2L (Sec. 4.2 matrices)  189 offsets per class; FP64: k_m2l8 (m2l.hip, int8 MFMA),
 //                               mixed: k_m2l32 (m2l32.hip, FP32 MFMA)
 //   5  L2L                      k_gemm<MODE_L2L>    MFMA, adds g
 //   6  lhat = Delta^T l         k_trsm
-//   7  L2P and f = f_far + f_near, input order  k_l2p  one wave per 64 targets
+//   7  L2P and f = f_far + f_near, input order  k_l2p  one wave per 32 targets
 #include <algorithm>
 #include <cfloat>
 #include <climits>
