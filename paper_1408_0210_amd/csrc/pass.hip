@@ -3,7 +3,7 @@
 // Expansions of level k live in slot-major arrays [slot][rhs][dp_k] (slot =
 // rank of a non-empty box in key order; dp_k = d_k padded to 16 with zeros).
 // Steps and kernels:
-//   near field, eq. (13)        k_p2p64 / k_p2p32   one wave per 64 targets of a leaf
+//   near field, eq. (13)        k_p2p64 / k_p2p32   one wave per 32 targets of a leaf
 //   1  P2M                      k_p2m               one workgroup per leaf or segment of it
 //   2  M2M (Sec. 4.1 operators) k_gemm<MODE_M2M>    MFMA, 8 children per parent
 //   3  What = Delta W           k_trsm              blocked triangular solves (MFMA)
